@@ -415,7 +415,7 @@ mrstat_status adjoint(mrstat_ctx ctx, const float* theta, const void* w, float* 
         HIP_TRY(TRACED(MRSTAT_K_YADJ, launch_rd_adj(d, nc, ntr, p.adj_chunks, ctx->trains(), ctx->f16, theta,
                                                     ctx->coil, ctx->mask, ctx->rd_db0, ctx->db0_unit, ctx->deytab(),
                                                     ctx->rdW(), ctx->apart(), ctx->st.te, ctx->rd_tmax, s)));
-        HIP_TRY(TRACED(MRSTAT_K_FINISH, launch_jhw_finish(d, p, ctx->apart(), theta, ctx->mask, param_mask, g,
+        HIP_TRY(TRACED(MRSTAT_K_FINISH, launch_jhw_finish(d, p.adj_chunks, ctx->apart(), theta, ctx->mask, param_mask, g,
                                                           dir, dir ? ctx->red() : nullptr, s, step, res)));
         return MRSTAT_OK;
     }
@@ -423,7 +423,7 @@ mrstat_status adjoint(mrstat_ctx ctx, const float* theta, const void* w, float* 
         HIP_TRY(TRACED(MRSTAT_K_NC_ADJ, launch_nc_adj(d, ctx->enc, ntr, p.adj_chunks, ctx->trains(), ctx->f16,
                                                       ctx->coil, ctx->mask, ctx->dax(), ctx->day(),
                                                       (const float2*)w, ctx->apart(), s)));
-        HIP_TRY(TRACED(MRSTAT_K_FINISH, launch_jhw_finish(d, p, ctx->apart(), theta, ctx->mask, param_mask, g,
+        HIP_TRY(TRACED(MRSTAT_K_FINISH, launch_jhw_finish(d, p.adj_chunks, ctx->apart(), theta, ctx->mask, param_mask, g,
                                                           dir, dir ? ctx->red() : nullptr, s, step, res)));
         return MRSTAT_OK;
     }
@@ -431,9 +431,34 @@ mrstat_status adjoint(mrstat_ctx ctx, const float* theta, const void* w, float* 
                                                    ctx->bfrag(1), ctx->W(), s)));
     HIP_TRY(TRACED(MRSTAT_K_YADJ, launch_ystage_adj(d, p, ctx->trains(), ctx->f16, ntr, ctx->coil, ctx->mask,
                                                     ctx->deytab(), ctx->W(), ctx->apart(), s)));
-    HIP_TRY(TRACED(MRSTAT_K_FINISH, launch_jhw_finish(d, p, ctx->apart(), theta, ctx->mask, param_mask, g,
+    HIP_TRY(TRACED(MRSTAT_K_FINISH, launch_jhw_finish(d, p.adj_chunks, ctx->apart(), theta, ctx->mask, param_mask, g,
                                                       dir, dir ? ctx->red() : nullptr, s, step, res)));
     return MRSTAT_OK;
+}
+
+// The CG product q = Re(J^H J) dir with the CG partials left in ctx->red()
+// (step for the trust region's, res for the one-launch update's): one pass
+// over the trains for Cartesian contexts without readout dynamics, else J dir
+// followed by the adjoint. The FP16 contraction keeps the two products, whose
+// result carries that option's rounding. The chunk partials of the one pass
+// take the place of the line search's value train, written after CG.
+mrstat_status normal_product(mrstat_ctx ctx, const float* theta, const float* dir, float* q, int param_mask,
+                             const float* step, const float* res, hipStream_t s)
+{
+    const Dims& d = ctx->d;
+    const int chunks = ctx->nc || ctx->rd_nq > 0 || ctx->enc == MRSTAT_ENC_FP16 ? 0 : normal_chunks(d);
+    if (chunks > 0) {
+        float* apart = (float*)ctx->trial_m();
+        HIP_TRY(TRACED(MRSTAT_K_YADJ, launch_normal(d, ctx->lin_ntr, ctx->trains(), ctx->f16, theta, dir, ctx->mask,
+                                                    ctx->deytab(), apart, s)));
+        HIP_TRY(TRACED(MRSTAT_K_FINISH, launch_jhw_finish(d, chunks, apart, theta, ctx->mask, param_mask, q, dir,
+                                                          ctx->red(), s, step, res)));
+        return MRSTAT_OK;
+    }
+    mrstat_status st = forward(ctx, ctx->lin_ntr == 4 ? 1 : 3, 1, ctx->trains(), theta, dir, nullptr, ctx->y(),
+                               nullptr, s);
+    if (st != MRSTAT_OK) return st;
+    return adjoint(ctx, theta, ctx->y(), q, param_mask, s, dir, step, res);
 }
 
 }  // namespace
@@ -926,9 +951,7 @@ mrstat_status mrstat_gn_step(mrstat_ctx ctx, float* d_theta, const void* d_data,
     // CG on Re(J^H J) p = -g with device-resident FP64 scalars.
     HIP_TRY(TRACED(MRSTAT_K_VECTOR, launch_cg_init(d, g, step, res, dir, sc, ctx->red(), s)));
     for (int it = 0; it < o->n_cg; ++it) {
-        st = forward(ctx, ntr == 4 ? 1 : 3, 1, ctx->trains(), d_theta, dir, nullptr, ctx->y(), nullptr, s);
-        if (st != MRSTAT_OK) return st;
-        st = adjoint(ctx, d_theta, ctx->y(), q, o->param_mask, s, dir, nullptr, res);
+        st = normal_product(ctx, d_theta, dir, q, o->param_mask, nullptr, res, s);
         if (st != MRSTAT_OK) return st;
         HIP_TRY(TRACED(MRSTAT_K_VECTOR, launch_cg_update(d, q, step, res, dir, sc, ctx->red(), it, s)));
     }
@@ -1026,9 +1049,7 @@ mrstat_status mrstat_tr_step(mrstat_ctx ctx, float* d_theta, const void* d_data,
     HIP_TRY(TRACED(MRSTAT_K_VECTOR, launch_cg_init(d, g, step, res, dir, sc, ctx->red(), s)));
     HIP_TRY(TRACED(MRSTAT_K_VECTOR, launch_tr_init(sc, delta * delta, s)));
     for (int it = 0; it < o->n_cg; ++it) {
-        st = forward(ctx, mode_jv, 1, ctx->trains(), d_theta, dir, nullptr, ctx->y(), nullptr, s);
-        if (st != MRSTAT_OK) return st;
-        st = adjoint(ctx, d_theta, ctx->y(), q, o->param_mask, s, dir, step);
+        st = normal_product(ctx, d_theta, dir, q, o->param_mask, step, nullptr, s);
         if (st != MRSTAT_OK) return st;
         HIP_TRY(TRACED(MRSTAT_K_VECTOR, launch_tr_update(d, q, step, res, dir, sc, ctx->red(), it, s)));
     }

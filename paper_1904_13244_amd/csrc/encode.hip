@@ -918,8 +918,11 @@ __global__ void wsum_kernel(float2* __restrict__ W, int nsplit, size_t count)
 // step . dir (the trust-region CG's, with its boundary test); 3 = dir . g,
 // dir . dir, res . res, res . g and g . g (what the one-launch CG update
 // needs for alpha and beta).
-template <int CURV, int NP>
-__global__ __launch_bounds__(256) void jhw_finish_kernel(const float* __restrict__ apart, int n_chunk,
+// G groups of 256 threads share a block's 256 voxels, group k summing chunks
+// k, k + G, ...: with the one-pass CG product's 16 to 32 chunks one thread per
+// voxel is a serial chain of loads.
+template <int CURV, int NP, int G>
+__global__ __launch_bounds__(256 * G) void jhw_finish_kernel(const float* __restrict__ apart, int n_chunk,
                                                          const float* __restrict__ theta,
                                                          const uint8_t* __restrict__ mask, int param_mask,
                                                          float* __restrict__ g, int nv,
@@ -930,14 +933,14 @@ __global__ __launch_bounds__(256) void jhw_finish_kernel(const float* __restrict
 {
     constexpr int PL = NP == 6 ? 10 : 8;   // planes per chunk
     constexpr int NPART = CURV == 3 ? 5 : 3;   // partial kinds
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
+    const int vl = threadIdx.x % 256, grp = threadIdx.x / 256;
+    const int j = blockIdx.x * 256 + vl;
+    __shared__ float gs[G > 1 ? (G - 1) * PL * 256 : 1];
     double acc[NPART];
 #pragma unroll
     for (int k = 0; k < NPART; ++k) acc[k] = 0.0;
+    float A[PL];
     if (j < nv) {
-        const bool on = mask == nullptr || mask[j] != 0;
-        const float rr = theta[3 * nv + j], ri = theta[4 * nv + j];
-        float A[PL];
 #pragma unroll
         for (int q = 0; q < PL; ++q) A[q] = 0.f;
         // The dm/dB1 pair (A[6], A[7]) is read only when B1 is reconstructed
@@ -956,22 +959,36 @@ __global__ __launch_bounds__(256) void jhw_finish_kernel(const float* __restrict
                 t[9] = f5 ? apart[((size_t)ch * PL + 9) * nv + j] : 0.f;
             }
         };
-        int ch = 0;
-        for (; ch + 3 <= n_chunk; ch += 3) {
+        int ch = grp;
+        for (; ch + 2 * G < n_chunk; ch += 3 * G) {
             float t[3][PL];
 #pragma unroll
-            for (int c = 0; c < 3; ++c) load(ch + c, t[c]);
+            for (int c = 0; c < 3; ++c) load(ch + c * G, t[c]);
 #pragma unroll
             for (int c = 0; c < 3; ++c)
 #pragma unroll
                 for (int q = 0; q < PL; ++q) A[q] += t[c][q];
         }
-        for (; ch < n_chunk; ++ch) {
+        for (; ch < n_chunk; ch += G) {
             float t[PL];
             load(ch, t);
 #pragma unroll
             for (int q = 0; q < PL; ++q) A[q] += t[q];
         }
+    }
+    if constexpr (G > 1) {
+        if (grp > 0 && j < nv)
+#pragma unroll
+            for (int q = 0; q < PL; ++q) gs[((grp - 1) * PL + q) * 256 + vl] = A[q];
+        __syncthreads();
+        if (grp == 0 && j < nv)
+            for (int k = 1; k < G; ++k)
+#pragma unroll
+                for (int q = 0; q < PL; ++q) A[q] += gs[((k - 1) * PL + q) * 256 + vl];
+    }
+    if (grp == 0 && j < nv) {
+        const bool on = mask == nullptr || mask[j] != 0, f5 = (param_mask >> 5) & 1;
+        const float rr = theta[3 * nv + j], ri = theta[4 * nv + j];
         // Rows of parameters outside param_mask are zero.
         float gq[NP];
 #pragma unroll
@@ -1007,7 +1024,7 @@ __global__ __launch_bounds__(256) void jhw_finish_kernel(const float* __restrict
         for (int k = 0; k < NPART; ++k)
             for (int off = 32; off > 0; off >>= 1) acc[k] += __shfl_xor(acc[k], off);
         const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-        if (lane == 0)
+        if (lane == 0 && wave < 4)
 #pragma unroll
             for (int k = 0; k < NPART; ++k) sh[k][wave] = acc[k];
         __syncthreads();
@@ -1849,26 +1866,28 @@ hipError_t launch_ystage_adj(const Dims& d, const YPlan& p, const void* trains, 
                : adj_typed(d, p, static_cast<const float*>(trains), ntr_trains, coil, mask, eytab, W, apart, s);
 }
 
-hipError_t launch_jhw_finish(const Dims& d, const YPlan& p, const float* apart, const float* theta,
+hipError_t launch_jhw_finish(const Dims& d, int n_chunk, const float* apart, const float* theta,
                              const uint8_t* mask, int param_mask, float* g, const float* dir,
                              double* part, hipStream_t s, const float* step, const float* res)
 {
     const int nb = ceil_div(d.nv, 256);
     if (dir != nullptr && step == nullptr && res == nullptr) return hipErrorInvalidValue;
-#define FINISH(NP)                                                                                       \
+#define FINISH(NP, G)                                                                                    \
     if (dir != nullptr && step != nullptr)                                                               \
-        jhw_finish_kernel<2, NP><<<nb, 256, 0, s>>>(apart, p.adj_chunks, theta, mask, param_mask, g, d.nv, \
-                                                    dir, step, nullptr, part);                           \
+        jhw_finish_kernel<2, NP, G><<<nb, 256 * G, 0, s>>>(apart, n_chunk, theta, mask, param_mask, g,   \
+                                                           d.nv, dir, step, nullptr, part);              \
     else if (dir != nullptr)                                                                             \
-        jhw_finish_kernel<3, NP><<<nb, 256, 0, s>>>(apart, p.adj_chunks, theta, mask, param_mask, g, d.nv, \
-                                                    dir, nullptr, res, part);                            \
+        jhw_finish_kernel<3, NP, G><<<nb, 256 * G, 0, s>>>(apart, n_chunk, theta, mask, param_mask, g,   \
+                                                           d.nv, dir, nullptr, res, part);               \
     else                                                                                                 \
-        jhw_finish_kernel<0, NP><<<nb, 256, 0, s>>>(apart, p.adj_chunks, theta, mask, param_mask, g, d.nv, \
-                                                    nullptr, nullptr, nullptr, nullptr);
+        jhw_finish_kernel<0, NP, G><<<nb, 256 * G, 0, s>>>(apart, n_chunk, theta, mask, param_mask, g,   \
+                                                           d.nv, nullptr, nullptr, nullptr, nullptr);
     if (d.np == 6) {
-        FINISH(6)
+        FINISH(6, 1)
+    } else if (n_chunk > 9) {
+        FINISH(5, 4)
     } else {
-        FINISH(5)
+        FINISH(5, 1)
     }
 #undef FINISH
     return hipGetLastError();

@@ -42,6 +42,15 @@ struct SeqTimes {
     float tr, te, tinv;
 };
 
+// ---------------------------------------------------------------- normal operator
+// Chunk partials of the CG product Re(J^H J) v in one pass over the trains
+// (normal.hip), in the adjoint y-stage's layout with 8 planes per chunk (the
+// dm/dB1 pair unwritten with ntr 3). normal_chunks: the number of chunks, at
+// most n_tr / 8, or 0 when the problem takes the two products instead.
+int normal_chunks(const Dims& d);
+hipError_t launch_normal(const Dims& d, int ntr, const void* trains, bool f16, const float* theta, const float* v,
+                         const uint8_t* mask, const float2* eytab, float* apart, hipStream_t s);
+
 // ---------------------------------------------------------------- readout dynamics
 // Term-wise y-stages and sample weighting of the readout-dynamics expansion
 // (readout.hip): nq power-series sums per voxel column and TR, economised to
@@ -173,7 +182,7 @@ hipError_t launch_ystage_adj(const Dims& d, const YPlan& p, const void* trains, 
                              const float2* coil, const uint8_t* mask, const float2* eytab,
                              const float2* W, float* apart, hipStream_t s);
 
-// g[np][nv] = Re(J^H w) from the chunk partials (sums in chunk order; 8
+// g[np][nv] = Re(J^H w) from the partials of n_chunk chunks (8
 // planes per chunk, 10 with Delta B0 fitted); rows of parameters outside
 // param_mask (and masked voxels) are zero, and the dm/dB1 partials are read
 // only when B1 is in param_mask.
@@ -182,7 +191,7 @@ hipError_t launch_ystage_adj(const Dims& d, const YPlan& p, const void* trains, 
 // step non-null, step . dir in part[2 nblocks + b], or, with res non-null,
 // res . res, res . g and g . g in planes 2, 3 and 4 (dir with neither is
 // hipErrorInvalidValue).
-hipError_t launch_jhw_finish(const Dims& d, const YPlan& p, const float* apart, const float* theta,
+hipError_t launch_jhw_finish(const Dims& d, int n_chunk, const float* apart, const float* theta,
                              const uint8_t* mask, int param_mask, float* g, const float* dir,
                              double* part, hipStream_t s, const float* step = nullptr,
                              const float* res = nullptr);
