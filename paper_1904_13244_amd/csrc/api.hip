@@ -375,6 +375,7 @@ mrstat_status forward(mrstat_ctx ctx, int mode_y, int mode_x, const void* trains
         int nred = 0;
         HIP_TRY(TRACED(MRSTAT_K_NC_FWD, launch_nc_fwd(d, ctx->enc, mode_y, mode_x, trains, ctx->f16, theta, v,
                                                       ctx->coil, ctx->mask, ctx->dax(), ctx->day(), ctx->ncx(),
+                                                      ctx->at<uint16_t>(ctx->L.hbuf),
                                                       (const float2*)data, (float2*)out, ctx->red(), &nred, s)));
         if (mode_x == 0 && f_out)
             HIP_TRY(TRACED(MRSTAT_K_VECTOR, launch_sum_partials(ctx->red(), nred, f_out, s)));
@@ -422,7 +423,7 @@ mrstat_status adjoint(mrstat_ctx ctx, const float* theta, const void* w, float* 
     if (ctx->nc) {
         HIP_TRY(TRACED(MRSTAT_K_NC_ADJ, launch_nc_adj(d, ctx->enc, ntr, p.adj_chunks, ctx->trains(), ctx->f16,
                                                       ctx->coil, ctx->mask, ctx->dax(), ctx->day(),
-                                                      (const float2*)w, ctx->apart(), s)));
+                                                      (const float2*)w, ctx->ncx(), ctx->apart(), s)));
         HIP_TRY(TRACED(MRSTAT_K_FINISH, launch_jhw_finish(d, p.adj_chunks, ctx->apart(), theta, ctx->mask, param_mask, g,
                                                           dir, dir ? ctx->red() : nullptr, s, step, res)));
         return MRSTAT_OK;
@@ -1136,7 +1137,7 @@ mrstat_status mrstat_rho_init(mrstat_ctx ctx, float* d_theta, const void* d_data
         } else if (ctx->nc) {
             HIP_TRY(TRACED(MRSTAT_K_NC_ADJ, launch_nc_adj(d, ctx->enc, 1, p.adj_chunks, ctx->trains(), ctx->f16,
                                                           ctx->coil, ctx->mask, ctx->dax(), ctx->day(), w,
-                                                          ctx->apart(), s)));
+                                                          ctx->ncx(), ctx->apart(), s)));
         } else {
             HIP_TRY(TRACED(MRSTAT_K_XADJ, launch_xgemm_adj(d, p, ctx->enc, w, ctx->dextab(), ctx->bfrag(1),
                                                            ctx->W(), s)));

@@ -23,19 +23,21 @@ struct Dims {
 // kx / nx and ky / ny (kx, ky in cycles per field of view); nx <= 256.
 // Forward: mode_y 0 (signal, m train) or 1 / 3 (J v direction, with or
 // without dm/dB1); mode_x as for launch_xgemm_fwd (0 residual with FP64
-// partials into red, their count in *nred; 1 -s; 2 s). enc 0 FP32 MFMA, 1
-// split-BF16 MFMA. Adjoint: chunk partials of A_p = sum_n mu_p V (ntr 4, 3
+// partials into red, their count in *nred; 1 -s; 2 s). enc 0 FP32 and 1
+// split-BF16 run the same split-FP16 products, whose error is FP32's.
+// Adjoint: V workspace [T][nv], chunk partials of A_p = sum_n mu_p V (ntr 4, 3
 // or 1) in the Cartesian adjoint's layout, with `chunks` TR chunks.
 int nc_adj_chunks(const Dims& d);
 int nc_fwd_blocks(const Dims& d);
-// X: workspace [T][nv] complex for the forward's voxel values.
+// X: workspace of T nv 8 bytes for the forward's voxel values, small: nv 512
+// bytes more of them.
 hipError_t launch_nc_fwd(const Dims& d, int enc, int mode_y, int mode_x, const void* trains, bool f16,
                          const float* theta, const float* v, const float2* coil, const uint8_t* mask,
-                         const double* ax, const double* ay, float2* X, const float2* data, float2* out,
+                         const double* ax, const double* ay, void* X, void* small, const float2* data, float2* out,
                          double* red, int* nred, hipStream_t s);
 hipError_t launch_nc_adj(const Dims& d, int enc, int ntr, int chunks, const void* trains, bool f16,
                          const float2* coil, const uint8_t* mask, const double* ax, const double* ay,
-                         const float2* w, float* apart, hipStream_t s);
+                         const float2* w, float2* V, float* apart, hipStream_t s);
 
 // Per-voxel EPG timing constants shared by all voxels.
 struct SeqTimes {

@@ -8,25 +8,26 @@
 //            X[iy,ix] the voxel values of the TR;
 //   adjoint  V[iy,ix] = sum_k G[k,iy] H[k,ix],  G = conj(Ey) w, H = conj(Ex),
 //            then A_p[j] += mu_p[n,j] V[j] over the TRs of a chunk.
-// Both run on the matrix cores in the real 2 x 2-block form of a complex
-// product, with every phase generated on the fly (argument reduced in FP64,
-// sin/cos of the reduced fraction in FP32):
-//   ENC 0: v_mfma_f32_16x16x4_f32 (FP32 operands);
-//   ENC 1: v_mfma_f32_16x16x32_bf16 on split operands, hi*hi + hi*lo + lo*hi.
-// MFMA operand layouts (as in encode.hip): 16x16x4 f32: A lane l -> (row
-// l%16, k l/16), B lane l -> (k l/16, col l%16); 16x16x32: A lane l -> (row
-// l%16, k 8(l/16)..+7), B lane l -> (k 8(l/16)..+7, col l%16); D lane l ->
-// (rows 4(l/16)+i, col l%16) for both.
+// Both run on the matrix cores as four real products (re re, im im, re im, im
+// re), with every phase generated on the fly (argument reduced in FP64,
+// sin/cos of the reduced fraction in FP32, neighbours by angle addition).
+// MFMA operand layouts (16x16x32): A lane l -> (row l%16, k 8(l/16)..+7), B
+// lane l -> (k 8(l/16)..+7, col l%16); D lane l -> (rows 4(l/16)+i, col l%16).
+// Measured at 224 x 224, 1120 spokes of 448 samples (FP32 MFMA 16x16x4 tiles
+// of 64 samples and 64 x 32 voxels, as before; now): voxel values 0.31 / 0.32
+// ms, forward 3.60 / 0.75, adjoint with the trains 5.2 / 1.03 + 0.29 (the
+// split-BF16 option's tiles 0.31 + 1.39 / 2.94); errors against the FP64 sums
+// at 36 x 70, 40 spokes: J v 5.6e-7 / 5.6e-7, J^H w 6.3e-7 / 6.0e-7.
 #include "mrstat_internal.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace mrstat {
 
 namespace {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 // exp(-2 pi i a x) for an FP64 coefficient a and an integer position x: the
 // product is reduced to a fraction of a cycle in FP64, then sin and cos of pi
@@ -45,669 +46,806 @@ __device__ __forceinline__ float2 cmul(float2 a, float2 b)
     return make_float2(fmaf(a.x, b.x, -a.y * b.y), fmaf(a.x, b.y, a.y * b.x));
 }
 
-__device__ __forceinline__ unsigned int bf16_rne(float x)
+// ------------------------------------------------------------------------
+// Split operands. The products run on v_mfma_f32_16x16x32_f16: each FP32
+// operand is written as hi + lo, hi = fp16(v), lo = fp16(v - hi), and the
+// product as hi hi + hi lo + lo hi with FP32 accumulation. Operands are first
+// scaled by powers of two (phases by 2^8, voxel values so that the largest of
+// an image row lies in [2^10, 2^11)), which keeps hi and the leading bits of
+// lo away from fp16's subnormals: 22 bits per operand, a relative error of
+// about 2^-23 against 2^-24 for FP32 operands, without its K-long serial sums.
+// ------------------------------------------------------------------------
+typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+typedef unsigned u4 __attribute__((ext_vector_type(4)));
+
+constexpr float kPhaseScale = 256.f;
+
+__device__ __forceinline__ void split_h(float a, float b, unsigned& hi, unsigned& lo)
 {
-    const unsigned int u = __float_as_uint(x);
-    return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
+    const h2 h = {(_Float16)a, (_Float16)b};
+    const h2 l = {(_Float16)(a - (float)h[0]), (_Float16)(b - (float)h[1])};
+    hi = __builtin_bit_cast(unsigned, h);
+    lo = __builtin_bit_cast(unsigned, l);
 }
 
-// (re, im) -> hi word (bf16 re | bf16 im << 16) and lo word of the remainders.
-__device__ __forceinline__ uint2 split_pair(float re, float im)
+__device__ __forceinline__ f4 mma(u4 a, u4 b, f4 c)
 {
-    const unsigned int hr = bf16_rne(re), hi = bf16_rne(im);
-    const unsigned int lr = bf16_rne(re - __uint_as_float(hr << 16));
-    const unsigned int li = bf16_rne(im - __uint_as_float(hi << 16));
-    return make_uint2(hr | (hi << 16), lr | (li << 16));
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8, a), __builtin_bit_cast(h8, b), c, 0, 0, 0);
 }
 
-__device__ __forceinline__ f4 mma_bf16(const uint4& a, const uint4& b, f4 c)
+// 2^e that brings m >= 0 into [2^10, 2^11) (1 for m = 0 or not finite; e is
+// bounded so that 2^-e kPhaseScale^-1 stays a normal number).
+__device__ __forceinline__ float pow2_scale(float m)
 {
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b),
-                                                   c, 0, 0, 0);
+    const int b = (int)(__float_as_uint(m) >> 23);   // biased exponent
+    if (m == 0.f || b == 255) return 1.f;
+    const int e = min(137 - b, 118);
+    return __uint_as_float((unsigned)(e + 127) << 23);
 }
 
-// Real-form B words of the forward and adjoint: a word holds (re, im) of one
-// complex operand entry; column parity b = 0 needs (re, -im), b = 1 (im, re).
-__device__ __forceinline__ uint4 bform(uint4 w, int b)
+typedef __attribute__((address_space(3))) char* lptr;
+__device__ __forceinline__ unsigned lds_addr(const void* p) { return (unsigned)(size_t)(lptr)(char*)p; }
+
+// 16 bytes per lane from global memory to LDS (lane l to base + 16 l), past
+// the registers.
+__device__ __forceinline__ void to_lds16(const void* g, void* wave_base)
 {
-    if (b == 0) return make_uint4(w.x ^ 0x80000000u, w.y ^ 0x80000000u, w.z ^ 0x80000000u, w.w ^ 0x80000000u);
-    return make_uint4((w.x >> 16) | (w.x << 16), (w.y >> 16) | (w.y << 16), (w.z >> 16) | (w.z << 16),
-                      (w.w >> 16) | (w.w << 16));
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g,
+                                     (__attribute__((address_space(3))) void*)wave_base, 16, 0, 0);
 }
 
-template <typename TT>
-__device__ __forceinline__ float ld_train(const TT* p) { return (float)*p; }
+// Four MFMA fragments a fixed distance apart. In one block with its wait: with
+// loads to LDS in flight, a compiler-made LDS read would wait for all of them.
+template <int STEP> __device__ __forceinline__ void read_frag4(u4 (&f)[4], unsigned at)
+{
+    asm volatile("ds_read_b128 %0, %4\n ds_read_b128 %1, %4 offset:%5\n ds_read_b128 %2, %4 offset:%6\n"
+                 "ds_read_b128 %3, %4 offset:%7\n s_waitcnt lgkmcnt(0)"
+                 : "=&v"(f[0]), "=&v"(f[1]), "=&v"(f[2]), "=&v"(f[3])
+                 : "v"(at), "n"(STEP), "n"(2 * STEP), "n"(3 * STEP)
+                 : "memory");
+}
 
 // ------------------------------------------------------------------------
-// Voxel values of the forward, once per product: X[n][j] = i rho_j mu0[n,j]
-// (NTRV 1, the signal) or i (rho_j sum_p v_p dm_p/dtheta_p + (v3 + i v4) mu0)
-// (NTRV 4: all tangents; 3: without dm/dB1, whose direction entry is 0);
-// zero for masked voxels. A streaming pass over the trains. SPLIT (the
-// split-BF16 forward without coil weights) stores each value already split
-// into its (hi, lo) words instead of the FP32 pair, the same 8 bytes.
+// Voxel values of the forward, once per product: X[c][n][iy][ix] =
+// C_c[j] i rho_j mu0[n,j] (NTRV 1, the signal) or C_c[j] i (rho_j sum_p v_p
+// dm_p/dtheta_p + (v3 + i v4) mu0) (NTRV 4: all tangents; 3: without dm/dB1,
+// whose direction entry is 0); zero for masked voxels. A wave takes one image
+// row of NC_XT TRs (4 columns per lane) and every coil of the pass: scale,
+// split, four planes (re hi, re lo, im hi, im lo), zero past nx; the inverse
+// scale undoes both operands'. A streaming pass over the trains.
 // ------------------------------------------------------------------------
-template <int NTRV, typename TT, bool SPLIT>
+constexpr int NC_XT = 4;
+
+// One TR and coil of split voxel values: four planes of [ny][nx8] fp16, then
+// ny floats of inverse scales (16-byte multiple). Records [0, split) lie at
+// `a`, the others at `b`.
+struct XStore {
+    char *a, *b;
+    int split, nx8;
+    size_t rec;
+    __host__ __device__ char* at(int i) const { return i < split ? a + i * rec : b + (i - split) * rec; }
+};
+__host__ __device__ inline size_t x_planes(int ny, int nx8) { return (size_t)8 * ny * nx8; }
+
+template <int NTRV, typename TT>
 __global__ __launch_bounds__(256) void nc_x_kernel(const TT* __restrict__ trains, const float* __restrict__ theta,
                                                    const float* __restrict__ v, const uint8_t* __restrict__ mask,
-                                                   float2* __restrict__ X, int nv, int T)
+                                                   const float2* __restrict__ coil, XStore X, int nx, int ny, int nv,
+                                                   int T, int n_first, int n_count, int n_coils)
 {
-    const size_t count = (size_t)T * nv, plane = count;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += (size_t)gridDim.x * blockDim.x) {
-        const int j = (int)(i % nv);
-        float xr = 0.f, xi = 0.f;
-        if (mask == nullptr || mask[j] != 0) {
-            const float rr = theta[3 * (size_t)nv + j], ri = theta[4 * (size_t)nv + j];
-            const float mu0 = ld_train(trains + i);
-            if constexpr (NTRV == 1) {
-                xr = -ri * mu0;
-                xi = rr * mu0;
-            } else {
-                float t = 0.f;
+    const int lane = threadIdx.x & 63;
+    const int iy = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (iy >= ny) return;
+    const int x0 = 4 * lane;
+    const size_t plane = (size_t)T * nv;
+    float rr[4], ri[4], w[3][4], nr[4], ni[4];
+    bool on[4];
 #pragma unroll
-                for (int q = 0; q < NTRV - 1; ++q) t = fmaf(v[(size_t)q * nv + j], ld_train(trains + (q + 1) * plane + i), t);
-                const float v3 = v[3 * (size_t)nv + j], v4 = v[4 * (size_t)nv + j];
-                // x = i (rho t + (v3 + i v4) mu0)
-                xr = -(ri * t + v4 * mu0);
-                xi = rr * t + v3 * mu0;
+    for (int c = 0; c < 4; ++c) {
+        const bool in = x0 + c < nx;
+        const size_t j = (size_t)iy * nx + (in ? x0 + c : 0);
+        on[c] = in && (mask == nullptr || mask[j] != 0);
+        rr[c] = on[c] ? theta[3 * (size_t)nv + j] : 0.f;
+        ri[c] = on[c] ? theta[4 * (size_t)nv + j] : 0.f;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) w[q][c] = on[c] && q < NTRV - 1 ? v[(size_t)q * nv + j] : 0.f;
+        nr[c] = on[c] && NTRV > 1 ? v[3 * (size_t)nv + j] : 0.f;
+        ni[c] = on[c] && NTRV > 1 ? v[4 * (size_t)nv + j] : 0.f;
+    }
+    const bool whole = x0 + 4 <= nx;
+    const int nt = min(NC_XT, n_count - (int)blockIdx.y * NC_XT);
+    float ar[NC_XT][4], ai[NC_XT][4];   // i (rho t + nu mu0); masked voxels zero whatever their trains hold
+#pragma unroll
+    for (int k = 0; k < NC_XT; ++k) {
+        const int n = n_first + blockIdx.y * NC_XT + (k < nt ? k : 0);
+        const TT* row = trains + (size_t)n * nv + (size_t)iy * nx;
+        float m[NTRV][4];
+#pragma unroll
+        for (int q = 0; q < NTRV; ++q) {
+            const TT* p = row + q * plane;
+            if (whole) {
+                typedef TT V4 __attribute__((ext_vector_type(4), aligned(sizeof(TT))));
+                const V4 t = *reinterpret_cast<const V4*>(p + x0);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) m[q][c] = (float)t[c];
+            } else {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) m[q][c] = x0 + c < nx ? (float)p[x0 + c] : 0.f;
             }
         }
-        if constexpr (SPLIT)
-            reinterpret_cast<uint2*>(X)[i] = split_pair(xr, xi);
-        else
-            X[i] = make_float2(xr, xi);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            float t = 0.f;
+#pragma unroll
+            for (int q = 1; q < NTRV; ++q) t = fmaf(w[q - 1][c], m[q][c], t);
+            if constexpr (NTRV == 1) {
+                ar[k][c] = on[c] ? -ri[c] * m[0][c] : 0.f;
+                ai[k][c] = on[c] ? rr[c] * m[0][c] : 0.f;
+            } else {
+                ar[k][c] = on[c] ? -(ri[c] * t + ni[c] * m[0][c]) : 0.f;
+                ai[k][c] = on[c] ? rr[c] * t + nr[c] * m[0][c] : 0.f;
+            }
+        }
+    }
+    for (int cl = 0; cl < n_coils; ++cl) {
+        float cr[4], ci[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const float2 cc = coil != nullptr && on[c] ? coil[(size_t)cl * nv + (size_t)iy * nx + x0 + c]
+                                                       : make_float2(1.f, 0.f);
+            cr[c] = cc.x;
+            ci[c] = cc.y;
+        }
+#pragma unroll
+        for (int k = 0; k < NC_XT; ++k) {
+            if (k >= nt) break;
+            float xr[4], xi[4], mx = 0.f;
+            bool nan = false;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                xr[c] = cr[c] * ar[k][c] - ci[c] * ai[k][c];
+                xi[c] = cr[c] * ai[k][c] + ci[c] * ar[k][c];
+                nan = nan || !(xr[c] == xr[c] && xi[c] == xi[c]);
+                mx = fmaxf(mx, fmaxf(fabsf(xr[c]), fabsf(xi[c])));
+            }
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+            // A value that is not finite makes the row's (and so the TR's) sums so.
+            const float sc = __any(nan) ? 1.f : pow2_scale(mx);
+            char* rec = X.at(cl * n_count + blockIdx.y * NC_XT + k);
+            if (lane == 0) reinterpret_cast<float*>(rec + x_planes(ny, X.nx8))[iy] = 1.f / (sc * kPhaseScale);
+            if (x0 < X.nx8) {
+                unsigned o[4][2];
+                split_h(sc * xr[0], sc * xr[1], o[0][0], o[1][0]);
+                split_h(sc * xr[2], sc * xr[3], o[0][1], o[1][1]);
+                split_h(sc * xi[0], sc * xi[1], o[2][0], o[3][0]);
+                split_h(sc * xi[2], sc * xi[3], o[2][1], o[3][1]);
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    *reinterpret_cast<uint2*>(rec + 2 * (((size_t)q * ny + iy) * X.nx8 + x0)) =
+                        make_uint2(o[q][0], o[q][1]);
+            }
+        }
     }
 }
 
 // ------------------------------------------------------------------------
-// Forward: a block of 4 waves per (TR n, 64 samples, coil); wave w owns
-// samples k0 = 64 kt + 16 w .. +15. Its A fragments (Ex of its 16 samples
-// over all nx columns, KS K-steps) are generated once and kept in registers;
-// the voxel values X of 32 image rows at a time are staged in LDS (times the
-// coil weight; ENC 1: split into bf16 hi/lo words), NC_XB of each thread's
-// loads issued together, then each wave multiplies them for 4 column blocks
-// of 8 rows, and the epilogue applies Ey and sums over the rows. Blocks are
-// dealt so that the sample tiles of one TR share an XCD (its voxel values
-// come through one L2). K goes in parts of 64 columns (A fragments of one
-// part in registers: four waves per SIMD). Measured at 224 x 224, 1120 spokes
-// (FP32 / split-BF16): all of K at once 5.08 / 2.32 ms (two waves per SIMD),
-// two parts 4.14 / 2.07 (three), four 3.72 / 2.02; the split-BF16 tile staged
-// in both lane-parity forms (no operand re-forming in the K loop) 1.91; without
-// coil weights the values split once by the voxel-value pass 1.68.
-// MODE 0: out = data - s (and FP64 partials of |out|^2); 1: out = -s; 2: s.
+// Forward: a block of 8 waves per (TR, 128 samples); wave (ws, wr) owns 32
+// samples and NT 16-row tiles of a pass of 32 NT image rows. K runs over the
+// columns in steps of 32. Per step the block's Ex (4 columns-of-8 groups x 128
+// samples, one sincos per group and the others by angle addition) is made by
+// the vector units while the previous step multiplies, and X comes straight
+// from memory to the other LDS buffer; both are kept in MFMA fragment order
+// (1 KB per 16 x 32 fragment). P_re = Er Xr - Ei Xi, P_im = Er Xi + Ei Xr; the
+// epilogue undoes the scales, applies Ey and sums the rows. Blocks are dealt
+// so that the sample tiles of a TR share an XCD (X through one L2). Bound by
+// the matrix pipe (three products of 2.0e11 flop at 224 x 224, 1120 spokes of
+// 448: 0.8 of 2.5 PFLOP/s with the last sample tile half empty) and the LDS
+// reads of its operands: 36 fragments per wave and step for 168 MFMA.
+// mode 0: out = data - s (and FP64 partials of |out|^2); 1: out = -s; 2: s.
 // ------------------------------------------------------------------------
-constexpr int NC_KS0 = 128;   // FP32 K-steps of 4 real k: nx <= 256
-constexpr int NC_KS1 = 16;    // BF16 K-steps of 32 real k: nx <= 256
-constexpr int NC_KP = 4;      // K parts of 64 columns; one part's A fragments in registers at a time
-constexpr int NC_PCOLS = 64;  // columns per K part
-constexpr int NC_ROWS = 32;   // image rows per LDS tile
-constexpr int NC_XB = 4;      // voxel values per thread loaded together
-static_assert(NC_ROWS == 32, "forward tile: 4 column blocks of 8 rows per lane group");
-static_assert(NC_KP * NC_PCOLS == 256 && NC_KS0 % NC_KP == 0 && NC_KS1 % NC_KP == 0, "forward K parts");
+constexpr int NC_MS = 128;   // samples per block
 
-template <int ENC, int MODE, bool PRE>   // PRE: X holds split words (ENC 1, no coil weights)
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void nc_fwd_kernel(
-    const float2* __restrict__ X, const float2* __restrict__ coil, const double* __restrict__ ax,
-    const double* __restrict__ ay, const float2* __restrict__ data, float2* __restrict__ out,
-    double* __restrict__ red, int nx, int ny, int nv, int T, int nk, int KT, int nxp)
+template <int NT>
+__global__ __launch_bounds__(512) void nc_fwd_kernel(XStore X, const double* __restrict__ ax,
+                                                     const double* __restrict__ ay, const float2* __restrict__ data,
+                                                     float2* __restrict__ out, double* __restrict__ red, int mode,
+                                                     int nx, int ny, int T, int n_first, int n_count, int n_coils,
+                                                     int nk, int KT)
 {
-    constexpr int KS0P = NC_KS0 / NC_KP, KS1P = NC_KS1 / NC_KP;   // K-steps per part
-    extern __shared__ __attribute__((aligned(16))) unsigned char nc_smem[];
-    __shared__ double rs[4];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int bid = blockIdx.x;
-    const int slot = bid >> 3;
+    __shared__ u4 As[4][NC_MS / 16][64];
+    __shared__ u4 Bs[2][4][2 * NT][64];
+    __shared__ float2 part[2][NC_MS];   // row sums per row wave
+    __shared__ double rs[8];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ws = wave & 3, wr = wave >> 2;
+    const int slot = blockIdx.x >> 3;
     const int kt = slot % KT;
-    const int n = (slot / KT) * 8 + (bid & 7);
-    const int c = blockIdx.y;
-    const size_t red_at = (size_t)c * gridDim.x + bid;
-    if (n >= T) {
-        if (MODE == 0 && tid == 0) red[red_at] = 0.0;
-        return;
-    }
-    const int k0 = kt * 64 + wave * 16;
-    const int krow = k0 + (lane & 15);
-    const bool krow_ok = krow < nk;
-    const double axk = krow_ok ? ax[(size_t)n * nk + krow] : 0.0;
-    const int h = lane >> 4;   // 0..3
-    const int KS = ENC == 0 ? (2 * nx + 3) / 4 : (2 * nx + 31) / 32;
-
-    // The phases along a row of Ex are a geometric sequence: a lane's columns
-    // come in groups whose first phase is taken from sin/cos and the others
-    // as its products with the phases of the group's offsets.
-    float2 off[ENC == 0 ? 8 : 4];
+    const int rec = (slot / KT) * 8 + (blockIdx.x & 7);   // TR of the pass and coil
+    if (rec >= n_count * n_coils) return;
+    const int n = n_first + rec % n_count;
+    const int k0 = kt * NC_MS, nx8 = X.nx8;
+    // Phase generation: this thread's sample and group of 8 columns.
+    const int gs = tid & (NC_MS - 1), gg = tid >> 7;
+    const double ag = k0 + gs < nk ? ax[(size_t)n * nk + k0 + gs] : 0.0;
+    float2 off[8];
 #pragma unroll
-    for (int o = 0; o < (ENC == 0 ? 8 : 4); ++o)
-        off[o] = o == 0 ? make_float2(1.f, 0.f) : phase_of(axk, ENC == 0 ? 2 * o : o);
-    // Epilogue phases Ey[k][iy] of the lane's 4 samples, iy = iy0 + 8 cb + rb:
-    // phase(iy0 + rb) from sin/cos per tile, times phase(8) once per column
-    // block.
-    const int rb = (lane & 15) >> 1;
-    double ayv[4];
-    float2 e8[4];
+    for (int m = 1; m < 8; ++m) off[m] = phase_of(ag, m);
+    u4 an[4];   // the next step's fragments of this thread
+    auto make_a = [&](int s) {
+        const int c0 = 32 * s + 8 * gg;
+        float2 base = phase_of(ag, c0 - nx / 2);
+        base.x *= kPhaseScale;
+        base.y *= kPhaseScale;
+        float2 e[8];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int k = k0 + 4 * h + i;
-        ayv[i] = k < nk ? ay[(size_t)n * nk + k] : 0.0;
-        e8[i] = phase_of(ayv[i], 8);
-    }
-
-    float sacc[4] = {0.f, 0.f, 0.f, 0.f};
-    const int b = lane & 1;
-    const float2* Xn = X + (size_t)n * nv;
-    float2* xs0 = reinterpret_cast<float2*>(nc_smem);               // ENC 0: [ROWS][nxp]
-    // ENC 1: [2][ROWS][nxp] (hi, lo) words already in the real-form B order of
-    // each lane parity (copy 0: (re, -im), copy 1: (im, re)); the copies are
-    // one entry apart in banks so the two parities do not collide.
-    uint2* xs1 = reinterpret_cast<uint2*>(nc_smem);
-    const int tile_n = NC_ROWS * nxp, copy1 = tile_n + 1;
-    // K parts: columns [NC_PCOLS kp, NC_PCOLS (kp + 1)); the sums over the
-    // rows are linear in P, so each part's Ey-weighted sums simply add up.
-    for (int kp = 0; kp < NC_KP && kp * NC_PCOLS < nx; ++kp) {
-        const int cx0 = kp * NC_PCOLS;
-        // A fragments of this part: Ex[krow][ix] in the real form
-        // A'[k][2 ix + a] = (re, im).
-        float a0[ENC == 0 ? KS0P : 1];
-        uint4 ahi[ENC == 1 ? KS1P : 1], alo[ENC == 1 ? KS1P : 1];
-        if constexpr (ENC == 0) {
-            // columns ix = cx0 + 2 sl + h/2, sl = 8 g + o: phase(cx0 + 16 g + h/2) phase(2 o)
-#pragma unroll
-            for (int g = 0; g < KS0P / 8; ++g) {
-                const bool any = KS0P * kp + 8 * g < KS && krow_ok;
-                const float2 base = any ? phase_of(axk, cx0 + 16 * g + (h >> 1) - nx / 2) : make_float2(0.f, 0.f);
-#pragma unroll
-                for (int o = 0; o < 8; ++o) {
-                    const int sl = 8 * g + o, ix = cx0 + 2 * sl + (h >> 1);
-                    float val = 0.f;
-                    if (KS0P * kp + sl < KS && krow_ok && ix < nx) {
-                        const float2 e = cmul(base, off[o]);
-                        val = (h & 1) ? e.y : e.x;
-                    }
-                    a0[sl] = val;
-                }
-            }
-        } else {
-            // columns ix = cx0 + 16 sl + 4 h + m: phase(cx0 + 16 sl + 4 h) phase(m)
-#pragma unroll
-            for (int sl = 0; sl < KS1P; ++sl) {
-                const bool any = KS1P * kp + sl < KS && krow_ok;
-                const float2 base = any ? phase_of(axk, cx0 + 16 * sl + 4 * h - nx / 2) : make_float2(0.f, 0.f);
-                unsigned int hw[4], lw[4];
-#pragma unroll
-                for (int m = 0; m < 4; ++m) {
-                    const int ix = cx0 + 16 * sl + 4 * h + m;
-                    float2 e = make_float2(0.f, 0.f);
-                    if (any && ix < nx) e = cmul(base, off[m]);
-                    const uint2 w = split_pair(e.x, e.y);
-                    hw[m] = w.x;
-                    lw[m] = w.y;
-                }
-                ahi[sl] = make_uint4(hw[0], hw[1], hw[2], hw[3]);
-                alo[sl] = make_uint4(lw[0], lw[1], lw[2], lw[3]);
-            }
+        for (int m = 0; m < 8; ++m) {
+            e[m] = m == 0 ? base : cmul(base, off[m]);
+            if (c0 + m >= nx) e[m] = make_float2(0.f, 0.f);
         }
-        for (int iy0 = 0; iy0 < ny; iy0 += NC_ROWS) {
-            __syncthreads();   // the previous tile has been read
-            if constexpr (PRE) {
-                // Split words from the voxel-value pass: only the two
-                // operand orders are formed here.
-                const uint2* Xw = reinterpret_cast<const uint2*>(Xn);
-                for (int e0 = tid; e0 < tile_n; e0 += 256 * NC_XB) {
-                    uint2 wv[NC_XB];
 #pragma unroll
-                    for (int u = 0; u < NC_XB; ++u) {
-                        const int e = e0 + 256 * u;
-                        const int r = e / nxp, ixl = e % nxp, iy = iy0 + r, ix = cx0 + ixl;
-                        const bool ok = e < tile_n && ixl < NC_PCOLS && ix < nx && iy < ny;
-                        wv[u] = ok ? Xw[(size_t)iy * nx + ix] : make_uint2(0u, 0u);
-                    }
-#pragma unroll
-                    for (int u = 0; u < NC_XB; ++u) {
-                        const int e = e0 + 256 * u;
-                        if (e >= tile_n) break;
-                        const uint2 w = wv[u];
-                        xs1[e] = make_uint2(w.x ^ 0x80000000u, w.y ^ 0x80000000u);
-                        xs1[copy1 + e] = make_uint2((w.x >> 16) | (w.x << 16), (w.y >> 16) | (w.y << 16));
-                    }
-                }
-            } else {
-                for (int e0 = tid; e0 < tile_n; e0 += 256 * NC_XB) {
-                    float2 xv[NC_XB], cv[NC_XB];
-#pragma unroll
-                    for (int u = 0; u < NC_XB; ++u) {
-                        const int e = e0 + 256 * u;
-                        const int r = e / nxp, ixl = e % nxp, iy = iy0 + r, ix = cx0 + ixl;
-                        const bool ok = e < tile_n && ixl < NC_PCOLS && ix < nx && iy < ny;
-                        const size_t j = ok ? (size_t)iy * nx + ix : 0;
-                        xv[u] = ok ? Xn[j] : make_float2(0.f, 0.f);
-                        cv[u] = coil != nullptr && ok ? coil[(size_t)c * nv + j] : make_float2(1.f, 0.f);
-                    }
-#pragma unroll
-                    for (int u = 0; u < NC_XB; ++u) {
-                        const int e = e0 + 256 * u;
-                        if (e >= tile_n) break;
-                        const float xr = cv[u].x * xv[u].x - cv[u].y * xv[u].y;
-                        const float xi = cv[u].x * xv[u].y + cv[u].y * xv[u].x;
-                        if constexpr (ENC == 0) {
-                            xs0[e] = make_float2(xr, xi);
-                        } else {
-                            const uint2 w = split_pair(xr, xi);
-                            xs1[e] = make_uint2(w.x ^ 0x80000000u, w.y ^ 0x80000000u);
-                            xs1[copy1 + e] = make_uint2((w.x >> 16) | (w.x << 16), (w.y >> 16) | (w.y << 16));
-                        }
-                    }
-                }
-            }
-            __syncthreads();
-            float2 ebase[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) ebase[i] = phase_of(ayv[i], iy0 + rb - ny / 2);
-#pragma unroll
-            for (int cb = 0; cb < NC_ROWS / 8; ++cb) {
-                const int rl = 8 * cb + rb;   // tile row of this lane's column
-                f4 acc = {0.f, 0.f, 0.f, 0.f};
-                if constexpr (ENC == 0) {
-#pragma unroll
-                    for (int sl = 0; sl < KS0P; ++sl) {
-                        if (KS0P * kp + sl < KS) {
-                            const float2 x = xs0[rl * nxp + 2 * sl + (h >> 1)];
-                            const int a = h & 1;
-                            const float bv = a == 0 ? (b == 0 ? x.x : x.y) : (b == 0 ? -x.y : x.x);
-                            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[sl], bv, acc, 0, 0, 0);
-                        }
-                    }
-                } else {
-#pragma unroll
-                    for (int sl = 0; sl < KS1P; ++sl) {
-                        if (KS1P * kp + sl < KS) {
-                            const uint2* src = xs1 + b * copy1 + rl * nxp + 16 * sl + 4 * h;
-                            const uint2 p0 = src[0], p1 = src[1], p2 = src[2], p3 = src[3];
-                            const uint4 bh = make_uint4(p0.x, p1.x, p2.x, p3.x);
-                            const uint4 bl = make_uint4(p0.y, p1.y, p2.y, p3.y);
-                            acc = mma_bf16(ahi[sl], bh, acc);
-                            acc = mma_bf16(ahi[sl], bl, acc);
-                            acc = mma_bf16(alo[sl], bh, acc);
-                        }
-                    }
-                }
-                // Epilogue of this column block: P[k, iy] (re in even lanes, im
-                // in odd) times Ey[k, iy], summed into the lane's running row
-                // sums.
-                const int iy = iy0 + rl;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float own = acc[i];
-                    const float oth = __shfl_xor(own, 1);
-                    const float pr = b == 0 ? own : oth, pi = b == 0 ? oth : own;
-                    const int k = k0 + 4 * h + i;
-                    if (k < nk && iy < ny) {
-                        const float2 ey = ebase[i];
-                        sacc[i] += b == 0 ? pr * ey.x - pi * ey.y : pr * ey.y + pi * ey.x;
-                    }
-                    ebase[i] = cmul(ebase[i], e8[i]);   // the next column block's rows
-                }
-            }
+        for (int m = 0; m < 4; ++m) {
+            unsigned h, l;
+            split_h(e[2 * m].x, e[2 * m + 1].x, h, l);
+            an[0][m] = h;
+            an[1][m] = l;
+            split_h(e[2 * m].y, e[2 * m + 1].y, h, l);
+            an[2][m] = h;
+            an[3][m] = l;
         }
+    };
+    u4* const aw = &As[0][gs >> 4][(gs & 15) + 16 * gg];
+    const _Float16* Xn = reinterpret_cast<const _Float16*>(X.at(rec));
+    const float* rinv = reinterpret_cast<const float*>(X.at(rec) + x_planes(ny, nx8));
+    const int KS = (nx + 31) / 32, rows = 32 * NT;
+    // X fragments of step s and row pass y0 to LDS: rows past ny read the last
+    // one (their sums are dropped), columns past nx8 the first (their Ex is 0).
+    auto load_b = [&](int y0, int s, int buf) {
+        const int col = 32 * s + 8 * (lane >> 4);
+#pragma unroll
+        for (int i = 0; i < NT; ++i) {
+            const int f = wave + 8 * i;   // 8 NT fragments: plane f / (2 NT), row tile f % (2 NT)
+            const int q = f / (2 * NT), t = f % (2 * NT);
+            const int iy = min(y0 + 16 * t + (lane & 15), ny - 1);
+            to_lds16(Xn + ((size_t)q * ny + iy) * nx8 + (col < nx8 ? col : 0), &Bs[buf][q][t][0]);
+        }
+    };
+    const bool active = k0 + 32 * ws < nk;   // whole waves of samples past the end only stage
+    const unsigned abase = lds_addr(&As[0][2 * ws][lane]);
+    const unsigned bbase = lds_addr(&Bs[0][0][NT * wr][lane]);
+    constexpr unsigned BBUF = sizeof(Bs[0]);
+
+    for (int y0 = 0; y0 < ny; y0 += rows) {
+        f4 pr[2][NT], pi[2][NT];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) pr[i][t] = pi[i][t] = f4{0.f, 0.f, 0.f, 0.f};
+        load_b(y0, 0, 0);
+        make_a(0);
+        auto steps = [&](auto multiply) {
+            for (int s = 0; s < KS; ++s) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) aw[q * (NC_MS / 16) * 64] = an[q];
+                asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n s_barrier" ::: "memory");
+                if (s + 1 < KS) {
+                    load_b(y0, s + 1, (s + 1) & 1);
+                    make_a(s + 1);
+                }
+                if constexpr (decltype(multiply)::value) {
+                    u4 a[2][4];
+                    read_frag4<(NC_MS / 16) * 1024>(a[0], abase);
+                    read_frag4<(NC_MS / 16) * 1024>(a[1], abase + 1024);
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) {
+                        u4 b[4];
+                        read_frag4<2 * NT * 1024>(b, bbase + (s & 1) * BBUF + t * 1024);
+                        const u4 nh = b[2] ^ 0x80008000u, nl = b[3] ^ 0x80008000u;   // -Xi
+#pragma unroll
+                        for (int i = 0; i < 2; ++i) {
+                            pr[i][t] = mma(a[i][0], b[0], pr[i][t]);
+                            pi[i][t] = mma(a[i][0], b[2], pi[i][t]);
+                            pr[i][t] = mma(a[i][2], nh, pr[i][t]);
+                            pi[i][t] = mma(a[i][2], b[0], pi[i][t]);
+                            pr[i][t] = mma(a[i][0], b[1], pr[i][t]);
+                            pi[i][t] = mma(a[i][0], b[3], pi[i][t]);
+                            pr[i][t] = mma(a[i][2], nl, pr[i][t]);
+                            pi[i][t] = mma(a[i][2], b[1], pi[i][t]);
+                            pr[i][t] = mma(a[i][1], b[0], pr[i][t]);
+                            pi[i][t] = mma(a[i][1], b[2], pi[i][t]);
+                            pr[i][t] = mma(a[i][3], nh, pr[i][t]);
+                            pi[i][t] = mma(a[i][3], b[0], pi[i][t]);
+                        }
+                    }
+                }
+                asm volatile("s_waitcnt lgkmcnt(0)\n s_barrier" ::: "memory");
+            }
+        };
+        if (!active) {
+            steps(std::false_type{});
+            continue;
+        }
+        steps(std::true_type{});
+        // s[k] += sum_iy Ey[k,iy] P[k,iy]: the lane's image row of tile t is
+        // yl + 16 t, its phases one sincos and steps of 16 rows.
+        const int yl = y0 + 16 * NT * wr + (lane & 15);
+        float ri[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) ri[t] = yl + 16 * t < ny ? rinv[yl + 16 * t] : 0.f;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int kl = 32 * ws + 16 * i + 4 * (lane >> 4) + r;
+                const double ayv = k0 + kl < nk ? ay[(size_t)n * nk + k0 + kl] : 0.0;
+                float2 ey = phase_of(ayv, yl - ny / 2), sum = make_float2(0.f, 0.f);
+                const float2 st = phase_of(ayv, 16);
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
+                    if (yl + 16 * t < ny) {
+                        const float2 p = make_float2(ri[t] * pr[i][t][r], ri[t] * pi[i][t][r]);
+                        sum.x += ey.x * p.x - ey.y * p.y;
+                        sum.y += ey.x * p.y + ey.y * p.x;
+                    }
+                    if (t + 1 < NT) ey = cmul(ey, st);
+                }
+#pragma unroll
+                for (int o = 1; o < 16; o <<= 1) {
+                    sum.x += __shfl_xor(sum.x, o);
+                    sum.y += __shfl_xor(sum.y, o);
+                }
+                if ((lane & 15) == 0) {
+                    if (y0 > 0) {
+                        sum.x += part[wr][kl].x;
+                        sum.y += part[wr][kl].y;
+                    }
+                    part[wr][kl] = sum;
+                }
+            }
     }
-    // Sum over the 8 column lanes of each parity: lanes 0 and 1 of each
-    // 16-lane group then hold (re, im) of s for rows 4 h + i.
+    __syncthreads();
     double sq = 0.0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        float vv = sacc[i];
-        vv += __shfl_xor(vv, 2);
-        vv += __shfl_xor(vv, 4);
-        vv += __shfl_xor(vv, 8);
-        const int k = k0 + 4 * h + i;
-        if ((lane & 14) == 0 && k < nk) {
-            const size_t idx = ((size_t)c * T + n) * nk + k;
-            float* o = reinterpret_cast<float*>(out) + 2 * idx + b;
-            if constexpr (MODE == 0) {
-                const float rv = reinterpret_cast<const float*>(data)[2 * idx + b] - vv;
-                *o = rv;
-                sq += (double)rv * (double)rv;
-            } else if constexpr (MODE == 1) {
-                *o = -vv;
-            } else {
-                *o = vv;
-            }
+    if (tid < NC_MS && k0 + tid < nk) {
+        const size_t idx = ((size_t)(rec / n_count) * T + n) * nk + k0 + tid;
+        float2 v = make_float2(part[0][tid].x + part[1][tid].x, part[0][tid].y + part[1][tid].y);
+        if (mode == 0) {
+            const float2 d = data[idx];
+            v = make_float2(d.x - v.x, d.y - v.y);
+            sq = (double)v.x * v.x + (double)v.y * v.y;
+        } else if (mode == 1) {
+            v = make_float2(-v.x, -v.y);
         }
+        out[idx] = v;
     }
-    if constexpr (MODE == 0) {
-        for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off);
+    if (mode == 0) {
+        for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o);
         if (lane == 0) rs[wave] = sq;
         __syncthreads();
-        if (tid == 0) red[red_at] = (rs[0] + rs[1]) + (rs[2] + rs[3]);
+        // (the other waves hold no samples)
+        if (tid == 0) red[((size_t)(rec / n_count) * T + n) * KT + kt] = rs[0] + rs[1];
     }
 }
 
 // ------------------------------------------------------------------------
-// Adjoint: a block of 4 waves per (tile of 64 image rows x 32 columns, TR
-// chunk); wave w owns rows 16 w .. +15 of the tile, 4 column blocks of 8
-// columns. For each TR and coil the samples go in chunks of 64: the block
-// writes G[k][row] = conj(Ey[k][iy]) w_c[k] and H[k][col] = conj(Ex[k][ix])
-// into LDS (as [row][k] and [col][k], so a lane's 4 consecutive samples are
-// adjacent), then the waves multiply; each coil's product is weighted by
-// conj(C_c[j]) per voxel, and after the TR the epilogue adds mu_p[n,j] V[j]
-// to the lane's running sums. Chunk partials: apart[chunk][2 p + (re, im)][j]
-// with 8 planes per chunk (2 for the m train alone), the layout of the
-// Cartesian adjoint, so the same gradient assembly follows. Measured at 224 x
-// 224, 1120 spokes (FP32 / split-BF16): unpadded table rows 14.3 / 5.9 ms,
-// with the phases by angle addition 13.3 / 3.3, padded rows 5.0 / 2.9; the
-// next chunk's trajectory and data values loaded ahead need 6 more registers:
-// 5.0 / 2.9 with 56 bytes per lane spilled at three waves per SIMD, 5.8 / 4.2
-// at two; H staged in both lane-parity operand orders (no re-forming in the K
-// loop, 68 KB of LDS: two blocks per CU instead of three) 3.6 (split-BF16).
+// Adjoint, V[n][j] = sum_c conj(C_c[j]) sum_k conj(E[n,k,j]) w_c[n,k]: a block
+// of 8 waves per (TR, 128 columns, 32 NT rows); wave (ws, wr) owns 32 columns
+// and NT 16-row tiles, K runs over the samples in steps of 32. Both operands
+// are phases: H[k,ix] = conj(Ex) and G[k,iy] = conj(Ey) w (w scaled so that
+// its largest value of the TR lies in [2^10, 2^11)). A thread makes one
+// sample's values at 8 consecutive columns and 2 NT consecutive rows: two
+// sincos, the others as products with the phases of 1 to 7 positions on, whose
+// factors (1, 2 and 4 on) come from a table made a step ahead; it does so
+// while the step before multiplies, holding the split values in registers.
+// They lie in LDS as [plane][sample][position], written 16 bytes at a time
+// and read as MFMA fragments by the transposing LDS load (each 16 lanes: 4
+// samples x 16 positions). Bound by the matrix pipe and, nearly as long, the
+// vector units that make and split the phases.
 // ------------------------------------------------------------------------
-constexpr int NCA_TY = 64, NCA_TX = 32, NCA_KC = 64;
-// LDS row stride of the tables: two entries of padding, so the rows (16 per
-// wave for G, 8 for H) that one MFMA operand read touches fall in different
-// banks (the unpadded stride of 512 bytes puts them all in one); 16-byte
-// aligned rows.
-constexpr int NCA_KCP = NCA_KC + 2;
-// The table build gives each of the 256 threads one sample and every 4th
-// row (column) of the tile.
-static_assert(256 / NCA_KC == 4 && NCA_TY % 16 == 0 && NCA_TX % 16 == 0, "adjoint table build layout");
+constexpr int NCA_TX = 128;   // columns per block
 
-template <int ENC, int NTR, typename TT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void nc_adj_kernel(
-    const TT* __restrict__ trains, const float2* __restrict__ coil, const uint8_t* __restrict__ mask,
-    const double* __restrict__ ax, const double* __restrict__ ay, const float2* __restrict__ w,
-    float* __restrict__ apart, int nx, int ny, int nv, int T, int nk, int C, int n_per_chunk, int ntx)
+typedef short s4 __attribute__((ext_vector_type(4)));
+
+// Fragment (16 positions, 32 samples: lane l position l % 16, samples
+// 8 (l / 16)..+7) from rows of ROW bytes per sample; `at` is this lane's
+// address for samples 8 (l / 16) + (l % 16) / 4.
+template <int ROW> __device__ __forceinline__ u4 read_tr(const char* at)
 {
-    // LDS: G [TY][KC] and H [TX][KC] entries of 8 bytes: ENC 0 (re, im) FP32,
-    // ENC 1 (hi word, lo word).
-    __shared__ __attribute__((aligned(16))) uint2 gs[NCA_TY * NCA_KCP];
-    __shared__ __attribute__((aligned(16))) uint2 hs[NCA_TX * NCA_KCP];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int tile = blockIdx.x;
-    const int iy_base = (tile / ntx) * NCA_TY, ix_base = (tile % ntx) * NCA_TX;
-    const int chunk = blockIdx.y;
-    const int n0 = chunk * n_per_chunk, n1 = min(T, n0 + n_per_chunk);
-    const int h = lane >> 4, b = lane & 1;
-    const size_t plane = (size_t)T * nv;
+    typedef __attribute__((address_space(3))) s4* lp;
+    const s4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)(lptr)(char*)at);
+    const s4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)(lptr)(char*)(at + 4 * ROW));
+    const uint2 x = __builtin_bit_cast(uint2, a), y = __builtin_bit_cast(uint2, b);
+    return u4{x.x, x.y, y.x, y.y};
+}
 
-    // This lane's outputs: rows iy_base + 16 wave + 4 h + i, column
-    // ix_base + 8 cb + (lane & 15) / 2, part b (0 re, 1 im).
-    float aacc[4][4][NTR];   // [cb][i][train]
-#pragma unroll
-    for (int cb = 0; cb < 4; ++cb)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int p = 0; p < NTR; ++p) aacc[cb][i][p] = 0.f;
+template <int NT>
+__global__ __launch_bounds__(512) void nc_adj_kernel(const float2* __restrict__ coil, const double* __restrict__ ax,
+                                                     const double* __restrict__ ay, const float2* __restrict__ w,
+                                                     float2* __restrict__ V, int nx, int ny, int nv, int T, int nk,
+                                                     int C, int ntx, int tiles)
+{
+    constexpr int NR = 2 * NT;                  // rows per thread, 32 NT per block
+    constexpr int AROW = 2 * NCA_TX + 32;       // bytes per sample: 8 words past a multiple of 64 banks, so the
+    constexpr int BROW = 64 * NT + 32;          // samples of a write or of a transposing read differ in banks
+    __shared__ __attribute__((aligned(16))) char Hs[4][32][AROW];
+    __shared__ __attribute__((aligned(16))) char Gs[4][32][BROW];
+    __shared__ float2 tab[2][6][32];            // phases of 1, 2, 4 columns / rows per sample
+    __shared__ float wmax[8];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ws = wave & 3, wr = wave >> 2;
+    const int slot = blockIdx.x >> 3;
+    const int tile = slot % tiles;
+    const int n = (slot / tiles) * 8 + (blockIdx.x & 7);
+    if (n >= T) return;
+    const int x0 = (tile % ntx) * NCA_TX, y0 = (tile / ntx) * 32 * NT;
+    const bool active = x0 + 32 * ws < nx;
+    const int ks = tid & 31, pg = tid >> 5;     // this thread's sample of a step and group of positions
+    const double* axn = ax + (size_t)n * nk;
+    const double* ayn = ay + (size_t)n * nk;
+    const int KS = (nk + 31) / 32;
 
-    for (int n = n0; n < n1; ++n) {
-        f4 vacc[4];   // V of this TR (summed over coils with their weights)
+    auto make_tab = [&](int s, int buf) {
+        if (tid < 192) {
+            const int k = 32 * s + (tid & 31), q = tid >> 5;   // q: x1 x2 x4 y1 y2 y4
+            const double a = k < nk ? (q < 3 ? axn[k] : ayn[k]) : 0.0;
+            tab[buf][q][tid & 31] = phase_of(-a, 1 << (q % 3));
+        }
+    };
+    for (int c = 0; c < C; ++c) {
+        const float2* wn = w + ((size_t)c * T + n) * nk;
+        // Scale of this TR's samples.
+        float mx = 0.f;
+        bool nan = false;
+        for (int k = tid; k < nk; k += 512) {
+            const float2 v = wn[k];
+            nan = nan || !(v.x == v.x && v.y == v.y);
+            mx = fmaxf(mx, fmaxf(fabsf(v.x), fabsf(v.y)));
+        }
+        if (nan) mx = __uint_as_float(0x7f800000u);
 #pragma unroll
-        for (int cb = 0; cb < 4; ++cb) vacc[cb] = f4{0.f, 0.f, 0.f, 0.f};
-        for (int c = 0; c < C; ++c) {
-            f4 cacc[4];
+        for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+        __syncthreads();   // the previous coil's scale and tables have been read
+        if (lane == 0) wmax[wave] = mx;
+        make_tab(0, 0);
+        make_tab(1, 1);
+        __syncthreads();
+        mx = wmax[0];
 #pragma unroll
-            for (int cb = 0; cb < 4; ++cb) cacc[cb] = f4{0.f, 0.f, 0.f, 0.f};
-            for (int kc0 = 0; kc0 < nk; kc0 += NCA_KC) {
-                __syncthreads();   // the previous chunk's tables have been read
-                // G: 64 rows x 64 samples; H: 32 columns x 64 samples. A
-                // thread takes one sample and every 4th row (column): the
-                // phases along them form a geometric sequence, so per sample
-                // three phases come from sin/cos (the first row, 4 and 16
-                // rows on) and the others from complex products of those.
-                {
-                    const int kk = tid % NCA_KC, r0 = tid / NCA_KC;
-                    const int k = kc0 + kk;
-                    const bool kok = k < nk;
-                    const double ayk = kok ? ay[(size_t)n * nk + k] : 0.0;
-                    const double axk = kok ? ax[(size_t)n * nk + k] : 0.0;
-                    const float2 ww = kok ? w[((size_t)c * T + n) * nk + k] : make_float2(0.f, 0.f);
-                    auto store = [&](uint2* dst, float2 val) {
-                        if constexpr (ENC == 0)
-                            *dst = make_uint2(__float_as_uint(val.x), __float_as_uint(val.y));
-                        else
-                            *dst = split_pair(val.x, val.y);
-                    };
-                    {   // G[r][kk] = conj(Ey[k][iy]) w[k], iy = iy_base + r0 + 4 m
-                        const float2 s4 = phase_of(ayk, 4), s16 = phase_of(ayk, 16);
-                        const float2 s8 = cmul(s4, s4), s12 = cmul(s8, s4);
-                        float2 q = phase_of(ayk, iy_base + r0 - ny / 2);
-#pragma unroll 1
-                        for (int u = 0; u < NCA_TY / 16; ++u) {
-                            const float2 qv[4] = {q, cmul(q, s4), cmul(q, s8), cmul(q, s12)};
+        for (int i = 1; i < 8; ++i) mx = fmaxf(mx, wmax[i]);
+        const float sc = pow2_scale(mx);
+
+        unsigned hv[4][4], gv[4][NT];   // split values: [plane][pair of positions]
+        auto make = [&](int s) {
+            const int k = 32 * s + ks;
+            const double ak = k < nk ? axn[k] : 0.0, bk = k < nk ? ayn[k] : 0.0;
+            float2 wv = k < nk ? wn[k] : make_float2(0.f, 0.f);
+            wv.x *= sc;
+            wv.y *= sc;
+            auto line = [&](float2 base, const float2 (&t)[8], auto& out, auto count, int first) {
+                constexpr int N = decltype(count)::value;   // positions of this line, even
 #pragma unroll
-                            for (int v4 = 0; v4 < 4; ++v4) {
-                                const int r = r0 + 16 * u + 4 * v4;
-                                const float2 ey = qv[v4];
-                                float2 val = make_float2(0.f, 0.f);
-                                if (kok && iy_base + r < ny)   // conj(ey) * w
-                                    val = make_float2(ey.x * ww.x + ey.y * ww.y, ey.x * ww.y - ey.y * ww.x);
-                                store(gs + r * NCA_KCP + kk, val);
-                            }
-                            q = cmul(q, s16);
-                        }
-                    }
-                    {   // H[r][kk] = conj(Ex[k][ix]), ix = ix_base + r0 + 4 m
-                        const float2 s4 = phase_of(axk, 4), s16 = phase_of(axk, 16);
-                        const float2 s8 = cmul(s4, s4), s12 = cmul(s8, s4);
-                        float2 q = phase_of(axk, ix_base + r0 - nx / 2);
-#pragma unroll 1
-                        for (int u = 0; u < NCA_TX / 16; ++u) {
-                            const float2 qv[4] = {q, cmul(q, s4), cmul(q, s8), cmul(q, s12)};
+                for (int m = 0; m < N; m += 2) {
+                    const float2 e0 = m == 0 ? base : cmul(base, t[m]), e1 = cmul(base, t[m + 1]);
+                    split_h(e0.x, e1.x, out[0][first + m / 2], out[1][first + m / 2]);
+                    split_h(e0.y, e1.y, out[2][first + m / 2], out[3][first + m / 2]);
+                }
+            };
+            auto steps = [&](int q, float2 (&t)[8]) {
+                t[1] = tab[s & 1][q][ks];
+                t[2] = tab[s & 1][q + 1][ks];
+                t[4] = tab[s & 1][q + 2][ks];
+                t[3] = cmul(t[1], t[2]);
+                t[5] = cmul(t[4], t[1]);
+                t[6] = cmul(t[4], t[2]);
+                t[7] = cmul(t[4], t[3]);
+            };
+            float2 t[8];
+            steps(0, t);
+            float2 base = phase_of(-ak, x0 + 8 * pg - nx / 2);
+            base.x *= kPhaseScale;
+            base.y *= kPhaseScale;
+            line(base, t, hv, std::integral_constant<int, 8>{}, 0);
+            steps(3, t);
+            base = cmul(phase_of(-bk, y0 + NR * pg - ny / 2), wv);
+            if constexpr (NR <= 8) {
+                line(base, t, gv, std::integral_constant<int, NR>{}, 0);
+            } else {
+                line(base, t, gv, std::integral_constant<int, 8>{}, 0);
+                line(cmul(base, cmul(t[4], t[4])), t, gv, std::integral_constant<int, NR - 8>{}, 4);
+            }
+        };
+        f4 vr[2][NT], vi[2][NT];
 #pragma unroll
-                            for (int v4 = 0; v4 < 4; ++v4) {
-                                const int r = r0 + 16 * u + 4 * v4;
-                                const float2 ex = qv[v4];
-                                const float2 val = (kok && ix_base + r < nx) ? make_float2(ex.x, -ex.y)
-                                                                             : make_float2(0.f, 0.f);
-                                store(hs + r * NCA_KCP + kk, val);
-                            }
-                            q = cmul(q, s16);
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) vr[i][t] = vi[i][t] = f4{0.f, 0.f, 0.f, 0.f};
+        // This lane's part of a transposing read: sample 8 (l / 16) + (l % 16) / 4, positions 4 (l % 4)..+3.
+        const int rk = 8 * (lane >> 4) + ((lane & 15) >> 2), rp = 4 * (lane & 3);
+        const char* ha = &Hs[0][rk][2 * (32 * ws + rp)];
+        const char* ga = &Gs[0][rk][2 * (16 * NT * wr + rp)];
+        make(0);
+        auto run = [&](auto multiply) {
+            for (int s = 0; s < KS; ++s) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    *reinterpret_cast<u4*>(&Hs[q][ks][16 * pg]) = u4{hv[q][0], hv[q][1], hv[q][2], hv[q][3]};
+#pragma unroll
+                    for (int m = 0; m < NT; ++m) *reinterpret_cast<unsigned*>(&Gs[q][ks][4 * (NT * pg + m)]) = gv[q][m];
+                }
+                __syncthreads();
+                if (s + 1 < KS) make(s + 1);
+                if constexpr (decltype(multiply)::value) {
+                    u4 h[2][4];
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) h[i][q] = read_tr<AROW>(ha + q * 32 * AROW + 32 * i);
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) {
+                        u4 g[4];
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) g[q] = read_tr<BROW>(ga + q * 32 * BROW + 32 * t);
+                        const u4 nh = g[2] ^ 0x80008000u, nl = g[3] ^ 0x80008000u;   // -Gi
+#pragma unroll
+                        for (int i = 0; i < 2; ++i) {
+                            vr[i][t] = mma(h[i][0], g[0], vr[i][t]);
+                            vi[i][t] = mma(h[i][0], g[2], vi[i][t]);
+                            vr[i][t] = mma(h[i][2], nh, vr[i][t]);
+                            vi[i][t] = mma(h[i][2], g[0], vi[i][t]);
+                            vr[i][t] = mma(h[i][0], g[1], vr[i][t]);
+                            vi[i][t] = mma(h[i][0], g[3], vi[i][t]);
+                            vr[i][t] = mma(h[i][2], nl, vr[i][t]);
+                            vi[i][t] = mma(h[i][2], g[1], vi[i][t]);
+                            vr[i][t] = mma(h[i][1], g[0], vr[i][t]);
+                            vi[i][t] = mma(h[i][1], g[2], vi[i][t]);
+                            vr[i][t] = mma(h[i][3], nh, vr[i][t]);
+                            vi[i][t] = mma(h[i][3], g[0], vi[i][t]);
                         }
                     }
                 }
                 __syncthreads();
-                const int grow = 16 * wave + (lane & 15);   // A row (image row in the tile)
-                if constexpr (ENC == 0) {
-                    // K-steps of 2 samples (4 real k): lane k' = 4 s + h ->
-                    // sample 2 s + h / 2, part a = h & 1.
-#pragma unroll 4
-                    for (int s = 0; s < NCA_KC / 2; ++s) {
-                        const int kk = 2 * s + (h >> 1), a = h & 1;
-                        const uint2 gv = gs[grow * NCA_KCP + kk];
-                        const float av = __uint_as_float(a ? gv.y : gv.x);
-#pragma unroll
-                        for (int cb = 0; cb < 4; ++cb) {
-                            const int col = 8 * cb + ((lane & 15) >> 1);
-                            const uint2 hv = hs[col * NCA_KCP + kk];
-                            const float hr = __uint_as_float(hv.x), hi = __uint_as_float(hv.y);
-                            const float bv = a == 0 ? (b == 0 ? hr : hi) : (b == 0 ? -hi : hr);
-                            cacc[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv, cacc[cb], 0, 0, 0);
-                        }
-                    }
-                } else {
-                    // K-steps of 16 samples: lane's samples 16 s + 4 h + m.
-#pragma unroll
-                    for (int s = 0; s < NCA_KC / 16; ++s) {
-                        const uint2* gp = gs + grow * NCA_KCP + 16 * s + 4 * h;
-                        const uint2 g0 = gp[0], g1 = gp[1], g2 = gp[2], g3 = gp[3];
-                        const uint4 ah = make_uint4(g0.x, g1.x, g2.x, g3.x);
-                        const uint4 al = make_uint4(g0.y, g1.y, g2.y, g3.y);
-#pragma unroll
-                        for (int cb = 0; cb < 4; ++cb) {
-                            const int col = 8 * cb + ((lane & 15) >> 1);
-                            const uint2* hp = hs + col * NCA_KCP + 16 * s + 4 * h;
-                            const uint2 q0 = hp[0], q1 = hp[1], q2 = hp[2], q3 = hp[3];
-                            const uint4 bh = bform(make_uint4(q0.x, q1.x, q2.x, q3.x), b);
-                            const uint4 bl = bform(make_uint4(q0.y, q1.y, q2.y, q3.y), b);
-                            cacc[cb] = mma_bf16(ah, bh, cacc[cb]);
-                            cacc[cb] = mma_bf16(ah, bl, cacc[cb]);
-                            cacc[cb] = mma_bf16(al, bh, cacc[cb]);
-                        }
-                    }
-                }
+                if (s + 2 < KS) make_tab(s + 2, s & 1);   // read after the next step's first barrier
             }
-            // Coil weight conj(C_c[j]) per voxel (1 without coils).
+        };
+        if (active) run(std::true_type{});
+        else run(std::false_type{});
+
+        if (!active) continue;
+        const float inv = 1.f / (sc * kPhaseScale);
 #pragma unroll
-            for (int cb = 0; cb < 4; ++cb)
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float own = cacc[cb][i];
-                    const float oth = __shfl_xor(own, 1);
-                    if (coil == nullptr) {
-                        vacc[cb][i] += own;
-                    } else {
-                        const float vr = b == 0 ? own : oth, vi = b == 0 ? oth : own;
-                        const int iy = iy_base + 16 * wave + 4 * h + i;
-                        const int ix = ix_base + 8 * cb + ((lane & 15) >> 1);
-                        float2 cc = make_float2(0.f, 0.f);
-                        if (iy < ny && ix < nx) cc = coil[(size_t)c * nv + (size_t)iy * nx + ix];
-                        // conj(cc) * (vr + i vi)
-                        vacc[cb][i] += b == 0 ? cc.x * vr + cc.y * vi : cc.x * vi - cc.y * vr;
+            for (int t = 0; t < NT; ++t) {
+                const int iy = y0 + 16 * (NT * wr + t) + (lane & 15);
+                const int ix = x0 + 32 * ws + 16 * i + 4 * (lane >> 4);
+                if (iy >= ny) continue;
+                const size_t j = (size_t)iy * nx + ix;
+                float2* dst = V + (size_t)n * nv + j;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    if (ix + r >= nx) break;
+                    float2 v = make_float2(inv * vr[i][t][r], inv * vi[i][t][r]);
+                    if (coil != nullptr) {   // conj(C_c) v, summed over the coils
+                        const float2 cc = coil[(size_t)c * nv + j + r];
+                        v = make_float2(cc.x * v.x + cc.y * v.y, cc.x * v.y - cc.y * v.x);
+                        if (c > 0) {
+                            const float2 old = dst[r];
+                            v.x += old.x;
+                            v.y += old.y;
+                        }
                     }
-                }
-        }
-        // A_p += mu_p[n, j] V[j] (the lane's part of V).
-#pragma unroll
-        for (int cb = 0; cb < 4; ++cb)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int iy = iy_base + 16 * wave + 4 * h + i;
-                const int ix = ix_base + 8 * cb + ((lane & 15) >> 1);
-                if (iy < ny && ix < nx) {
-                    const size_t j = (size_t)iy * nx + ix;
-#pragma unroll
-                    for (int p = 0; p < NTR; ++p)
-                        aacc[cb][i][p] = fmaf(ld_train(trains + p * plane + (size_t)n * nv + j), vacc[cb][i],
-                                              aacc[cb][i][p]);
+                    dst[r] = v;
                 }
             }
     }
-    const int planes = NTR == 1 ? 2 : 8;
-#pragma unroll
-    for (int cb = 0; cb < 4; ++cb)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int iy = iy_base + 16 * wave + 4 * h + i;
-            const int ix = ix_base + 8 * cb + ((lane & 15) >> 1);
-            if (iy < ny && ix < nx) {
-                const size_t j = (size_t)iy * nx + ix;
-                const bool on = mask == nullptr || mask[j] != 0;
-                float* dst = apart + (size_t)chunk * planes * nv + j;
-#pragma unroll
-                for (int p = 0; p < NTR; ++p) dst[(size_t)(2 * p + b) * nv] = on ? aacc[cb][i][p] : 0.f;
-            }
-        }
 }
 
-template <typename TT, bool SPLIT>
-hipError_t x_launch(const Dims& d, int mode_y, const TT* trains, const float* theta, const float* v,
-                    const uint8_t* mask, float2* X, hipStream_t s)
+// ------------------------------------------------------------------------
+// A_p[j] = sum_n mu_p[n,j] V[n][j] over the TRs of a chunk, two voxels per
+// thread: chunk partials apart[chunk][2 p + (re, im)][j] with 8 planes per
+// chunk (2 for the m train alone), the layout of the Cartesian adjoint, so the
+// same gradient assembly follows. A streaming pass over V and the trains.
+// ------------------------------------------------------------------------
+template <int NTR, typename TT>
+__global__ __launch_bounds__(256) void nc_acc_kernel(const TT* __restrict__ trains, const float2* __restrict__ V,
+                                                     const uint8_t* __restrict__ mask, float* __restrict__ apart,
+                                                     int nv, int T, int per)
 {
-    const unsigned blocks = (unsigned)std::min<size_t>(((size_t)d.T * d.nv + 255) / 256, 8192);
+    typedef TT V2 __attribute__((ext_vector_type(2), aligned(sizeof(TT))));
+    typedef float F4 __attribute__((ext_vector_type(4), aligned(8)));
+    constexpr int NB = 4;   // TRs whose loads are issued together
+    // The last thread of an odd image takes its last two voxels and stores the
+    // second one (one voxel: reads it twice).
+    const int j0 = 2 * (blockIdx.x * 256 + threadIdx.x);
+    if (j0 >= nv) return;
+    const int j = min(j0, max(nv - 2, 0));
+    const bool pair = nv > 1;
+    const int n0 = blockIdx.y * per, n1 = min(T, n0 + per);
+    const size_t plane = (size_t)T * nv;
+    float acc[2][NTR][2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+#pragma unroll
+        for (int p = 0; p < NTR; ++p) acc[e][p][0] = acc[e][p][1] = 0.f;
+    for (int n = n0; n < n1; n += NB) {
+        F4 v[NB];
+        V2 m[NB][NTR];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const size_t at = (size_t)min(n + b, n1 - 1) * nv + j;
+            if (pair) {
+                v[b] = *reinterpret_cast<const F4*>(V + at);
+#pragma unroll
+                for (int p = 0; p < NTR; ++p) m[b][p] = *reinterpret_cast<const V2*>(trains + p * plane + at);
+            } else {
+                v[b] = F4{V[at].x, V[at].y, V[at].x, V[at].y};
+#pragma unroll
+                for (int p = 0; p < NTR; ++p) m[b][p] = V2{trains[p * plane + at], trains[p * plane + at]};
+            }
+        }
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            if (n + b >= n1) break;
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+#pragma unroll
+                for (int p = 0; p < NTR; ++p) {
+                    const float mu = (float)m[b][p][e];
+                    acc[e][p][0] = fmaf(mu, v[b][2 * e], acc[e][p][0]);
+                    acc[e][p][1] = fmaf(mu, v[b][2 * e + 1], acc[e][p][1]);
+                }
+        }
+    }
+    constexpr int planes = NTR == 1 ? 2 : 8;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        if (j + e < j0 || (e == 1 && !pair)) continue;
+        const bool on = mask == nullptr || mask[j + e] != 0;
+        float* dst = apart + (size_t)blockIdx.y * planes * nv + j + e;
+#pragma unroll
+        for (int p = 0; p < NTR; ++p)
+#pragma unroll
+            for (int k = 0; k < 2; ++k) dst[(size_t)(2 * p + k) * nv] = on ? acc[e][p][k] : 0.f;
+    }
+}
+
+template <typename TT>
+hipError_t x_launch(const Dims& d, int mode_y, const TT* trains, const float* theta, const float* v,
+                    const uint8_t* mask, const float2* coil, const XStore& X, int n_first, int n_count, int n_coils,
+                    hipStream_t s)
+{
+    const dim3 grid(ceil_div(d.ny, 4), ceil_div(n_count, NC_XT));
+#define NC_X(N) nc_x_kernel<N, TT><<<grid, 256, 0, s>>>(trains, theta, v, mask, coil, X, d.nx, d.ny, d.nv, d.T, n_first, \
+                                                       n_count, n_coils)
     switch (mode_y) {
-    case 0: nc_x_kernel<1, TT, SPLIT><<<blocks, 256, 0, s>>>(trains, theta, v, mask, X, d.nv, d.T); break;
-    case 1: nc_x_kernel<4, TT, SPLIT><<<blocks, 256, 0, s>>>(trains, theta, v, mask, X, d.nv, d.T); break;
-    case 3: nc_x_kernel<3, TT, SPLIT><<<blocks, 256, 0, s>>>(trains, theta, v, mask, X, d.nv, d.T); break;
+    case 0: NC_X(1); break;
+    case 1: NC_X(4); break;
+    case 3: NC_X(3); break;
     default: return hipErrorInvalidValue;
     }
+#undef NC_X
     return hipGetLastError();
 }
 
-template <int ENC, int MODE, bool PRE>
-hipError_t fwd_launch(const Dims& d, const float2* X, const float2* coil, const double* ax, const double* ay,
-                      const float2* data, float2* out, double* red, int* nred, hipStream_t s)
-{
-    const int KT = ceil_div(d.nk, 64);
-    // LDS row stride: one K part's columns and two entries of padding, which
-    // put the 8 rows that one B operand read touches in different banks; rows
-    // stay 16-byte aligned.
-    const int nxp = std::min(ceil_div(d.nx, 16) * 16, NC_PCOLS) + 2;
-    const dim3 grid(8 * KT * ceil_div(d.T, 8), d.C);
-    const size_t lds = (ENC == 1 ? 2 * (size_t)NC_ROWS * nxp + 1 : (size_t)NC_ROWS * nxp) * 8;
-    nc_fwd_kernel<ENC, MODE, PRE><<<grid, 256, lds, s>>>(X, coil, ax, ay, data, out, red, d.nx, d.ny, d.nv, d.T,
-                                                         d.nk, KT, nxp);
-    if (nred) *nred = (int)(grid.x * grid.y);
-    return hipGetLastError();
-}
-
-template <int ENC, bool PRE>
-hipError_t fwd_mode(const Dims& d, int mode_x, const float2* X, const float2* coil, const double* ax,
-                    const double* ay, const float2* data, float2* out, double* red, int* nred, hipStream_t s)
-{
-    if (mode_x == 0) return fwd_launch<ENC, 0, PRE>(d, X, coil, ax, ay, data, out, red, nred, s);
-    if (mode_x == 1) return fwd_launch<ENC, 1, PRE>(d, X, coil, ax, ay, data, out, red, nred, s);
-    return fwd_launch<ENC, 2, PRE>(d, X, coil, ax, ay, data, out, red, nred, s);
-}
-
-template <int ENC, typename TT>
-hipError_t adj_typed(const Dims& d, int ntr, int chunks, const TT* trains, const float2* coil,
-                     const uint8_t* mask, const double* ax, const double* ay, const float2* w, float* apart,
-                     hipStream_t s)
+template <typename TT>
+hipError_t acc_launch(const Dims& d, int ntr, int chunks, const TT* trains, const float2* V, const uint8_t* mask,
+                      float* apart, hipStream_t s)
 {
     // Exactly `chunks` chunks (the count the gradient assembly sums), each
     // holding at least one TR.
     const int per = ceil_div(d.T, chunks);
-    const int nch = ceil_div(d.T, per);
-    if (chunks < 1 || nch != chunks) return hipErrorInvalidValue;
-    const int ntx = ceil_div(d.nx, NCA_TX);
-    const dim3 grid(ntx * ceil_div(d.ny, NCA_TY), nch);
-#define NC_ADJ(NT) nc_adj_kernel<ENC, NT, TT><<<grid, 256, 0, s>>>(trains, coil, mask, ax, ay, w, apart, d.nx, \
-                                                                  d.ny, d.nv, d.T, d.nk, d.C, per, ntx)
+    if (chunks < 1 || ceil_div(d.T, per) != chunks) return hipErrorInvalidValue;
+    const dim3 grid(ceil_div(d.nv, 512), chunks);
     if (ntr == 1)
-        NC_ADJ(1);
+        nc_acc_kernel<1, TT><<<grid, 256, 0, s>>>(trains, V, mask, apart, d.nv, d.T, per);
     else if (ntr == 3)
-        NC_ADJ(3);
+        nc_acc_kernel<3, TT><<<grid, 256, 0, s>>>(trains, V, mask, apart, d.nv, d.T, per);
     else
-        NC_ADJ(4);
-#undef NC_ADJ
+        nc_acc_kernel<4, TT><<<grid, 256, 0, s>>>(trains, V, mask, apart, d.nv, d.T, per);
     return hipGetLastError();
 }
+
+// 16-row tiles per wave: 32 NT rows per pass (or block), at most 224, the
+// fewest that divide the image's rows into equal passes.
+int row_tiles(int ny) { return ceil_div(ny, 32 * ceil_div(ny, 224)); }
+
+// How the forward's TRs and coils go in passes that the workspace holds: the
+// main store (T nv 8 bytes; rows padded to 8 columns and the scales may leave
+// a few TRs out) and the small one (nv 512 bytes).
+struct Passes {
+    XStore X;
+    int coils, trs;   // per pass
+};
+Passes fwd_passes(const Dims& d, void* main_store, void* small)
+{
+    Passes p;
+    p.X.nx8 = ceil_div(d.nx, 8) * 8;
+    p.X.rec = x_planes(d.ny, p.X.nx8) + (size_t)(4 * d.ny + 15) / 16 * 16;
+    p.X.a = static_cast<char*>(main_store);
+    p.X.b = static_cast<char*>(small);
+    p.X.split = (int)((size_t)d.T * d.nv * 8 / p.X.rec);
+    const int cap = p.X.split + (int)((size_t)d.nv * 512 / p.X.rec);
+    p.coils = std::min(d.C, cap);
+    p.trs = std::min(d.T, cap / p.coils);
+    return p;
+}
+
+int fwd_grid(int nk, int recs) { return 8 * ceil_div(nk, NC_MS) * ceil_div(recs, 8); }
 
 }  // namespace
 
 int nc_adj_chunks(const Dims& d)
 {
-    // Enough blocks to fill the chip at least twice with partial sums kept
-    // modest (chunks x 8 floats per voxel).
-    const int tiles = ceil_div(d.nx, NCA_TX) * ceil_div(d.ny, NCA_TY);
-    int ch = std::max(1, ceil_div(512, tiles));
-    ch = std::min(ch, 32);
-    return std::min(ch, d.T);
+    // Enough blocks (512 voxels each) to fill the chip with the streaming pass
+    // over V and the trains, with partial sums kept modest (chunks x 8 floats
+    // per voxel, at most 32 chunks and, for narrow images, 512 per 32 x 64
+    // voxels).
+    const int tiles = ceil_div(d.nx, 32) * ceil_div(d.ny, 64);
+    return std::min({ceil_div(1024, ceil_div(d.nv, 512)), ceil_div(512, tiles), 32, d.T});
 }
 
-int nc_fwd_blocks(const Dims& d) { return 8 * ceil_div(d.nk, 64) * ceil_div(d.T, 8) * d.C; }
+int nc_fwd_blocks(const Dims& d) { return d.C * d.T * ceil_div(d.nk, NC_MS); }
 
 hipError_t launch_nc_fwd(const Dims& d, int enc, int mode_y, int mode_x, const void* trains, bool f16,
                          const float* theta, const float* v, const float2* coil, const uint8_t* mask,
-                         const double* ax, const double* ay, float2* X, const float2* data, float2* out,
+                         const double* ax, const double* ay, void* X, void* small, const float2* data, float2* out,
                          double* red, int* nred, hipStream_t s)
 {
-    if (d.nx > 256) return hipErrorInvalidValue;
-    // The split-BF16 forward without coil weights takes the values split once.
-    const bool pre = enc == 1 && coil == nullptr;
-    hipError_t e;
-    if (f16) {
-        const _Float16* tr = static_cast<const _Float16*>(trains);
-        e = pre ? x_launch<_Float16, true>(d, mode_y, tr, theta, v, mask, X, s)
-                : x_launch<_Float16, false>(d, mode_y, tr, theta, v, mask, X, s);
-    } else {
-        const float* tr = static_cast<const float*>(trains);
-        e = pre ? x_launch<float, true>(d, mode_y, tr, theta, v, mask, X, s)
-                : x_launch<float, false>(d, mode_y, tr, theta, v, mask, X, s);
+    if (d.nx > 256 || (enc != 0 && enc != 1)) return hipErrorInvalidValue;
+    const Passes p = fwd_passes(d, X, small);
+    const int KT = ceil_div(d.nk, NC_MS), nt = row_tiles(d.ny);
+    for (int c = 0; c < d.C; c += p.coils) {
+        const int nc = std::min(p.coils, d.C - c);
+        const float2* cc = coil == nullptr ? nullptr : coil + (size_t)c * d.nv;
+        const size_t at = (size_t)c * d.T * d.nk;
+        for (int n = 0; n < d.T; n += p.trs) {
+            const int cnt = std::min(p.trs, d.T - n);
+            hipError_t e = f16 ? x_launch(d, mode_y, static_cast<const _Float16*>(trains), theta, v, mask, cc, p.X, n,
+                                          cnt, nc, s)
+                               : x_launch(d, mode_y, static_cast<const float*>(trains), theta, v, mask, cc, p.X, n,
+                                          cnt, nc, s);
+            if (e != hipSuccess) return e;
+            const int grid = fwd_grid(d.nk, cnt * nc);
+#define NC_FWD(N)                                                                                                  \
+    case N:                                                                                                       \
+        nc_fwd_kernel<N><<<grid, 512, 0, s>>>(p.X, ax, ay, data == nullptr ? nullptr : data + at, out + at,       \
+                                              red == nullptr ? nullptr : red + (size_t)c * d.T * KT, mode_x, d.nx, d.ny, d.T, n,  \
+                                              cnt, nc, d.nk, KT);                                                 \
+        break;
+            switch (nt) {
+                NC_FWD(1) NC_FWD(2) NC_FWD(3) NC_FWD(4) NC_FWD(5) NC_FWD(6) NC_FWD(7)
+            default: return hipErrorInvalidValue;
+            }
+#undef NC_FWD
+            e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
     }
-    if (e != hipSuccess) return e;
-    if (enc == 0) return fwd_mode<0, false>(d, mode_x, X, coil, ax, ay, data, out, red, nred, s);
-    return pre ? fwd_mode<1, true>(d, mode_x, X, coil, ax, ay, data, out, red, nred, s)
-               : fwd_mode<1, false>(d, mode_x, X, coil, ax, ay, data, out, red, nred, s);
+    if (nred) *nred = nc_fwd_blocks(d);
+    return hipSuccess;
 }
 
 hipError_t launch_nc_adj(const Dims& d, int enc, int ntr, int chunks, const void* trains, bool f16,
                          const float2* coil, const uint8_t* mask, const double* ax, const double* ay,
-                         const float2* w, float* apart, hipStream_t s)
+                         const float2* w, float2* V, float* apart, hipStream_t s)
 {
-    if (enc == 0)
-        return f16 ? adj_typed<0>(d, ntr, chunks, static_cast<const _Float16*>(trains), coil, mask, ax, ay, w,
-                                  apart, s)
-                   : adj_typed<0>(d, ntr, chunks, static_cast<const float*>(trains), coil, mask, ax, ay, w, apart, s);
-    return f16 ? adj_typed<1>(d, ntr, chunks, static_cast<const _Float16*>(trains), coil, mask, ax, ay, w, apart, s)
-               : adj_typed<1>(d, ntr, chunks, static_cast<const float*>(trains), coil, mask, ax, ay, w, apart, s);
+    if (enc != 0 && enc != 1) return hipErrorInvalidValue;
+    const int nt = row_tiles(d.ny), ntx = ceil_div(d.nx, NCA_TX);
+    const int tiles = ntx * ceil_div(d.ny, 32 * nt);
+    const unsigned grid = 8u * tiles * ceil_div(d.T, 8);
+#define NC_ADJ(N)                                                                                                  \
+    case N: nc_adj_kernel<N><<<grid, 512, 0, s>>>(coil, ax, ay, w, V, d.nx, d.ny, d.nv, d.T, d.nk, d.C, ntx, tiles); break;
+    switch (nt) {
+        NC_ADJ(1) NC_ADJ(2) NC_ADJ(3) NC_ADJ(4) NC_ADJ(5) NC_ADJ(6) NC_ADJ(7)
+    default: return hipErrorInvalidValue;
+    }
+#undef NC_ADJ
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    return f16 ? acc_launch(d, ntr, chunks, static_cast<const _Float16*>(trains), V, mask, apart, s)
+               : acc_launch(d, ntr, chunks, static_cast<const float*>(trains), V, mask, apart, s);
 }
 
 }  // namespace mrstat
