@@ -479,8 +479,9 @@ __global__ __launch_bounds__(1024) void ystage_fwd_coil_kernel(
     }
 }
 
-// Sums the row-block partials of the forward y-stage into block 0.
-__global__ void usum_kernel(float2* __restrict__ upart, int nby, size_t count)
+// out = scale times the sum of the forward y-stage's row-block partials (out
+// may be block 0).
+__global__ void usum_kernel(const float2* upart, float2* out, int nby, size_t count, float scale)
 {
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= count) return;
@@ -501,7 +502,7 @@ __global__ void usum_kernel(float2* __restrict__ upart, int nby, size_t count)
         s.x += t.x;
         s.y += t.y;
     }
-    upart[i] = s;
+    out[i] = make_float2(scale * s.x, scale * s.y);
 }
 
 // ------------------------------------------------------------------------
@@ -1744,7 +1745,14 @@ hipError_t launch_usum(const Dims& d, float2* upart, int nby, hipStream_t s)
 {
     if (nby <= 1) return hipSuccess;
     const size_t count = (size_t)d.C * d.T * d.nx;
-    usum_kernel<<<(unsigned)((count + 255) / 256), 256, 0, s>>>(upart, nby, count);
+    usum_kernel<<<(unsigned)((count + 255) / 256), 256, 0, s>>>(upart, upart, nby, count, 1.f);
+    return hipGetLastError();
+}
+
+hipError_t launch_uscale(const Dims& d, const float2* upart, int nby, float scale, float2* out, hipStream_t s)
+{
+    const size_t count = (size_t)d.C * d.T * d.nx;
+    usum_kernel<<<(unsigned)((count + 255) / 256), 256, 0, s>>>(upart, out, nby, count, scale);
     return hipGetLastError();
 }
 

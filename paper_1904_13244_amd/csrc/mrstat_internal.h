@@ -152,6 +152,8 @@ hipError_t launch_ystage_fwd(const Dims& d, const YPlan& p, int mode, const void
 // Sums the nby row-block partials of U written by the forward y-stage into
 // partial 0 (nothing to do for nby = 1).
 hipError_t launch_usum(const Dims& d, float2* upart, int nby, hipStream_t s);
+// out = scale times that sum (nby >= 1).
+hipError_t launch_uscale(const Dims& d, const float2* upart, int nby, float scale, float2* out, hipStream_t s);
 
 // x-stage forward GEMM: s[c][n][k] = sum_ix Ex[k][ix] U[c][n][ix].
 // mode 0: out = data - s and per-block FP64 sums of |out|^2 into red;
