@@ -348,135 +348,127 @@ void ystage_fwd_wide_kernel(
 }
 
 // ------------------------------------------------------------------------
-// Forward y-stage with coils (CC = 8 or 16 coil slots). The per-wave sums of
-// CC coils make the chunk-wide LDS staging above hold only 1-2 TRs, so the
-// voxel weights and coil maps would be re-read every 2 TRs. Here each TR's
-// per-wave sums go to one of two LDS buffers and are reduced across the
-// waves right after a single barrier (the next TR uses the other buffer), so
-// a block streams a long TR chunk with its voxels' weights and coil maps in
-// registers. The next TR's trains are loaded before that barrier. Layout as
-// G = 0 above: two rows of 32 columns per wave, R row steps per lane.
+// Forward y-stage with coils (CC = 8 or 16 coil slots): a block of CW waves
+// takes TB TRs, XW columns and a slab of rows; its waves walk the rows (one
+// row of 64 columns, or two of 32 per wave and step), load each voxel's
+// weights and coil sensitivities (from L2: the blocks of neighbouring TRs
+// share them, the grid's fastest axis) and add its TB x CC terms to sums in
+// registers, which meet across the waves in LDS once per block. Bound by the
+// vector units (four of about eleven FMAs per voxel, TR and pair of coils).
+// Per TR the previous layout's 16 waves exchanged every coil's sum through LDS.
 // ------------------------------------------------------------------------
-template <int MODE, int R, int CC, typename TT, int TB>
-__global__ __launch_bounds__(1024) void ystage_fwd_coil_kernel(
+constexpr int CW = 8;
+__host__ __device__ constexpr int coil_trs(int cc) { return 32 / cc; }   // TRs per block of the forward
+
+template <int MODE, int CC, int XW, typename TT>
+__global__ __launch_bounds__(CW * 64) void ystage_fwd_coil_kernel(
     const TT* __restrict__ trains, const float* __restrict__ theta, const float* __restrict__ v,
     const float2* __restrict__ coil, const uint8_t* __restrict__ mask,
-    const float2* __restrict__ eytab, float2* __restrict__ U, int nx, int ny, int nv, int T, int C,
-    int n_per_chunk)
+    const float2* __restrict__ eytab, float2* __restrict__ U, int nx, int ny, int nv, int T, int C, int rows)
 {
-    constexpr int RS = 2 * FW;
+    constexpr int TB = coil_trs(CC);
+    constexpr int HR = 64 / XW;                               // rows per wave and step
     constexpr int NT = MODE == 0 ? 1 : (MODE == 1 ? 4 : 3);   // trains read per voxel and TR
-    // LDS: two buffers of per-wave sums [TB][CC][FW][32] (TB TRs per
-    // barrier), then the block's y-phases [TRs per chunk][RS R].
+    // LDS: sums of half of the waves [CW / 2][TB CC][XW]; before that the
+    // slab's y-phases [rows][TB].
     extern __shared__ float2 lds[];
-    float2* eys = lds + 2 * TB * CC * FW * 32;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int xl = lane & 31, half = lane >> 5;
-    const int ix = blockIdx.x * 32 + xl;
-    const int yb = blockIdx.y;
-    const int iyb = yb * RS * R + 2 * wave + half;
-    const int n0 = fwd_chunk(blockIdx.z, gridDim.z) * n_per_chunk;
-    const int n1 = min(T, n0 + n_per_chunk);
-    const bool colok = ix < nx;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int xl = lane % XW;
+    const int ix = blockIdx.y * XW + xl;
+    const int yb = blockIdx.z, y0 = yb * rows, y1 = min(ny, y0 + rows);
+    const int n0 = fwd_chunk(blockIdx.x, gridDim.x) * TB;
     const size_t plane = (size_t)T * nv;
-    for (int e = threadIdx.x; e < (n1 - n0) * RS * R; e += blockDim.x) {
-        const int nl = e / (RS * R), rr = e % (RS * R);
-        const int iy = yb * RS * R + rr;
-        eys[e] = iy < ny ? eytab[(size_t)(n0 + nl) * ny + iy] : make_float2(0.f, 0.f);
+    for (int e = threadIdx.x; e < rows * TB; e += CW * 64) {
+        const int iy = y0 + e / TB, n = n0 + e % TB;
+        lds[e] = iy < y1 && n < T ? eytab[(size_t)n * ny + iy] : make_float2(0.f, 0.f);
     }
+    __syncthreads();
 
-    float2 P[R], Q[R];
-    float v0[R], v1[R], v2[R];
-    int jr[R];
-    float2 cw[R][CC];
+    float2 acc[TB][CC];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int iy = iyb + RS * r;
-        const bool ok = colok && iy < ny;
-        const int j = ok ? iy * nx + ix : 0;   // invalid voxels read voxel 0 with zero weight
-        jr[r] = j;
-        const bool on = ok && (mask == nullptr || mask[j] != 0);
-        const float rr = on ? theta[3 * nv + j] : 0.f, ri = on ? theta[4 * nv + j] : 0.f;
-        P[r] = make_float2(-ri, rr);   // i rho
-        if constexpr (NT > 1) {
-            const float nr = on ? v[3 * nv + j] : 0.f, ni = on ? v[4 * nv + j] : 0.f;
-            Q[r] = make_float2(-ni, nr);   // i nu
-            v0[r] = on ? v[j] : 0.f;
-            v1[r] = on ? v[nv + j] : 0.f;
-            if constexpr (NT == 4) v2[r] = on ? v[2 * nv + j] : 0.f;
+    for (int t = 0; t < TB; ++t)
+#pragma unroll
+        for (int c = 0; c < CC; ++c) acc[t][c] = make_float2(0.f, 0.f);
+    // Columns past the image read its last one, TRs past the sequence the
+    // last one (with a zero phase); neither is stored.
+    const int xc = min(ix, nx - 1);
+    for (int r = HR * wave; r < y1 - y0; r += HR * CW) {
+        const int iyl = HR == 1 ? r : r + lane / XW;
+        const bool rok = iyl < y1 - y0;
+        const int il = rok ? iyl : 0;
+        const unsigned j = (unsigned)((y0 + il) * nx + xc);
+        TT mu[TB][NT];
+#pragma unroll
+        for (int t = 0; t < TB; ++t) {
+            const TT* base = trains + (size_t)min(n0 + t, T - 1) * nv;
+#pragma unroll
+            for (int q = 0; q < NT; ++q) mu[t][q] = (base + q * plane)[j];
+        }
+        const bool on = rok && (mask == nullptr || mask[j] != 0);
+        float2 cw[CC];
+#pragma unroll
+        for (int c = 0; c < CC; ++c) cw[c] = (coil + (size_t)min(c, C - 1) * nv)[j];
+        const float rr = on ? (theta + 3 * (size_t)nv)[j] : 0.f, ri = on ? (theta + 4 * (size_t)nv)[j] : 0.f;
+        float nr = 0.f, ni = 0.f, w0 = 0.f, w1 = 0.f, w2 = 0.f;
+        if constexpr (MODE != 0) {
+            nr = on ? (v + 3 * (size_t)nv)[j] : 0.f;
+            ni = on ? (v + 4 * (size_t)nv)[j] : 0.f;
+            w0 = on ? v[j] : 0.f;
+            w1 = on ? (v + nv)[j] : 0.f;
+            if constexpr (NT == 4) w2 = on ? (v + 2 * (size_t)nv)[j] : 0.f;
         }
 #pragma unroll
-        for (int c = 0; c < CC; ++c)
-            cw[r][c] = (ok && c < C) ? coil[(size_t)c * nv + j] : make_float2(0.f, 0.f);
-    }
-    __syncthreads();   // y-phases staged
-
-    auto load_tr = [&](float (&buf)[R][NT], int n) {
-        const TT* __restrict__ b0 = trains + (size_t)n * nv;
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-#pragma unroll
-            for (int q = 0; q < NT; ++q) buf[r][q] = (float)b0[q * plane + jr[r]];
-    };
-    float nxt[R][NT];
-    load_tr(nxt, n0);
-    int buf = 0;
-    for (int nb = n0; nb < n1; nb += TB) {
-#pragma unroll
-        for (int tb = 0; tb < TB; ++tb) {
-            // TRs past the chunk repeat its last TR; their sums are not stored.
-            const int n = min(nb + tb, n1 - 1);
-            float cur[R][NT];
-#pragma unroll
-            for (int r = 0; r < R; ++r)
-#pragma unroll
-                for (int q = 0; q < NT; ++q) cur[r][q] = nxt[r][q];
-            load_tr(nxt, min(n + 1, n1 - 1));
-            const float2* eyrow = eys + (size_t)(n - n0) * RS * R + 2 * wave + half;
-            float2 acc[CC];
-#pragma unroll
-            for (int c = 0; c < CC; ++c) acc[c] = make_float2(0.f, 0.f);
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                float2 x;
-                if constexpr (MODE == 0) {
-                    x = make_float2(P[r].x * cur[r][0], P[r].y * cur[r][0]);
-                } else {
-                    float a;
-                    if constexpr (NT == 4)
-                        a = fmaf(v0[r], cur[r][1], fmaf(v1[r], cur[r][2], v2[r] * cur[r][3]));
-                    else
-                        a = fmaf(v0[r], cur[r][1], v1[r] * cur[r][2]);
-                    x = make_float2(fmaf(P[r].x, a, Q[r].x * cur[r][0]), fmaf(P[r].y, a, Q[r].y * cur[r][0]));
-                }
-                const float2 z = cmul(eyrow[RS * r], x);
-#pragma unroll
-                for (int c = 0; c < CC; ++c) acc[c] = cfma(cw[r][c], z, acc[c]);
+        for (int t = 0; t < TB; ++t) {
+            const float m0 = (float)mu[t][0];
+            float2 x;   // i rho mu (mode 0); i (rho a + nu mu) (modes 1, 3)
+            if constexpr (MODE == 0) {
+                x = make_float2(-ri * m0, rr * m0);
+            } else {
+                float a = fmaf(w0, (float)mu[t][1], w1 * (float)mu[t][2]);
+                if constexpr (NT == 4) a = fmaf(w2, (float)mu[t][3], a);
+                x = make_float2(-fmaf(ri, a, ni * m0), fmaf(rr, a, nr * m0));
             }
-            float2* red = lds + (size_t)(buf * TB + tb) * CC * FW * 32;
+            const float2 z = cmul(lds[il * TB + t], x);
+#pragma unroll
+            for (int c = 0; c < CC; ++c) acc[t][c] = cfma(cw[c], z, acc[t][c]);
+        }
+    }
+    if constexpr (HR == 2) {
+#pragma unroll
+        for (int t = 0; t < TB; ++t)
 #pragma unroll
             for (int c = 0; c < CC; ++c) {
-                const float2 t = shfl_xor2(acc[c], 32);
-                if (half == 0) red[(c * FW + wave) * 32 + xl] = make_float2(acc[c].x + t.x, acc[c].y + t.y);
+                const float2 o = shfl_xor2(acc[t][c], 32);
+                acc[t][c].x += o.x;
+                acc[t][c].y += o.y;
             }
-        }
-        __syncthreads();
-        // Reduce these TRs across the waves (the next batch writes the other buffer).
-        for (int o = threadIdx.x; o < TB * CC * 32; o += blockDim.x) {
-            const int tb = o / (CC * 32), c = (o >> 5) % CC, l = o & 31;
-            const float2* red = lds + (size_t)(buf * TB + tb) * CC * FW * 32;
-            float2 sum = red[(c * FW) * 32 + l];
-#pragma unroll
-            for (int w = 1; w < FW; ++w) {
-                const float2 t = red[(c * FW + w) * 32 + l];
-                sum.x += t.x;
-                sum.y += t.y;
-            }
-            const int oix = blockIdx.x * 32 + l;
-            if (oix < nx && c < C && nb + tb < n1) U[(((size_t)yb * C + c) * T + nb + tb) * nx + oix] = sum;
-        }
-        buf ^= 1;
     }
+    // Waves h..2h-1 hand their sums to waves 0..h-1.
+#pragma unroll
+    for (int h = CW / 2; h > 0; h /= 2) {
+        __syncthreads();
+        if (wave >= h && wave < 2 * h && lane < XW)
+#pragma unroll
+            for (int t = 0; t < TB; ++t)
+#pragma unroll
+                for (int c = 0; c < CC; ++c) lds[((wave - h) * TB * CC + t * CC + c) * XW + xl] = acc[t][c];
+        __syncthreads();
+        if (wave < h)
+#pragma unroll
+            for (int t = 0; t < TB; ++t)
+#pragma unroll
+                for (int c = 0; c < CC; ++c) {
+                    const float2 o = lds[(wave * TB * CC + t * CC + c) * XW + xl];
+                    acc[t][c].x += o.x;
+                    acc[t][c].y += o.y;
+                }
+    }
+    if (wave == 0 && lane < XW && ix < nx)
+#pragma unroll
+        for (int t = 0; t < TB; ++t)
+#pragma unroll
+            for (int c = 0; c < CC; ++c)
+                if (n0 + t < T && c < C) U[(((size_t)yb * C + c) * T + n0 + t) * nx + ix] = acc[t][c];
 }
 
 // out = scale times the sum of the forward y-stage's row-block partials (out
@@ -762,57 +754,60 @@ __global__ __launch_bounds__(NWA * 64) void ystage_adj_wide_kernel(
 }
 
 // ------------------------------------------------------------------------
-// Adjoint y-stage with coils (CC = 8 or 16 coil slots). A block covers 32
-// columns x 16 rows (two rows per thread), so each TR's W rows of all coils
-// (CC x 32 complex) are staged once in LDS and used by 16 image rows instead
-// of being fetched per voxel; TR batches of NBA are double-buffered (the next
-// batch's W is loaded into registers while the current one is used, one
-// barrier per batch). Partial sums per TR chunk as in the kernel above.
+// Adjoint y-stage with coils (CC = 8 or 16 coil slots). A block of CW waves
+// covers XW columns and two rows (of 64 columns; two of 32 twice) per wave, so
+// each TR's W rows of all coils (CC x XW complex) are staged once in LDS and
+// used by every row of the block instead of being fetched per voxel; TR
+// batches of NBA are double-buffered (the next batch's W is loaded into
+// registers while the current one is used, one barrier per batch). Bound by
+// the vector units. Partial sums per TR chunk as in the kernel above.
 // ------------------------------------------------------------------------
-template <int NTRAIN, int CC, int NBA, typename TT>
-__global__ __launch_bounds__(256) void ystage_adj_coil_kernel(
+template <int NTRAIN, int CC, int XW, int NBA, typename TT>
+__global__ __launch_bounds__(CW * 64) __attribute__((amdgpu_waves_per_eu(CC > 8 ? 2 : 4))) void ystage_adj_coil_kernel(
     const TT* __restrict__ trains, const float2* __restrict__ coil,
     const uint8_t* __restrict__ mask, const float2* __restrict__ eytab,
     const float2* __restrict__ W, float* __restrict__ apart, int nx, int ny, int nv, int T,
     int C, int n_per_chunk)
 {
-    constexpr int RY = 2, BR = 8 * RY;               // rows per thread, rows per block
-    constexpr int WT = NBA * CC * 32;                 // float2 per W tile
-    constexpr int WPT = (WT + 255) / 256;             // W loads per thread
+    constexpr int HR = 64 / XW, RY = 2, BR = RY * HR * CW;   // rows per block
+    constexpr int NTH = CW * 64;
+    constexpr int WT = NBA * CC * XW;                 // float2 per W tile
+    constexpr int WPT = (WT + NTH - 1) / NTH;         // W loads per thread
     extern __shared__ float2 sm[];
-    float2* Ws = sm;                                  // [2][NBA][CC][32]
-    float2* eys = sm + 2 * WT;                        // [n_per_chunk][BR]
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-    const int ix = blockIdx.x * 32 + tx;
+    float2* Ws = sm;                                  // [2][NBA][CC][XW]
+    float2* eys = sm + 2 * WT;                        // y-phases [2][NBA][BR]
+    static_assert(NBA * BR <= NTH, "one y-phase per thread");
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int tx = lane % XW, ty = HR * wave + lane / XW;   // rows ty + HR CW u
+    const int ix = blockIdx.x * XW + tx;
     const int row0 = blockIdx.y * BR;
     const int chunk = blockIdx.z;
     const int n0 = chunk * n_per_chunk;
     const int n1 = min(T, n0 + n_per_chunk);
     const size_t plane = (size_t)T * nv;
-    for (int e = threadIdx.x; e < (n1 - n0) * BR; e += 256) {
-        const int nl = e / BR, rr = e % BR;
-        const int iy = row0 + rr;
-        eys[e] = iy < ny ? eytab[(size_t)(n0 + nl) * ny + iy] : make_float2(0.f, 0.f);
-    }
     int jr[RY];
     bool ok[RY];
     float2 cw[RY][CC];
 #pragma unroll
     for (int u = 0; u < RY; ++u) {
-        const int iy = row0 + ty + 8 * u;
+        const int iy = row0 + ty + HR * CW * u;
         ok[u] = ix < nx && iy < ny;
         jr[u] = ok[u] ? iy * nx + ix : 0;
 #pragma unroll
         for (int c = 0; c < CC; ++c)
             cw[u][c] = (ok[u] && c < C) ? coil[(size_t)c * nv + jr[u]] : make_float2(0.f, 0.f);
     }
-    // W tile of the batch starting at TR nb: [b][c][column], zero outside.
+    // W tile of the batch starting at TR nb: [b][c][column], zero outside, and
+    // its y-phases.
+    float2 er;
     auto load_w = [&](float2 (&wr)[WPT], int nb) {
+        const int eb = threadIdx.x / BR, iy = row0 + threadIdx.x % BR;
+        er = eb < NBA && nb + eb < n1 && iy < ny ? eytab[(size_t)(nb + eb) * ny + iy] : make_float2(0.f, 0.f);
 #pragma unroll
         for (int i = 0; i < WPT; ++i) {
-            const int e = threadIdx.x + 256 * i;
-            const int b = e / (CC * 32), c = (e / 32) % CC, col = e % 32;
-            const int n = nb + b, x = blockIdx.x * 32 + col;
+            const int e = threadIdx.x + NTH * i;
+            const int b = e / (CC * XW), c = (e / XW) % CC, col = e % XW;
+            const int n = nb + b, x = blockIdx.x * XW + col;
             wr[i] = (e < WT && n < n1 && c < C && x < nx) ? W[((size_t)c * T + n) * nx + x]
                                                           : make_float2(0.f, 0.f);
         }
@@ -820,9 +815,10 @@ __global__ __launch_bounds__(256) void ystage_adj_coil_kernel(
     auto store_w = [&](const float2 (&wr)[WPT], int buf) {
 #pragma unroll
         for (int i = 0; i < WPT; ++i) {
-            const int e = threadIdx.x + 256 * i;
+            const int e = threadIdx.x + NTH * i;
             if (e < WT) Ws[buf * WT + e] = wr[i];
         }
+        if (threadIdx.x < NBA * BR) eys[buf * NBA * BR + threadIdx.x] = er;
     };
     float2 wr[WPT];
     load_w(wr, n0);
@@ -851,20 +847,21 @@ __global__ __launch_bounds__(256) void ystage_adj_coil_kernel(
         const float2* wt = Ws + buf * WT;
 #pragma unroll
         for (int b = 0; b < NBA; ++b) {
-            const int nl = min(nb0 + b, n1 - 1) - n0;
-            const float keep = (nb0 + b < n1) ? 1.f : 0.f;
+            float2 wc[RY];
+#pragma unroll
+            for (int u = 0; u < RY; ++u) wc[u] = make_float2(0.f, 0.f);
+#pragma unroll
+            for (int c = 0; c < CC; ++c) {   // W is zero for TRs past the chunk
+                const float2 t = wt[(b * CC + c) * XW + tx];
+#pragma unroll
+                for (int u = 0; u < RY; ++u) {   // + conj(cw) t
+                    wc[u].x = fmaf(cw[u][c].x, t.x, fmaf(cw[u][c].y, t.y, wc[u].x));
+                    wc[u].y = fmaf(cw[u][c].x, t.y, fmaf(-cw[u][c].y, t.x, wc[u].y));
+                }
+            }
 #pragma unroll
             for (int u = 0; u < RY; ++u) {
-                float2 wc = make_float2(0.f, 0.f);
-#pragma unroll
-                for (int c = 0; c < CC; ++c) {
-                    const float2 t = cmulconj(cw[u][c], wt[(b * CC + c) * 32 + tx]);
-                    wc.x += t.x;
-                    wc.y += t.y;
-                }
-                float2 V = cmulconj(eys[nl * BR + ty + 8 * u], wc);
-                V.x *= keep;
-                V.y *= keep;
+                const float2 V = cmulconj(eys[(buf * NBA + b) * BR + ty + HR * CW * u], wc[u]);
 #pragma unroll
                 for (int p = 0; p < NTRAIN; ++p) {
                     acc[u][p].x = fmaf(mu[b][u][p], V.x, acc[u][p].x);
@@ -1475,6 +1472,10 @@ void xgemm_any(dim3 grid, hipStream_t s, const float2* A, const float2* extab, c
     xgemm_f32_kernel<DIR, MODE><<<grid, 256, 0, s>>>(A, extab, data, out, red, M, nx, nk, per, stride);
 }
 
+// Coil y-stages: 64 columns per wave (its one row is then uniform and a row
+// segment whole lines), or two rows of 32 where that leaves fewer columns over.
+bool coil_wide(const Dims& d) { return ceil_div(d.nx, 64) * 64 == ceil_div(d.nx, 32) * 32; }
+
 template <int MODE, int CC, typename TT>
 hipError_t fwd_R(const Dims& d, const YPlan& p, const TT* trains, const float* theta,
                  const float* v, const float2* coil, const uint8_t* mask, const float2* eytab,
@@ -1507,7 +1508,7 @@ hipError_t fwd_R(const Dims& d, const YPlan& p, const TT* trains, const float* t
             return hipErrorInvalidValue;
         }
     }
-    *nby_used = CC > 1 ? p.nbyc : ((sizeof(TT) == 2 && p.g16 > 0) ? p.nby16 : p.nby);
+    *nby_used = (sizeof(TT) == 2 && p.g16 > 0) ? p.nby16 : p.nby;
     // 2-byte trains, one coil: one row per wave, all columns per block.
     if constexpr (sizeof(TT) == 2 && CC == 1) {
         if (p.g16 > 0) {
@@ -1529,28 +1530,23 @@ hipError_t fwd_R(const Dims& d, const YPlan& p, const TT* trains, const float* t
         }
     }
     if constexpr (CC > 1) {
-        // Coils: per-TR reduction, long TR chunks.
-        dim3 grid(ceil_div(d.nx, 32), p.nbyc, ceil_div(d.T, p.fwd_trc));
-        // TRs per barrier (LDS 2 TB CC 16 KB): 2 for up to 8 coils (256 x 256,
-        // 8 coils, 1280 TRs: FP16 trains 329 -> 261 us, FP32 395 -> 350 us).
-        constexpr int TB = CC <= 8 ? 2 : 1;
-        const size_t lds = (size_t)(2 * TB * CC * FW * 32 + p.fwd_trc * 2 * FW * p.r_fwdc) * sizeof(float2);
-#define FWDC_CASE(RR)                                                                           \
-    if (p.r_fwdc == RR) {                                                                       \
-        if (lds > 65536) {                                                                      \
-            const hipError_t ea = hipFuncSetAttribute(                                          \
-                reinterpret_cast<const void*>(&ystage_fwd_coil_kernel<MODE, RR, CC, TT, TB>),   \
-                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                          \
-            if (ea != hipSuccess) return ea;                                                    \
-        }                                                                                       \
-        ystage_fwd_coil_kernel<MODE, RR, CC, TT, TB><<<grid, FW * 64, lds, s>>>(                \
-            trains, theta, v, coil, mask, eytab, U, d.nx, d.ny, d.nv, d.T, d.C, p.fwd_trc);     \
-        return hipGetLastError();                                                               \
-    }
-        FWDC_CASE(1)
-        if constexpr (CC <= 8) { FWDC_CASE(2) }
-#undef FWDC_CASE
-        return hipErrorInvalidValue;
+        // Row slabs only where the columns and TRs alone leave the chip (256
+        // CUs, up to 4 blocks each) idle, at most the plan's.
+        constexpr int TB = coil_trs(CC);
+        const bool w64 = coil_wide(d);
+        const int tiles = ceil_div(d.nx, w64 ? 64 : 32), nch = ceil_div(d.T, TB);
+        const int slabs = std::max(ceil_div(d.ny, 1024), std::min(p.nbyc, ceil_div(1024, tiles * nch)));
+        const int rows = ceil_div(d.ny, slabs);
+        *nby_used = ceil_div(d.ny, rows);
+        const dim3 grid(nch, tiles, *nby_used);
+        const size_t lds = std::max((size_t)(CW / 2) * TB * CC * (w64 ? 64 : 32), (size_t)rows * TB) * sizeof(float2);
+        if (w64)
+            ystage_fwd_coil_kernel<MODE, CC, 64, TT><<<grid, CW * 64, lds, s>>>(
+                trains, theta, v, coil, mask, eytab, U, d.nx, d.ny, d.nv, d.T, d.C, rows);
+        else
+            ystage_fwd_coil_kernel<MODE, CC, 32, TT><<<grid, CW * 64, lds, s>>>(
+                trains, theta, v, coil, mask, eytab, U, d.nx, d.ny, d.nv, d.T, d.C, rows);
+        return hipGetLastError();
     }
     dim3 grid(ceil_div(d.nx, 32), p.nby, ceil_div(d.T, p.fwd_tr));
     const size_t lds = (size_t)p.fwd_tr * (CC * FW * 32 + 32 * p.r_fwd) * sizeof(float2);
@@ -1600,13 +1596,23 @@ hipError_t adj_launch(const Dims& d, const YPlan& p, const TT* trains, const flo
         }
     }
     if constexpr (CC > 1) {
-        // Coils: 32 x 16 voxel tiles sharing staged W rows.
-        constexpr int NBA = 4;
-        dim3 grid(ceil_div(d.nx, 32), ceil_div(d.ny, 16), p.adj_chunks);
-        const size_t lds = (size_t)(2 * NBA * CC * 32 + p.adj_per_chunk * 16) * sizeof(float2);
-        ystage_adj_coil_kernel<NTRAIN, CC, NBA, TT><<<grid, 256, lds, s>>>(
-            trains, coil, mask, eytab, W, apart, d.nx, d.ny, d.nv, d.T, d.C, p.adj_per_chunk);
-        return hipGetLastError();
+        constexpr int NBA = 2;
+        const bool w64 = coil_wide(d);
+        const int xw = w64 ? 64 : 32, br = 2 * CW * (64 / xw);
+        const dim3 grid(ceil_div(d.nx, xw), ceil_div(d.ny, br), p.adj_chunks);
+        const size_t lds = (size_t)2 * NBA * (CC * xw + br) * sizeof(float2);
+        auto go = [&](auto kernel) {
+            hipError_t e = hipSuccess;
+            if (lds > 65536)
+                e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            if (e != hipSuccess) return e;
+            kernel<<<grid, CW * 64, lds, s>>>(trains, coil, mask, eytab, W, apart, d.nx, d.ny, d.nv, d.T, d.C,
+                                              p.adj_per_chunk);
+            return hipGetLastError();
+        };
+        return w64 ? go(&ystage_adj_coil_kernel<NTRAIN, CC, 64, NBA, TT>)
+                   : go(&ystage_adj_coil_kernel<NTRAIN, CC, 32, NBA, TT>);
     }
     dim3 grid(ceil_div(d.nv, 256), p.adj_chunks);
     const int rows = std::min(d.ny, 256 / d.nx + 2);
@@ -1632,12 +1638,8 @@ YPlan make_yplan(const Dims& d)
     p.r_fwd = ceil_div(d.ny, 32 * p.nby);
     // TRs per block: the chunk's per-wave sums live in LDS (at most 64 KB).
     p.fwd_tr = d.C == 1 ? 16 : (d.C <= 8 ? 2 : 1);
-    // Coils: per-TR reduction kernel, 2 row steps per lane for up to 8 coils
-    // (1 for 16), 32 TRs per block.
-    p.r_fwdc = d.C <= 8 ? 2 : 1;
-    p.nbyc = ceil_div(d.ny, 2 * FW * p.r_fwdc);
-    p.r_fwdc = ceil_div(d.ny, 2 * FW * p.nbyc);
-    p.fwd_trc = 32;
+    // Coils: row slabs of the forward, of 64 rows at least (32 with 9 to 16 coils).
+    p.nbyc = ceil_div(d.ny, d.C <= 8 ? 64 : 32);
     // One-row-per-wave layout (FP16 trains, one coil): g16 column groups of
     // 64 (a power of two covering nx, so a block spans every column), FW/g16
     // row groups, up to 2 row steps per lane (two blocks per CU), 8 TRs per
@@ -1705,6 +1707,7 @@ hipError_t fwd_typed(const Dims& d, const YPlan& p, int mode, const TT* trains, 
         default: return hipErrorInvalidValue;                                                   \
     }
     if (d.C == 1) FWD_MODES(1)
+    if (d.C <= 4) FWD_MODES(4)
     if (d.C <= 8) FWD_MODES(8)
     FWD_MODES(16)
 #undef FWD_MODES
@@ -1717,16 +1720,19 @@ hipError_t adj_typed(const Dims& d, const YPlan& p, const TT* trains, int ntr_tr
 {
     if (ntr_trains == 4) {
         if (d.C == 1) return adj_launch<4, 1>(d, p, trains, coil, mask, eytab, W, apart, s);
+        if (d.C <= 4) return adj_launch<4, 4>(d, p, trains, coil, mask, eytab, W, apart, s);
         if (d.C <= 8) return adj_launch<4, 8>(d, p, trains, coil, mask, eytab, W, apart, s);
         return adj_launch<4, 16>(d, p, trains, coil, mask, eytab, W, apart, s);
     }
     if (ntr_trains == 3) {
         if (d.C == 1) return adj_launch<3, 1>(d, p, trains, coil, mask, eytab, W, apart, s);
+        if (d.C <= 4) return adj_launch<3, 4>(d, p, trains, coil, mask, eytab, W, apart, s);
         if (d.C <= 8) return adj_launch<3, 8>(d, p, trains, coil, mask, eytab, W, apart, s);
         return adj_launch<3, 16>(d, p, trains, coil, mask, eytab, W, apart, s);
     }
     if (ntr_trains != 1) return hipErrorInvalidValue;
     if (d.C == 1) return adj_launch<1, 1>(d, p, trains, coil, mask, eytab, W, apart, s);
+    if (d.C <= 4) return adj_launch<1, 4>(d, p, trains, coil, mask, eytab, W, apart, s);
     if (d.C <= 8) return adj_launch<1, 8>(d, p, trains, coil, mask, eytab, W, apart, s);
     return adj_launch<1, 16>(d, p, trains, coil, mask, eytab, W, apart, s);
 }

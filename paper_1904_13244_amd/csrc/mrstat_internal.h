@@ -104,7 +104,7 @@ struct YPlan {
     int adj_per_chunk;
     int ksplit_adj;   // split-K of the adjoint x-GEMM (partial W outputs)
     int g16, r_fwd16, nby16, fwd_tr16;   // forward y-stage, FP16 trains, one row per wave
-    int r_fwdc, nbyc, fwd_trc;           // forward y-stage with coils (per-TR reduction)
+    int nbyc;         // forward y-stage with coils: row slabs at most
     int ntw16, ntws16, nbyw, roww;       // forward y-stage, wide layout (FP16 trains): TRs per
                                          // block in mode 1 / mode 0 (0 = off), row slabs, rows
                                          // per slab
