@@ -74,14 +74,32 @@ __device__ __forceinline__ f4 mma(u4 a, u4 b, f4 c)
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8, a), __builtin_bit_cast(h8, b), c, 0, 0, 0);
 }
 
-// 2^e that brings m >= 0 into [2^10, 2^11) (1 for m = 0 or not finite; e is
-// bounded so that 2^-e kPhaseScale^-1 stays a normal number).
-__device__ __forceinline__ float pow2_scale(float m)
+// 2^e that brings the float of bits m (without its sign) into [2^10, 2^11) (1
+// for 0, infinities and NaN; e is bounded so that 2^-e kPhaseScale^-1 stays a
+// normal number).
+__device__ __forceinline__ float pow2_scale(unsigned m)
 {
-    const int b = (int)(__float_as_uint(m) >> 23);   // biased exponent
-    if (m == 0.f || b == 255) return 1.f;
+    const int b = (int)(m >> 23);   // biased exponent
+    if (m == 0u || b == 255) return 1.f;
     const int e = min(137 - b, 118);
     return __uint_as_float((unsigned)(e + 127) << 23);
+}
+
+// Bits of |x|: their order is that of the magnitudes, NaN above infinity.
+__device__ __forceinline__ unsigned mag(float x) { return __float_as_uint(x) & 0x7fffffffu; }
+
+template <int ROR> __device__ __forceinline__ unsigned max_ror(unsigned x)
+{
+    return max(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x120 + ROR, 0xf, 0xf, false));
+}
+// Maximum over the wave, in every lane.
+__device__ __forceinline__ unsigned wave_max(unsigned x)
+{
+    x = max_ror<1>(max_ror<2>(max_ror<4>(max_ror<8>(x))));
+    const auto a = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    x = max(a[0], a[1]);
+    const auto b = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    return max(b[0], b[1]);
 }
 
 typedef __attribute__((address_space(3))) char* lptr;
@@ -128,51 +146,63 @@ struct XStore {
 };
 __host__ __device__ inline size_t x_planes(int ny, int nx8) { return (size_t)8 * ny * nx8; }
 
-template <int NTRV, typename TT>
+template <int NTRV, bool VEC, typename TT>
 __global__ __launch_bounds__(256) void nc_x_kernel(const TT* __restrict__ trains, const float* __restrict__ theta,
                                                    const float* __restrict__ v, const uint8_t* __restrict__ mask,
                                                    const float2* __restrict__ coil, XStore X, int nx, int ny, int nv,
-                                                   int T, int n_first, int n_count, int n_coils)
+                                                   int T, int n_first, int n_count, int n_coils, int per_block)
 {
     const int lane = threadIdx.x & 63;
     const int iy = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (iy >= ny) return;
     const int x0 = 4 * lane;
     const size_t plane = (size_t)T * nv;
+    const size_t jrow = (size_t)iy * nx;
+    // Four adjacent values of a row, without branches: whole vectors where nx
+    // is a multiple of 4 (lanes past the row take its last one), else one by
+    // one (columns past the row its last one); both are masked out below.
+    auto row4 = [&](const auto* p, auto (&o)[4]) {
+        typedef std::remove_const_t<std::remove_reference_t<decltype(*p)>> E;
+        if constexpr (VEC) {
+            struct __attribute__((packed, aligned(sizeof(E) < 4 ? sizeof(E) : 4))) Q { E e[4]; };
+            const Q t = *reinterpret_cast<const Q*>(p + jrow + min(x0, nx - 4));
+#pragma unroll
+            for (int c = 0; c < 4; ++c) o[c] = t.e[c];
+        } else {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) o[c] = p[jrow + min(x0 + c, nx - 1)];
+        }
+    };
     float rr[4], ri[4], w[3][4], nr[4], ni[4];
     bool on[4];
+    row4(theta + 3 * (size_t)nv, rr);
+    row4(theta + 4 * (size_t)nv, ri);
+    if constexpr (NTRV > 1) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        const bool in = x0 + c < nx;
-        const size_t j = (size_t)iy * nx + (in ? x0 + c : 0);
-        on[c] = in && (mask == nullptr || mask[j] != 0);
-        rr[c] = on[c] ? theta[3 * (size_t)nv + j] : 0.f;
-        ri[c] = on[c] ? theta[4 * (size_t)nv + j] : 0.f;
-#pragma unroll
-        for (int q = 0; q < 3; ++q) w[q][c] = on[c] && q < NTRV - 1 ? v[(size_t)q * nv + j] : 0.f;
-        nr[c] = on[c] && NTRV > 1 ? v[3 * (size_t)nv + j] : 0.f;
-        ni[c] = on[c] && NTRV > 1 ? v[4 * (size_t)nv + j] : 0.f;
+        for (int q = 0; q < NTRV - 1; ++q) row4(v + (size_t)q * nv, w[q]);
+        row4(v + 3 * (size_t)nv, nr);
+        row4(v + 4 * (size_t)nv, ni);
     }
-    const bool whole = x0 + 4 <= nx;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) on[c] = x0 + c < nx;
+    if (mask != nullptr) {
+        uint8_t mk[4];
+        row4(mask, mk);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) on[c] = on[c] && mk[c] != 0;
+    }
     const int nt = min(NC_XT, n_count - (int)blockIdx.y * NC_XT);
     float ar[NC_XT][4], ai[NC_XT][4];   // i (rho t + nu mu0); masked voxels zero whatever their trains hold
 #pragma unroll
     for (int k = 0; k < NC_XT; ++k) {
         const int n = n_first + blockIdx.y * NC_XT + (k < nt ? k : 0);
-        const TT* row = trains + (size_t)n * nv + (size_t)iy * nx;
+        TT raw[NTRV][4];
         float m[NTRV][4];
 #pragma unroll
         for (int q = 0; q < NTRV; ++q) {
-            const TT* p = row + q * plane;
-            if (whole) {
-                typedef TT V4 __attribute__((ext_vector_type(4), aligned(sizeof(TT))));
-                const V4 t = *reinterpret_cast<const V4*>(p + x0);
+            row4(trains + (size_t)n * nv + q * plane, raw[q]);
 #pragma unroll
-                for (int c = 0; c < 4; ++c) m[q][c] = (float)t[c];
-            } else {
-#pragma unroll
-                for (int c = 0; c < 4; ++c) m[q][c] = x0 + c < nx ? (float)p[x0 + c] : 0.f;
-            }
+            for (int c = 0; c < 4; ++c) m[q][c] = (float)raw[q][c];
         }
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
@@ -188,31 +218,30 @@ __global__ __launch_bounds__(256) void nc_x_kernel(const TT* __restrict__ trains
             }
         }
     }
-    for (int cl = 0; cl < n_coils; ++cl) {
+    float2 cn[4];   // the next coil's sensitivities
+    const int c0 = blockIdx.z * per_block, c1 = min(n_coils, c0 + per_block);
+    if (coil != nullptr) row4(coil + (size_t)c0 * nv, cn);
+    for (int cl = c0; cl < c1; ++cl) {
         float cr[4], ci[4];
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            const float2 cc = coil != nullptr && on[c] ? coil[(size_t)cl * nv + (size_t)iy * nx + x0 + c]
-                                                       : make_float2(1.f, 0.f);
-            cr[c] = cc.x;
-            ci[c] = cc.y;
+            cr[c] = coil != nullptr ? cn[c].x : 1.f;
+            ci[c] = coil != nullptr ? cn[c].y : 0.f;
         }
+        if (coil != nullptr && cl + 1 < c1) row4(coil + (size_t)(cl + 1) * nv, cn);
 #pragma unroll
         for (int k = 0; k < NC_XT; ++k) {
-            if (k >= nt) break;
-            float xr[4], xi[4], mx = 0.f;
-            bool nan = false;
+            float xr[4], xi[4];
+            unsigned mx = 0u;
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 xr[c] = cr[c] * ar[k][c] - ci[c] * ai[k][c];
                 xi[c] = cr[c] * ai[k][c] + ci[c] * ar[k][c];
-                nan = nan || !(xr[c] == xr[c] && xi[c] == xi[c]);
-                mx = fmaxf(mx, fmaxf(fabsf(xr[c]), fabsf(xi[c])));
+                mx = max(mx, max(mag(xr[c]), mag(xi[c])));
             }
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
             // A value that is not finite makes the row's (and so the TR's) sums so.
-            const float sc = __any(nan) ? 1.f : pow2_scale(mx);
+            const float sc = pow2_scale(wave_max(mx));
+            if (k >= nt) continue;
             char* rec = X.at(cl * n_count + blockIdx.y * NC_XT + k);
             if (lane == 0) reinterpret_cast<float*>(rec + x_planes(ny, X.nx8))[iy] = 1.f / (sc * kPhaseScale);
             if (x0 < X.nx8) {
@@ -471,7 +500,7 @@ __global__ __launch_bounds__(512) void nc_adj_kernel(const float2* __restrict__ 
     __shared__ __attribute__((aligned(16))) char Hs[4][32][AROW];
     __shared__ __attribute__((aligned(16))) char Gs[4][32][BROW];
     __shared__ float2 tab[2][6][32];            // phases of 1, 2, 4 columns / rows per sample
-    __shared__ float wmax[8];
+    __shared__ unsigned wmax[8];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ws = wave & 3, wr = wave >> 2;
@@ -496,16 +525,12 @@ __global__ __launch_bounds__(512) void nc_adj_kernel(const float2* __restrict__ 
     for (int c = 0; c < C; ++c) {
         const float2* wn = w + ((size_t)c * T + n) * nk;
         // Scale of this TR's samples.
-        float mx = 0.f;
-        bool nan = false;
+        unsigned mx = 0u;
         for (int k = tid; k < nk; k += 512) {
             const float2 v = wn[k];
-            nan = nan || !(v.x == v.x && v.y == v.y);
-            mx = fmaxf(mx, fmaxf(fabsf(v.x), fabsf(v.y)));
+            mx = max(mx, max(mag(v.x), mag(v.y)));
         }
-        if (nan) mx = __uint_as_float(0x7f800000u);
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+        mx = wave_max(mx);
         __syncthreads();   // the previous coil's scale and tables have been read
         if (lane == 0) wmax[wave] = mx;
         make_tab(0, 0);
@@ -513,7 +538,7 @@ __global__ __launch_bounds__(512) void nc_adj_kernel(const float2* __restrict__ 
         __syncthreads();
         mx = wmax[0];
 #pragma unroll
-        for (int i = 1; i < 8; ++i) mx = fmaxf(mx, wmax[i]);
+        for (int i = 1; i < 8; ++i) mx = max(mx, wmax[i]);
         const float sc = pow2_scale(mx);
 
         unsigned hv[4][4], gv[4][NT];   // split values: [plane][pair of positions]
@@ -716,9 +741,17 @@ hipError_t x_launch(const Dims& d, int mode_y, const TT* trains, const float* th
                     const uint8_t* mask, const float2* coil, const XStore& X, int n_first, int n_count, int n_coils,
                     hipStream_t s)
 {
-    const dim3 grid(ceil_div(d.ny, 4), ceil_div(n_count, NC_XT));
-#define NC_X(N) nc_x_kernel<N, TT><<<grid, 256, 0, s>>>(trains, theta, v, mask, coil, X, d.nx, d.ny, d.nv, d.T, n_first, \
-                                                       n_count, n_coils)
+    // A block takes all coils of its TRs, or one where that leaves CUs idle.
+    dim3 grid(ceil_div(d.ny, 4), ceil_div(n_count, NC_XT));
+    const int per = (int)(grid.x * grid.y) < 512 ? 1 : n_coils;
+    grid.z = ceil_div(n_coils, per);
+#define NC_X(N)                                                                                                    \
+    if (d.nx % 4 == 0)                                                                                            \
+        nc_x_kernel<N, true, TT><<<grid, 256, 0, s>>>(trains, theta, v, mask, coil, X, d.nx, d.ny, d.nv, d.T,     \
+                                                      n_first, n_count, n_coils, per);                            \
+    else                                                                                                          \
+        nc_x_kernel<N, false, TT><<<grid, 256, 0, s>>>(trains, theta, v, mask, coil, X, d.nx, d.ny, d.nv, d.T,    \
+                                                       n_first, n_count, n_coils, per)
     switch (mode_y) {
     case 0: NC_X(1); break;
     case 1: NC_X(4); break;
