@@ -27,6 +27,14 @@
 namespace mrstat {
 namespace {
 
+// sin and cos of x: reduced to half turns in FP64 (full rate here, and far
+// fewer temporaries than the general FP32 reduction, which would spill states).
+__device__ __forceinline__ void sin_cos(float x, float& sn, float& cs)
+{
+    const double t = (double)x * 0.31830988618379067154;   // 1 / pi
+    sincospif((float)(t - 2.0 * rint(0.5 * t)), &sn, &cs);
+}
+
 // Spoiler shift of one state vector: order k of F+ takes order k-1, order k
 // of F- takes order k+1, F-_{K-1} = 0, and the new F+_0 = conj(F-_0), which
 // is -g_0 in the real form. Orders are spread over the L lanes of a group.
@@ -58,8 +66,31 @@ __device__ __forceinline__ void clear_above(float (&f)[S], int base, int K)
 // outputs are left untouched); whole blocks past the list exit at once.
 // TT: element type of the stored trains (float, or _Float16 rounded to
 // nearest from the FP32 recursion).
+//
+// Bound by the vector units: an order's update is 34 operations (value 7,
+// ln T1 8, ln T2 9, B1 10): with w = f - g and p = E2 (s^2 w + sg sin(a) z) the
+// rotation is f' = E2 f - p, g' = E2 g + p, and the B1 tangent takes the
+// rotation's generator, alpha sg (-z, z, w/2), before it is rotated itself.
+// The lane moves stay shuffles through LDS, a unit that is idle here: as DPP
+// moves they take vector slots and waits (3 tangents 2.03 ms instead of 1.78).
+// 224^2 voxels, 32 orders, 1120 TRs, 2 lanes: 1.78 ms with 3 tangents and
+// 0.45 ms for values (coefficients c^2, s^2 and their derivatives for every
+// row, sines per lane, one TR per turn: 2.13 and 0.52); 128^2 with 2 tangents, at
+// the lanes chosen below, 0.45 and 0.22 ms (1.24 and 0.52 with 2 lanes).
+//
+// FP16 trains keep the row products with c^2 and s^2 (PLAIN): their values and
+// gradients carry the rounding of the trains, to which a changed FP32 recursion
+// adds its own (a gradient's norm moved by up to 2e-6); 2.40 and 0.56 ms.
+// Waves per SIMD that the states (3 S (1 + NTAN) registers) leave room for:
+constexpr int epg_waves(int s, int ntan) { return 3 * s * (1 + ntan) > 130 ? 2 : 3 * s * (1 + ntan) > 84 ? 3 : 4; }
+
+// TRs per turn of the loop, whose shifts then need no register moves; the
+// largest states leave no room for a second copy.
+constexpr int epg_unroll(int s, int l, int ntan) { return 3 * s * (1 + ntan) > 150 ? 1 : l >= 4 && 3 * s * (1 + ntan) <= 50 ? 4 : 2; }
+
+
 template <int S, int L, int NTAN, bool MASKED, bool LIST, typename TT>
-__global__ __launch_bounds__(256) void epg_kernel(const float* __restrict__ theta,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(epg_waves(S, NTAN)))) void epg_kernel(const float* __restrict__ theta,
                                                   const float2* __restrict__ seq,
                                                   TT* __restrict__ out, int nv, int T,
                                                   int K, SeqTimes st,
@@ -78,7 +109,7 @@ __global__ __launch_bounds__(256) void epg_kernel(const float* __restrict__ thet
         j = idx[valid ? vox : cnt - 1];
     } else {
         valid = vox < nv;
-        j = valid ? vox : nv - 1;   // keep every lane active for the shuffles
+        j = valid ? vox : nv - 1;   // keep every lane active for the lane moves
     }
     const bool lead = (l == 0), last = (l == L - 1);
     const bool store = valid && lead;
@@ -87,14 +118,20 @@ __global__ __launch_bounds__(256) void epg_kernel(const float* __restrict__ thet
     const float lnT1 = theta[j], lnT2 = theta[nv + j], B1 = theta[2 * nv + j];
     const float rT1 = expf(-lnT1), rT2 = expf(-lnT2);   // 1/T1, 1/T2
     const float tau1 = st.tr * rT1, tau2 = st.tr * rT2, tau2e = st.te * rT2;
-    const float E1 = expf(-tau1), E2 = expf(-tau2);
-    const float R1 = lead ? -expm1f(-tau1) : 0.f;       // regrowth of Z_0 only
+    const float E1 = expf(-tau1), E1m = expm1f(-tau1), E2 = expf(-tau2);
+    const float R1 = lead ? -E1m : 0.f;                 // regrowth of Z_0 only
     const float dR1 = lead ? tau1 * E1 : 0.f;           // -d(1-E1)/dlnT1
     const float E2e = expf(-tau2e);
     const float taui = st.tinv * rT1;
     const float E1i = expf(-taui), R1i = -expm1f(-taui);
 
     constexpr bool TANG = NTAN > 0, TB1 = NTAN == 3;
+    // z + (E1 cos(a) - 1) z instead of E1 cos(a) z halves the trains' error at
+    // 128 TRs (1.2e-6 to 0.66e-6; at 1120 TRs 1.5e-6 to 1.25e-6) for nothing up
+    // to 8 orders per lane; with 16 it costs 6 to 11% (an FMA that reads three
+    // registers takes 3 cycles, a product 2), and the product stays.
+    constexpr bool FINE = S <= 8;
+    constexpr bool PLAIN = sizeof(TT) == 2;
     float f[S], g[S], z[S];
     float f1[S], g1[S], z1[S];   // d/d ln T1
     float f2[S], g2[S], z2[S];   // d/d ln T2
@@ -116,92 +153,115 @@ __global__ __launch_bounds__(256) void epg_kernel(const float* __restrict__ thet
 
     const size_t plane = (size_t)T * nv;
     TT* o0 = out + j;
-    for (int n = 0; n < T; ++n) {
-        const float2 sq = seq[n];
-        const float alpha = sq.x, sg = sq.y;
-        float sh, ch;
-        sincosf(0.5f * (B1 * alpha), &sh, &ch);
-        const float c2 = ch * ch, s2 = sh * sh;
-        const float sa = 2.f * sh * ch, ca = (ch - sh) * (ch + sh);
+    auto put = [&](int q, int n, float x) {
+        if (store) o0[q * plane + (size_t)n * nv] = (TT)x;
+    };
+    // One TR: sh, ch are sin and cos of half its flip angle B1 alpha.
+    auto tr = [&](int n, float alpha, float sg, float sh, float ch) {
+        const float s2 = sh * sh, sa = 2.f * sh * ch;
         const float sgsa = sg * sa;
+        const float ke = sg * E2e;
         // Coefficients with the TR relaxation folded in.
-        const float A = E2 * c2, B = E2 * s2, Cc = E2 * sgsa;
-        const float D = 0.5f * E1 * sgsa, G = E1 * ca;
-
-        // Readout at TE from the unrelaxed RF output of order 0.
-        {
+        const float B = E2 * s2, Cc = E2 * sgsa, D = 0.5f * E1 * sgsa;
+        if constexpr (PLAIN) {
+            const float c2 = ch * ch, ca = (ch - sh) * (ch + sh);
+            const float A = E2 * c2, G = E1 * ca;
+            // B1 derivatives of the coefficients (d a / d B1 = alpha): dA = -dB.
+            const float dA = -0.5f * E2 * alpha * sa, dC = E2 * alpha * sg * ca;
+            const float dD = 0.5f * E1 * alpha * sg * ca, dG = -E1 * alpha * sa;
             const float rp = fmaf(c2, f[0], fmaf(s2, g[0], -sgsa * z[0]));
-            const float ke = sg * E2e;
-            if (store) o0[(size_t)n * nv] = (TT)(ke * rp);
+            put(0, n, ke * rp);
             if constexpr (TANG) {
-                const float rp1 = fmaf(c2, f1[0], fmaf(s2, g1[0], -sgsa * z1[0]));
-                const float rp2 = fmaf(c2, f2[0], fmaf(s2, g2[0], -sgsa * z2[0]));
-                if (store) {
-                    o0[plane + (size_t)n * nv] = (TT)(ke * rp1);
-                    o0[2 * plane + (size_t)n * nv] = (TT)(ke * fmaf(tau2e, rp, rp2));
-                }
+                put(1, n, ke * fmaf(c2, f1[0], fmaf(s2, g1[0], -sgsa * z1[0])));
+                put(2, n, ke * fmaf(tau2e, rp, fmaf(c2, f2[0], fmaf(s2, g2[0], -sgsa * z2[0]))));
             }
             if constexpr (TB1) {
                 const float drp = fmaf(-0.5f * sa, f[0] - g[0], -sg * ca * z[0]);
-                const float rp3 = fmaf(c2, f3[0], fmaf(s2, g3[0], fmaf(alpha, drp, -sgsa * z3[0])));
-                if (store) o0[3 * plane + (size_t)n * nv] = (TT)(ke * rp3);
+                put(3, n, ke * fmaf(c2, f3[0], fmaf(s2, g3[0], fmaf(alpha, drp, -sgsa * z3[0]))));
             }
-        }
-
-        if constexpr (TANG) {
-            // B1 derivatives of the folded coefficients (d a / d B1 = alpha).
-            const float dA = -0.5f * E2 * alpha * sa;      // dA/dB1 = -dB/dB1
-            const float dC = E2 * alpha * sg * ca;
-            const float dD = 0.5f * E1 * alpha * sg * ca;
-            const float dG = -E1 * alpha * sa;
 #pragma unroll
             for (int i = 0; i < S; ++i) {
-                const float w = f[i] - g[i];
-                const float Cz = Cc * z[i];
+                const float w = f[i] - g[i], Cz = Cc * z[i];
                 const float nf = fmaf(A, f[i], fmaf(B, g[i], -Cz));
                 const float ng = fmaf(B, f[i], fmaf(A, g[i], Cz));
                 const float nz = fmaf(D, w, G * z[i]);
-                {   // ln T1: only E1 (Z rows) depends on T1
-                    const float w1 = f1[i] - g1[i];
-                    const float Cz1 = Cc * z1[i];
-                    const float a = fmaf(A, f1[i], fmaf(B, g1[i], -Cz1));
-                    const float b = fmaf(B, f1[i], fmaf(A, g1[i], Cz1));
-                    const float c = fmaf(D, w1, fmaf(G, z1[i], tau1 * nz));
-                    f1[i] = a; g1[i] = b; z1[i] = c;
+                if constexpr (TANG) {
+                    {
+                        const float w1 = f1[i] - g1[i], Cz1 = Cc * z1[i];
+                        const float a = fmaf(A, f1[i], fmaf(B, g1[i], -Cz1));
+                        g1[i] = fmaf(B, f1[i], fmaf(A, g1[i], Cz1));
+                        f1[i] = a;
+                        z1[i] = fmaf(D, w1, fmaf(G, z1[i], tau1 * nz));
+                    }
+                    {
+                        const float w2 = f2[i] - g2[i], Cz2 = Cc * z2[i];
+                        const float a = fmaf(A, f2[i], fmaf(B, g2[i], fmaf(tau2, nf, -Cz2)));
+                        g2[i] = fmaf(B, f2[i], fmaf(A, g2[i], fmaf(tau2, ng, Cz2)));
+                        f2[i] = a;
+                        z2[i] = fmaf(D, w2, G * z2[i]);
+                    }
                 }
-                {   // ln T2: only E2 (F rows) depends on T2
-                    const float w2 = f2[i] - g2[i];
-                    const float Cz2 = Cc * z2[i];
-                    const float a = fmaf(A, f2[i], fmaf(B, g2[i], fmaf(tau2, nf, -Cz2)));
-                    const float b = fmaf(B, f2[i], fmaf(A, g2[i], fmaf(tau2, ng, Cz2)));
-                    const float c = fmaf(D, w2, G * z2[i]);
-                    f2[i] = a; g2[i] = b; z2[i] = c;
-                }
-                if constexpr (TB1) {   // B1: the RF coefficients depend on a = B1 alpha
-                    const float w3 = f3[i] - g3[i];
+                if constexpr (TB1) {
+                    const float w3 = f3[i] - g3[i], Cz3 = Cc * z3[i];
                     const float t3 = fmaf(dA, w, -dC * z[i]);
-                    const float Cz3 = Cc * z3[i];
                     const float a = fmaf(A, f3[i], fmaf(B, g3[i], t3 - Cz3));
-                    const float b = fmaf(B, f3[i], fmaf(A, g3[i], Cz3 - t3));
-                    const float c = fmaf(D, w3, fmaf(G, z3[i], fmaf(dD, w, dG * z[i])));
-                    f3[i] = a; g3[i] = b; z3[i] = c;
+                    g3[i] = fmaf(B, f3[i], fmaf(A, g3[i], Cz3 - t3));
+                    f3[i] = a;
+                    z3[i] = fmaf(D, w3, fmaf(G, z3[i], fmaf(dD, w, dG * z[i])));
                 }
-                f[i] = nf; g[i] = ng; z[i] = nz;
+                f[i] = nf, g[i] = ng, z[i] = nz;
             }
-            z[0] += R1;
-            z1[0] -= dR1;
         } else {
+            const float Gm = fmaf(-2.f * E1, s2, E1m);   // E1 cos(a) - 1
+            const float G = FINE ? 1.f + Gm : E1 * ((ch - sh) * (ch + sh));
+            // Readout at TE from the unrelaxed RF output of order 0.
+            const float rp = f[0] - fmaf(s2, f[0] - g[0], sgsa * z[0]);
+            put(0, n, ke * rp);
+            if constexpr (TANG) {
+                const float rp1 = f1[0] - fmaf(s2, f1[0] - g1[0], sgsa * z1[0]);
+                const float rp2 = f2[0] - fmaf(s2, f2[0] - g2[0], sgsa * z2[0]);
+                put(1, n, ke * rp1);
+                put(2, n, ke * fmaf(tau2e, rp, rp2));
+            }
+            const float as = alpha * sg, hs = 0.5f * as;
 #pragma unroll
             for (int i = 0; i < S; ++i) {
                 const float w = f[i] - g[i];
-                const float Cz = Cc * z[i];
-                const float nf = fmaf(A, f[i], fmaf(B, g[i], -Cz));
-                const float ng = fmaf(B, f[i], fmaf(A, g[i], Cz));
-                z[i] = fmaf(D, w, G * z[i]);
-                f[i] = nf; g[i] = ng;
+                if constexpr (TB1) {   // the generator of the rotation, then the rotation itself
+                    f3[i] = fmaf(-as, z[i], f3[i]);
+                    g3[i] = fmaf(as, z[i], g3[i]);
+                    z3[i] = fmaf(hs, w, z3[i]);
+                    const float w3 = f3[i] - g3[i];
+                    if (i == 0) put(3, n, ke * (f3[0] - fmaf(s2, w3, sgsa * z3[0])));
+                    const float p3 = fmaf(B, w3, Cc * z3[i]);
+                    f3[i] = fmaf(E2, f3[i], -p3);
+                    g3[i] = fmaf(E2, g3[i], p3);
+                    z3[i] = fmaf(D, w3, G * z3[i]);
+                }
+                const float p = fmaf(B, w, Cc * z[i]);
+                f[i] = fmaf(E2, f[i], -p);
+                g[i] = fmaf(E2, g[i], p);
+                z[i] = fmaf(D, w, FINE ? fmaf(Gm, z[i], z[i]) : G * z[i]);
+                if constexpr (TANG) {
+                    {   // ln T1: only E1 (Z rows) depends on T1
+                        const float w1 = f1[i] - g1[i];
+                        const float p1 = fmaf(B, w1, Cc * z1[i]);
+                        f1[i] = fmaf(E2, f1[i], -p1);
+                        g1[i] = fmaf(E2, g1[i], p1);
+                        z1[i] = fmaf(D, w1, fmaf(G, z1[i], tau1 * z[i]));
+                    }
+                    {   // ln T2: only E2 (F rows) depends on T2
+                        const float w2 = f2[i] - g2[i];
+                        const float p2 = fmaf(B, w2, Cc * z2[i]);
+                        f2[i] = fmaf(E2, f2[i], fmaf(tau2, f[i], -p2));
+                        g2[i] = fmaf(E2, g2[i], fmaf(tau2, g[i], p2));
+                        z2[i] = fmaf(D, w2, G * z2[i]);
+                    }
+                }
             }
-            z[0] += R1;
         }
+        z[0] += R1;
+        if constexpr (TANG) z1[0] -= dR1;
 
         shift_orders<S, L>(f, g, lead, last);
         if constexpr (MASKED) clear_above<S>(f, base, K);
@@ -217,6 +277,70 @@ __global__ __launch_bounds__(256) void epg_kernel(const float* __restrict__ thet
             shift_orders<S, L>(f3, g3, lead, last);
             if constexpr (MASKED) clear_above<S>(f3, base, K);
         }
+    };
+    if constexpr (PLAIN) {
+        for (int n = 0; n < T; ++n) {
+            const float2 q = seq[n];
+            float sh, ch;
+            sincosf(0.5f * (B1 * q.x), &sh, &ch);
+            tr(n, q.x, q.y, sh, ch);
+        }
+        return;
+    }
+    // U TRs at a time. Lane l of the group makes the sines of TR l mod U (one
+    // lane: of all U), for the next U TRs while these ones run.
+    constexpr int U = epg_unroll(S, L, NTAN), NS = L == 1 ? U : 1;
+    static_assert(U <= L || L == 1, "one lane for each TR's sines");
+    float s0[NS], c0[NS];
+    float2 q[U];
+    auto load = [&](int n) {
+#pragma unroll
+        for (int k = 0; k < U; ++k) q[k] = seq[min(n + k, T - 1)];
+    };
+    auto sines = [&]() {
+        if constexpr (NS == U) {
+#pragma unroll
+            for (int k = 0; k < U; ++k) sin_cos(0.5f * (B1 * q[k].x), s0[k], c0[k]);
+        } else {
+            float a = l & 1 ? q[1].x : q[0].x;
+            if constexpr (U == 4) a = l & 2 ? (l & 1 ? q[3].x : q[2].x) : a;
+            sin_cos(0.5f * (B1 * a), s0[0], c0[0]);
+        }
+    };
+    float sh[U], ch[U], al[U], sg[U];
+    auto take = [&]() {   // the next U TRs become the present ones
+#pragma unroll
+        for (int k = 0; k < U; ++k) al[k] = q[k].x, sg[k] = q[k].y;
+        if constexpr (NS == U) {
+#pragma unroll
+            for (int k = 0; k < U; ++k) sh[k] = s0[k], ch[k] = c0[k];
+        } else {
+            sh[0] = __shfl(s0[0], 0, L), sh[1] = __shfl(s0[0], 1, L);
+            ch[0] = __shfl(c0[0], 0, L), ch[1] = __shfl(c0[0], 1, L);
+            if constexpr (U == 4) {
+                sh[2] = __shfl(s0[0], 2, L), sh[3] = __shfl(s0[0], 3, L);
+                ch[2] = __shfl(c0[0], 2, L), ch[3] = __shfl(c0[0], 3, L);
+            }
+        }
+    };
+    load(0);
+    if constexpr (U > 1) sines();
+    int n = 0;
+    for (; n + U <= T; n += U) {
+        if constexpr (U == 1) sines();   // no registers to make the next ones early
+        take();
+        load(n + U);
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            if (U > 1 && k == U / 2) sines();
+            tr(n + k, al[k], sg[k], sh[k], ch[k]);
+        }
+    }
+    if constexpr (U > 1) {
+        take();
+#pragma unroll
+        for (int k = 0; k < U - 1; ++k)
+            if (n + k < T) tr(n + k, al[k], sg[k], sh[k], ch[k]);
     }
 }
 
@@ -236,19 +360,46 @@ hipError_t launch_sl(const Dims& d, SeqTimes st, const float* theta, const float
     return hipGetLastError();
 }
 
+// Lanes per voxel where the caller left them open. A wave alone on its SIMD
+// issues a vector operation in 4 cycles, two together one in 2 (measured 1.67
+// and 0.87 ns per FMA), and a wave's time falls with its orders S: more lanes
+// while the chip is short of waves, fewer, with less work repeated per lane,
+// once it is full. w(l) = waves per SIMD at l lanes (256 CUs x 4). Measured in
+// us over 1120 TRs (512 for K <= 16), 3 tangents / values only:
+//   K 32: 128^2 (w(8) = 2) 2 lanes 1545 / 442, 4 lanes 888 / 273, 8 lanes 621 / 223;
+//         160^2 (3.1) 2 lanes 1557 / 443, 4 lanes 983 / 277, 8 lanes 1099 / 349;
+//         224^2 (w(2) = 1.5) 2 lanes 1776 / 453, 4 lanes 1923 / 481;
+//         320^2 (3.1) 2 lanes 3723 / 883, 4 lanes 3332 / 843.
+//   K 16: 128^2 (w(8) = 2) 4 lanes 263 / 104, 8 lanes 225 / 94;
+//         181^2 (w(4) = 2) 2 lanes 426 / 162, 4 lanes 296 / 107; 224^2 465 / 162 and 510 / 166.
+//   K 8:  181^2 (w(4) = 2) 2 lanes 293 / 134, 4 lanes 233 / 98; 224^2 314 / 134 and 365 / 139.
+//   K 64: 128^2 (w(8) = 2) 4 lanes 721 / 179, 8 lanes 476 / 134; 181^2 (w(4) = 2)
+//         819 / 183 and 880 / 227; 224^2 1585 / 344 and 1429 / 367.
+int auto_lanes(const Dims& d, int ntan)
+{
+    auto full = [&](int l, int w) { return (long)d.nv * l > 65536L * w; };   // w(l) > w
+    if (d.K <= 8) return full(4, 2) ? 2 : 4;
+    if (d.K <= 16) return !full(8, 2) ? 8 : full(4, 2) ? 2 : 4;
+    if (d.K <= 32) return !full(8, 2) ? 8 : full(2, 1) && !full(2, 2) ? 2 : 4;
+    return !full(8, 2) || (full(4, 2) && ntan == 3) ? 8 : 4;
+}
+
 template <int NTAN, bool LIST, typename TT>
 hipError_t launch_any(const Dims& d, SeqTimes st, const float* theta, const float2* seq,
                       TT* out, int lanes, const int* idx, const int* count, hipStream_t s)
 {
+    if (lanes == 0) lanes = auto_lanes(d, NTAN);
     const int K = d.K;
 #define SL(S_, L_) launch_sl<S_, L_, NTAN, LIST, TT>(d, st, theta, seq, out, idx, count, s)
     if (K <= 8) {
         if (lanes == 2) return SL(4, 2);
+        if (lanes == 4) return SL(2, 4);
         return SL(8, 1);
     }
     if (K <= 16) {
         if (lanes == 1) return SL(16, 1);
         if (lanes == 4) return SL(4, 4);
+        if (lanes == 8) return SL(2, 8);
         return SL(8, 2);
     }
     if (K <= 32) {
