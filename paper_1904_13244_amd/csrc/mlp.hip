@@ -42,140 +42,264 @@ __device__ __forceinline__ float gelu_grad(float z)
 // ------------------------------------------------------------------------
 // BF16 GEMM C[M][N] = A[M][K] B[K][N] on v_mfma_f32_16x16x32_bf16 with FP32
 // accumulation. A is row-major [M][K] (TA false) or stored [K][M] (TA true);
-// B is row-major [K][N] (TB false) or stored [N][K] (TB true). Tiles of
-// 64 x 64, K in chunks of 32 double-buffered in LDS, where A is kept
-// [m][k] and B [n][k] so each lane's 8-element fragment is one 128-bit read.
+// B is row-major [K][N] (TB false) or stored [N][K] (TB true). Four waves on
+// tiles of BM x BN, K in chunks of 64 double-buffered in LDS as they lie in
+// memory, the next chunk on its way in registers. An operand with K contiguous
+// is read as one 128-bit piece per lane, one with K strided through the
+// transposing LDS read (its pitch puts the four rows of a read on different
+// banks); element by element through a transposed copy in LDS that staging
+// took most of a small tile's time. The products are formed transposed, so
+// a lane holds four neighbouring columns and stores them as one piece.
+//
+// Too few tiles to fill the chip (weight gradients of hidden layers, 16 tiles
+// at width 256; the output layer's input gradient, K = 8 T) are split over K,
+// FP32 partial sums added in the order of the splits by splitk_kernel. Row sums
+// of A (bias gradients, g.rowsum) are one more product against ones.
+//
+// A gradient at batch 4096, 1120 TRs, width 256, against 64 x 64 tiles with K
+// in chunks of 32, no splits and row sums in passes of their own: output
+// layer and loss 84 us (123; it reads and writes 147 MB), its weight gradient
+// 66, its input gradient 61 (about 260), a hidden weight gradient 11 (about 60),
+// row sums 0 (50); the whole call 372 us (820).
 // Requirements (checked on the host): K, M (when TA), N (when !TB) and the
 // leading dimensions are multiples of 8; 16-byte aligned bases.
 // ------------------------------------------------------------------------
-constexpr int TM = 64, TN = 64, TK = 32, KP = 8;
+constexpr int TK = 64;
 
-template <bool TA, bool TB, int EPI>
+typedef short s4v __attribute__((ext_vector_type(4)));
+
+// 8 values of K for row (lane mod 16), K = 8 (lane / 16) + e, of a [k][m] tile of pitch P.
+template <int P> __device__ __forceinline__ bf16x8 frag_tr(const uint16_t* tile, int lane)
+{
+    typedef __attribute__((address_space(3))) s4v* lp;
+    typedef __attribute__((address_space(3))) char* lptr;
+    const int s = lane & 15;
+    const uint16_t* at = tile + (8 * (lane >> 4) + s / 4) * P + 4 * (s % 4);
+    const s4v a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)(lptr)(char*)at);
+    const s4v b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)(lptr)(char*)(at + 4 * P));
+    typedef short s8v __attribute__((ext_vector_type(8)));
+    return __builtin_bit_cast(bf16x8, (s8v)__builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+template <bool TA, bool TB, int EPI, int BM, int BN>
 __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs g)
 {
-    __shared__ __attribute__((aligned(16))) uint16_t As[2][TM][TK + KP];
-    __shared__ __attribute__((aligned(16))) uint16_t Bs[2][TN][TK + KP];
+    constexpr int PA = TA ? BM + 16 : TK + 8, PB = TB ? TK + 8 : BN + 16;   // LDS pitches
+    constexpr int SA = (TA ? TK : BM) * PA, SB = (TB ? BN : TK) * PB;
+    constexpr int MT = BM / 32, NT = BN / 32, NA = BM * TK / 2048, NB = BN * TK / 2048;
+    __shared__ __attribute__((aligned(16))) uint16_t As[2][SA];
+    __shared__ __attribute__((aligned(16))) uint16_t Bs[2][SB];
     __shared__ double rs[4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
-    const int m0 = blockIdx.y * TM, n0 = blockIdx.x * TN;
+    const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
     const int nchunk = (g.K + TK - 1) / TK;
+    const int c_begin = (int)((int64_t)nchunk * blockIdx.z / gridDim.z);
+    const int c_end = (int)((int64_t)nchunk * (blockIdx.z + 1) / gridDim.z);
+    constexpr bool SUMS = EPI == EPI_STORE_F32 && !TA;
+    const bool sums = SUMS && g.rowsum && blockIdx.x == 0 && wn == 0;
 
-    uint4 ra, rb;
+    uint4 ra[NA], rb[NB];
     auto load8 = [&](const uint16_t* base, int64_t idx, bool ok) -> uint4 {
         return ok ? *reinterpret_cast<const uint4*>(base + idx) : make_uint4(0, 0, 0, 0);
     };
+    // Piece e of a chunk: 8 values along the operand's contiguous direction.
     auto gload = [&](int kc) {
         const int k0 = kc * TK;
-        if (!TA) {   // row m = tid/4, k group 8(tid%4)
-            const int r = tid >> 2, kg = (tid & 3) * 8;
-            ra = load8(g.A, (int64_t)(m0 + r) * g.lda + k0 + kg, m0 + r < g.M && k0 + kg < g.K);
-        } else {     // k = tid/8, m group 8(tid%8)
-            const int k = tid >> 3, mg = (tid & 7) * 8;
-            ra = load8(g.A, (int64_t)(k0 + k) * g.lda + m0 + mg, k0 + k < g.K && m0 + mg < g.M);
+#pragma unroll
+        for (int i = 0; i < NA; ++i) {
+            const int e = tid + 256 * i;
+            if constexpr (!TA) {
+                const int m = m0 + e / (TK / 8), k = k0 + 8 * (e % (TK / 8));
+                ra[i] = load8(g.A, (int64_t)m * g.lda + k, m < g.M && k < g.K);
+            } else {
+                const int k = k0 + e / (BM / 8), m = m0 + 8 * (e % (BM / 8));
+                ra[i] = load8(g.A, (int64_t)k * g.lda + m, k < g.K && m < g.M);
+            }
         }
-        if (TB) {    // n = tid/4, k group
-            const int r = tid >> 2, kg = (tid & 3) * 8;
-            rb = load8(g.B, (int64_t)(n0 + r) * g.ldb + k0 + kg, n0 + r < g.N && k0 + kg < g.K);
-        } else {     // k = tid/8, n group
-            const int k = tid >> 3, ng = (tid & 7) * 8;
-            rb = load8(g.B, (int64_t)(k0 + k) * g.ldb + n0 + ng, k0 + k < g.K && n0 + ng < g.N);
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            const int e = tid + 256 * i;
+            if constexpr (TB) {
+                const int n = n0 + e / (TK / 8), k = k0 + 8 * (e % (TK / 8));
+                rb[i] = load8(g.B, (int64_t)n * g.ldb + k, n < g.N && k < g.K);
+            } else {
+                const int k = k0 + e / (BN / 8), n = n0 + 8 * (e % (BN / 8));
+                rb[i] = load8(g.B, (int64_t)k * g.ldb + n, k < g.K && n < g.N);
+            }
         }
     };
     auto sstore = [&](int buf) {
-        if (!TA) {
-            const int r = tid >> 2, kg = (tid & 3) * 8;
-            *reinterpret_cast<uint4*>(&As[buf][r][kg]) = ra;
-        } else {
-            const int k = tid >> 3, mg = (tid & 7) * 8;
-            const uint16_t* v = reinterpret_cast<const uint16_t*>(&ra);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) As[buf][mg + i][k] = v[i];
+        for (int i = 0; i < NA; ++i) {
+            const int e = tid + 256 * i;
+            constexpr int W = TA ? BM / 8 : TK / 8;
+            *reinterpret_cast<uint4*>(&As[buf][(e / W) * PA + 8 * (e % W)]) = ra[i];
         }
-        if (TB) {
-            const int r = tid >> 2, kg = (tid & 3) * 8;
-            *reinterpret_cast<uint4*>(&Bs[buf][r][kg]) = rb;
-        } else {
-            const int k = tid >> 3, ng = (tid & 7) * 8;
-            const uint16_t* v = reinterpret_cast<const uint16_t*>(&rb);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) Bs[buf][ng + i][k] = v[i];
+        for (int i = 0; i < NB; ++i) {
+            const int e = tid + 256 * i;
+            constexpr int W = TB ? TK / 8 : BN / 8;
+            *reinterpret_cast<uint4*>(&Bs[buf][(e / W) * PB + 8 * (e % W)]) = rb[i];
         }
     };
 
-    f4 acc[2][2];
+    f4 acc[MT][NT], ones_acc[MT];
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < MT; ++a) {
+        ones_acc[a] = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int b = 0; b < 2; ++b) acc[a][b] = f4{0.f, 0.f, 0.f, 0.f};
+        for (int b = 0; b < NT; ++b) acc[a][b] = f4{0.f, 0.f, 0.f, 0.f};
+    }
+    const __bf16 one = (__bf16)1.f;
+    const bf16x8 ones = bf16x8{one, one, one, one, one, one, one, one};
 
-    if (nchunk > 0) {
-        gload(0);
+    if (c_begin < c_end) {
+        gload(c_begin);
         sstore(0);
     }
     __syncthreads();
-    const int kq = 8 * (lane >> 4);
-    for (int kc = 0; kc < nchunk; ++kc) {
-        const int buf = kc & 1;
-        const bool more = kc + 1 < nchunk;
+    for (int kc = c_begin; kc < c_end; ++kc) {
+        const int buf = (kc - c_begin) & 1;
+        const bool more = kc + 1 < c_end;
         if (more) gload(kc + 1);
-        uint4 af[2], bf[2];
 #pragma unroll
-        for (int a = 0; a < 2; ++a)
-            af[a] = *reinterpret_cast<const uint4*>(&As[buf][wm * 32 + a * 16 + (lane & 15)][kq]);
+        for (int ks = 0; ks < TK; ks += 32) {
+            bf16x8 af[MT], bf[NT];
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
-            bf[b] = *reinterpret_cast<const uint4*>(&Bs[buf][wn * 32 + b * 16 + (lane & 15)][kq]);
+            for (int a = 0; a < MT; ++a) {
+                const int m = wm * (BM / 2) + a * 16;
+                if constexpr (TA) af[a] = frag_tr<PA>(&As[buf][ks * PA + m], lane);
+                else af[a] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(
+                                                            &As[buf][(m + (lane & 15)) * PA + ks + 8 * (lane >> 4)]));
+            }
 #pragma unroll
-        for (int a = 0; a < 2; ++a)
+            for (int b = 0; b < NT; ++b) {
+                const int n = wn * (BN / 2) + b * 16;
+                if constexpr (!TB) bf[b] = frag_tr<PB>(&Bs[buf][ks * PB + n], lane);
+                else bf[b] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(
+                                                            &Bs[buf][(n + (lane & 15)) * PB + ks + 8 * (lane >> 4)]));
+            }
 #pragma unroll
-            for (int b = 0; b < 2; ++b)
-                acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                    __builtin_bit_cast(bf16x8, af[a]), __builtin_bit_cast(bf16x8, bf[b]), acc[a][b],
-                    0, 0, 0);
+            for (int a = 0; a < MT; ++a)
+#pragma unroll
+                for (int b = 0; b < NT; ++b)
+                    acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[b], af[a], acc[a][b], 0, 0, 0);
+            if constexpr (SUMS)
+                if (sums)
+#pragma unroll
+                    for (int a = 0; a < MT; ++a)
+                        ones_acc[a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, af[a], ones_acc[a], 0, 0, 0);
+        }
         if (more) sstore(buf ^ 1);
         __syncthreads();
     }
 
+    // D: lane holds row m = lane mod 16 and columns n = 4 (lane / 16) + i.
+    const int64_t part = gridDim.z > 1 ? (int64_t)blockIdx.z * ((int64_t)g.M * g.N + (g.rowsum ? g.M : 0)) : 0;
+    float* cf = (gridDim.z > 1 ? g.part : g.Cf);
     double lsum = 0.0;
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < MT; ++a) {
+        const int m = m0 + wm * (BM / 2) + a * 16 + (lane & 15);
+        if (m >= g.M) continue;
+        if constexpr (SUMS)
+            if (sums && lane < 16) cf[part + (int64_t)g.M * g.N + m] = ones_acc[a][0];
+        float bias = 0.f, hs = 1.f;
+        const float* trow = nullptr;
+        float* orow = nullptr;
+        if constexpr (EPI == EPI_BIAS_GELU || EPI == EPI_OUT_LOSS || EPI == EPI_INFER) bias = g.bias[m];
+        if constexpr (EPI == EPI_OUT_LOSS) {
+            const int c = m / (4 * g.T), p = (m % (4 * g.T)) / g.T, nt = m % g.T;
+            hs = g.head_scale[p];
+            if (c) trow = g.target + ((int64_t)p * g.T + nt) * g.ld_t;
+        }
+        if constexpr (EPI == EPI_INFER) {   // rows are the imaginary outputs of trains p = m / T
+            const int p = m / g.T, nt = m % g.T;
+            hs = g.head_scale[p];
+            orow = g.Cf + (int64_t)p * g.plane + (int64_t)nt * g.ldo;
+        }
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int m = m0 + wm * 32 + a * 16 + 4 * (lane >> 4) + i;
-                const int n = n0 + wn * 32 + b * 16 + (lane & 15);
-                if (m >= g.M || n >= g.N) continue;
-                const float v = acc[a][b][i];
-                const int64_t o = (int64_t)m * g.ldo + n;
-                if constexpr (EPI == EPI_STORE_F32) {
-                    g.Cf[o] = v;
-                } else if constexpr (EPI == EPI_BIAS_GELU) {
-                    const float z = v + g.bias[m];
-                    if (g.Zb) g.Zb[o] = to_bf16(z);
-                    g.Hb[o] = to_bf16(gelu(z));
-                } else if constexpr (EPI == EPI_OUT_LOSS) {
-                    const float y = v + g.bias[m];
-                    const int T = g.T, c = m / (4 * T), p = (m % (4 * T)) / T, nt = m % T;
-                    const float t = c ? g.target[((int64_t)p * T + nt) * g.ld_t + n] / g.head_scale[p] : 0.f;
-                    const float d = y - t;
-                    g.Hb[o] = to_bf16(g.grad_scale * d);
-                    lsum += (double)d * (double)d;
-                } else if constexpr (EPI == EPI_GELU_BWD) {
-                    g.Hb[o] = to_bf16(v * gelu_grad(from_bf16(g.Zin[o])));
-                } else {   // EPI_INFER: rows are the imaginary outputs of trains p = m / T
-                    const float y = v + g.bias[m];
-                    const int p = m / g.T, nt = m % g.T;
-                    g.Cf[(int64_t)p * g.plane + (int64_t)nt * g.ldo + n] = y * g.head_scale[p];
+        for (int b = 0; b < NT; ++b) {
+            const int n = n0 + wn * (BN / 2) + b * 16 + 4 * (lane >> 4);
+            const int nn = min(4, g.N - n);
+            if (nn <= 0) continue;
+            const int64_t o = (int64_t)m * g.ldo + n;
+            const f4 v = acc[a][b];
+            uint16_t h[4], zb[4];
+            if constexpr (EPI == EPI_STORE_F32) {
+                if (gridDim.z > 1) *reinterpret_cast<f4*>(cf + part + (int64_t)m * g.N + n) = v;
+                else *reinterpret_cast<f4*>(cf + o) = v;
+                continue;
+            } else if constexpr (EPI == EPI_GELU_BWD) {
+                if (gridDim.z > 1) {
+                    *reinterpret_cast<f4*>(cf + part + (int64_t)m * g.N + n) = v;
+                    continue;
                 }
+                const uint2 zi = *reinterpret_cast<const uint2*>(g.Zin + o);
+                const uint32_t zw[2] = {zi.x, zi.y};
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    h[i] = to_bf16(v[i] * gelu_grad(from_bf16((uint16_t)(zw[i / 2] >> (16 * (i % 2))))));
+            } else if constexpr (EPI == EPI_BIAS_GELU) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float z = v[i] + bias;
+                    zb[i] = to_bf16(z);
+                    h[i] = to_bf16(gelu(z));
+                }
+                if (g.Zb) {
+                    if (nn == 4) *reinterpret_cast<uint2*>(g.Zb + o) = make_uint2(zb[0] | zb[1] << 16, zb[2] | zb[3] << 16);
+                    else for (int i = 0; i < nn; ++i) g.Zb[o + i] = zb[i];
+                }
+            } else if constexpr (EPI == EPI_OUT_LOSS) {
+                f4 t = f4{0.f, 0.f, 0.f, 0.f};
+                if (trow) {
+                    if (g.vec && nn == 4) t = *reinterpret_cast<const f4*>(trow + n);
+                    else for (int i = 0; i < nn; ++i) t[i] = trow[n + i];
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float d = i < nn ? (v[i] + bias) - t[i] / hs : 0.f;
+                    h[i] = to_bf16(g.grad_scale * d);
+                    lsum += (double)d * (double)d;
+                }
+            } else {
+                for (int i = 0; i < nn; ++i) orow[n + i] = (v[i] + bias) * hs;
+                continue;
             }
+            if (nn == 4) *reinterpret_cast<uint2*>(g.Hb + o) = make_uint2(h[0] | h[1] << 16, h[2] | h[3] << 16);
+            else for (int i = 0; i < nn; ++i) g.Hb[o + i] = h[i];
+        }
+    }
     if constexpr (EPI == EPI_OUT_LOSS) {
         for (int off = 32; off > 0; off >>= 1) lsum += __shfl_xor(lsum, off);
         if (lane == 0) rs[wave] = lsum;
         __syncthreads();
         if (tid == 0) g.loss_part[blockIdx.y * gridDim.x + blockIdx.x] = (rs[0] + rs[1]) + (rs[2] + rs[3]);
     }
+}
+
+// Sums of n_split partials of n floats each (a multiple of 4), in split order:
+// to out (weight gradients), or times GELU' as BF16 (Hb with Zin).
+__global__ __launch_bounds__(256) void splitk_kernel(const float* __restrict__ part, int n_split, int64_t n,
+                                                     float* __restrict__ out, const uint16_t* __restrict__ Zin,
+                                                     uint16_t* __restrict__ Hb)
+{
+    const int64_t i = 4 * ((int64_t)blockIdx.x * blockDim.x + threadIdx.x);
+    if (i >= n) return;
+    f4 v = *reinterpret_cast<const f4*>(part + i);
+    for (int z = 1; z < n_split; ++z) v += *reinterpret_cast<const f4*>(part + z * n + i);
+    if (!Hb) {
+        *reinterpret_cast<f4*>(out + i) = v;
+        return;
+    }
+    const uint2 zi = *reinterpret_cast<const uint2*>(Zin + i);
+    uint16_t h[4];
+    const uint32_t zw[2] = {zi.x, zi.y};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) h[q] = to_bf16(v[q] * gelu_grad(from_bf16((uint16_t)(zw[q / 2] >> (16 * (q % 2))))));
+    *reinterpret_cast<uint2*>(Hb + i) = make_uint2(h[0] | h[1] << 16, h[2] | h[3] << 16);
 }
 
 // First layer (3 inputs): x normalised onto [-1, 1] over the box, z = W1 x + b1.
@@ -205,49 +329,40 @@ __global__ void layer1_fwd_kernel(const float* __restrict__ x_in, int64_t ldx, i
     }
 }
 
-// Row sums of a bf16 [rows][n] matrix (bias gradients), one block per row,
-// fixed-order reduction.
-__global__ __launch_bounds__(256) void rowsum_kernel(const uint16_t* __restrict__ X, int64_t ld, int n,
-                                                     float* __restrict__ out)
-{
-    __shared__ float sh[256];
-    const int r = blockIdx.x;
-    float s = 0.f;
-    for (int i = threadIdx.x; i < n; i += 256) s += from_bf16(X[(int64_t)r * ld + i]);
-    sh[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) out[r] = sh[0];
-}
-
-// dW1[o][i] = sum_s dZ1[o][s] x[i][s]: one block per output row.
+// dW1[o][i] = sum_s dZ1[o][s] x[i][s] and db1[o] = sum_s dZ1[o][s]: one block
+// per output row, fixed-order reduction.
 __global__ __launch_bounds__(256) void layer1_wgrad_kernel(const uint16_t* __restrict__ dZ,
                                                            const float* __restrict__ xs, int64_t ld,
-                                                           int n, float* __restrict__ dW1)
+                                                           int n, float* __restrict__ dW1, float* __restrict__ db1)
 {
-    __shared__ float sh[3][256];
+    __shared__ float sh[4][256];
     const int o = blockIdx.x;
-    float a0 = 0.f, a1 = 0.f, a2 = 0.f;
-    for (int s = threadIdx.x; s < n; s += 256) {
-        const float d = from_bf16(dZ[(int64_t)o * ld + s]);
-        a0 = fmaf(d, xs[s], a0);
-        a1 = fmaf(d, xs[ld + s], a1);
-        a2 = fmaf(d, xs[2 * ld + s], a2);
+    float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
+    for (int s = 2 * threadIdx.x; s < n; s += 512) {   // n a multiple of 64
+        const uint32_t dd = *reinterpret_cast<const uint32_t*>(dZ + (int64_t)o * ld + s);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const float d = from_bf16((uint16_t)(dd >> (16 * q)));
+            a0 = fmaf(d, xs[s + q], a0);
+            a1 = fmaf(d, xs[ld + s + q], a1);
+            a2 = fmaf(d, xs[2 * ld + s + q], a2);
+            a3 += d;
+        }
     }
     sh[0][threadIdx.x] = a0;
     sh[1][threadIdx.x] = a1;
     sh[2][threadIdx.x] = a2;
+    sh[3][threadIdx.x] = a3;
     __syncthreads();
     for (int w = 128; w > 0; w >>= 1) {
         if (threadIdx.x < w)
-            for (int q = 0; q < 3; ++q) sh[q][threadIdx.x] += sh[q][threadIdx.x + w];
+            for (int q = 0; q < 4; ++q) sh[q][threadIdx.x] += sh[q][threadIdx.x + w];
         __syncthreads();
     }
-    if (threadIdx.x == 0)
+    if (threadIdx.x == 0) {
         for (int q = 0; q < 3; ++q) dW1[3 * o + q] = sh[q][0];
+        db1[o] = sh[3][0];
+    }
 }
 
 // Adam on FP32 master weights; refreshes the BF16 copy.
@@ -723,14 +838,34 @@ void mlp_out_kernel(InferArgs a, const uint16_t* __restrict__ H)
     }
 }
 
+// Tiles of 128 x 128 in the output layer's product where they fill the chip twice.
+bool loss_wide(int M, int N) { return (int64_t)ceil_div(N, 128) * ceil_div(M, 128) >= 512; }
+
 }  // namespace
+
+int gemm_tiles(int M, int N) { return ceil_div(N, 64) * ceil_div(M, 64); }
+int loss_tiles(int M, int N) { return loss_wide(M, N) ? ceil_div(N, 128) * ceil_div(M, 128) : gemm_tiles(M, N); }
 
 hipError_t launch_gemm_bf16(bool ta, bool tb, int epi, const GemmArgs& g, hipStream_t s)
 {
-    dim3 grid(ceil_div(g.N, TN), ceil_div(g.M, TM));
+    // Splits over K: two workgroups per CU, 256 of K each at least, as many as g.part holds.
+    int nz = 1;
+    const int64_t out = (int64_t)g.M * g.N + (g.rowsum ? g.M : 0);
+    if (g.part && out % 4 == 0 && (epi == EPI_STORE_F32 || epi == EPI_GELU_BWD))
+        nz = (int)std::max<int64_t>(1, std::min<int64_t>({(int64_t)ceil_div(512, gemm_tiles(g.M, g.N)),
+                                                          (int64_t)g.K / 256, g.part_floats / out}));
+    if (epi == EPI_OUT_LOSS && loss_wide(g.M, g.N)) {
+        gemm_bf16_kernel<false, false, EPI_OUT_LOSS, 128, 128>
+            <<<dim3(ceil_div(g.N, 128), ceil_div(g.M, 128)), 256, 0, s>>>(g);
+        return hipGetLastError();
+    }
+    dim3 grid(ceil_div(g.N, 64), ceil_div(g.M, 64), nz);
 #define GEMM_CASE(TA_, TB_, E_)                                                  \
     if (ta == TA_ && tb == TB_ && epi == E_) {                                   \
-        gemm_bf16_kernel<TA_, TB_, E_><<<grid, 256, 0, s>>>(g);                  \
+        gemm_bf16_kernel<TA_, TB_, E_, 64, 64><<<grid, 256, 0, s>>>(g);          \
+        if (nz > 1)                                                              \
+            splitk_kernel<<<(unsigned)((out / 4 + 255) / 256), 256, 0, s>>>(     \
+                g.part, nz, out, g.Cf, g.Zin, epi == EPI_GELU_BWD ? g.Hb : nullptr); \
         return hipGetLastError();                                                \
     }
     GEMM_CASE(false, false, EPI_BIAS_GELU)
@@ -742,8 +877,6 @@ hipError_t launch_gemm_bf16(bool ta, bool tb, int epi, const GemmArgs& g, hipStr
     return hipErrorInvalidValue;
 }
 
-int gemm_tiles(int M, int N) { return ceil_div(N, TN) * ceil_div(M, TM); }
-
 hipError_t launch_layer1_fwd(const float* x_in, int64_t ldx, int n, const float* W1,
                              const float* b1, int width, const float* lo, const float* hi,
                              float* xs, uint16_t* Zb, uint16_t* Hb, int64_t ldo, hipStream_t s)
@@ -753,17 +886,10 @@ hipError_t launch_layer1_fwd(const float* x_in, int64_t ldx, int n, const float*
     return hipGetLastError();
 }
 
-hipError_t launch_rowsum_bf16(const uint16_t* X, int64_t ld, int rows, int n, float* out,
-                              hipStream_t s)
-{
-    rowsum_kernel<<<rows, 256, 0, s>>>(X, ld, n, out);
-    return hipGetLastError();
-}
-
 hipError_t launch_layer1_wgrad(const uint16_t* dZ, const float* xs, int64_t ld, int width, int n,
-                               float* dW1, hipStream_t s)
+                               float* dW1, float* db1, hipStream_t s)
 {
-    layer1_wgrad_kernel<<<width, 256, 0, s>>>(dZ, xs, ld, n, dW1);
+    layer1_wgrad_kernel<<<width, 256, 0, s>>>(dZ, xs, ld, n, dW1, db1);
     return hipGetLastError();
 }
 

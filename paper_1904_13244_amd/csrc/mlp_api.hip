@@ -25,7 +25,7 @@ struct mrstat_mlp_s {
     size_t ws_bytes = 0;
     size_t o_w32, o_wb, o_m, o_v, o_g, o_z, o_h, o_dy, o_dz, o_xs, o_loss, o_scale, total;
     int n_loss = 0;    // doubles in the loss buffer (also the scaling reduction's partials)
-    int n_tiles = 0;   // loss partials written by the output layer (one per tile)
+    int n_tiles = 0;   // loss partials written by the output layer (loss_tiles)
     std::string err;
 
     float* w32() const { return (float*)(ws + o_w32); }
@@ -112,24 +112,11 @@ mrstat_status forward_backward(mrstat_mlp net, const float* theta, int64_t ldth,
         g.head_scale = net->dscale();
         g.grad_scale = (float)(2.0 / ((double)8 * T * B));
         g.loss_part = net->loss();
+        g.vec = ldtr % 4 == 0 && ((uintptr_t)trains & 15) == 0;
         MTRY(launch_gemm_bf16(false, false, EPI_OUT_LOSS, g, s));
     }
-    // dWout = dY H^T (NT), dbout = row sums of dY.
-    {
-        GemmArgs g = gargs();
-        g.A = net->dY();
-        g.lda = B;
-        g.B = net->H(L - 1);
-        g.ldb = B;
-        g.M = 8 * T;
-        g.N = W;
-        g.K = B;
-        g.ldo = W;
-        g.Cf = net->gr() + net->off_wo;
-        MTRY(launch_gemm_bf16(false, true, EPI_STORE_F32, g, s));
-        MTRY(launch_rowsum_bf16(net->dY(), B, 8 * T, B, net->gr() + net->off_bo, s));
-    }
-    // dZ_{L-1} = (Wout^T dY) * gelu'(Z_{L-1}) (TN).
+    // dZ_{L-1} = (Wout^T dY) * gelu'(Z_{L-1}) (TN); its partial sums lie in the
+    // place of dWout, which comes after it.
     int cur = 0;
     {
         GemmArgs g = gargs();
@@ -143,10 +130,28 @@ mrstat_status forward_backward(mrstat_mlp net, const float* theta, int64_t ldth,
         g.ldo = B;
         g.Zin = net->Z(L - 1);
         g.Hb = net->dZ(cur);
+        g.part = net->gr() + net->off_wo;
+        g.part_floats = (int64_t)8 * T * W;
         MTRY(launch_gemm_bf16(true, false, EPI_GELU_BWD, g, s));
     }
+    // dWout = dY H^T (NT), dbout = row sums of dY (bout lies behind Wout).
+    {
+        GemmArgs g = gargs();
+        g.A = net->dY();
+        g.lda = B;
+        g.B = net->H(L - 1);
+        g.ldb = B;
+        g.M = 8 * T;
+        g.N = W;
+        g.K = B;
+        g.ldo = W;
+        g.Cf = net->gr() + net->off_wo;
+        g.rowsum = true;
+        MTRY(launch_gemm_bf16(false, true, EPI_STORE_F32, g, s));
+    }
     for (int l = L - 1; l >= 1; --l) {
-        // dW_l = dZ_l H_{l-1}^T, db_l = row sums; dZ_{l-1} = (W_l^T dZ_l) * gelu'(Z_{l-1}).
+        // dW_l = dZ_l H_{l-1}^T, db_l = row sums (behind dW_l), partial sums in
+        // dY, which nothing reads any more; dZ_{l-1} = (W_l^T dZ_l) * gelu'(Z_{l-1}).
         GemmArgs g = gargs();
         g.A = net->dZ(cur);
         g.lda = B;
@@ -157,8 +162,10 @@ mrstat_status forward_backward(mrstat_mlp net, const float* theta, int64_t ldth,
         g.K = B;
         g.ldo = W;
         g.Cf = net->gr() + net->off_w[l];
+        g.rowsum = true;
+        g.part = reinterpret_cast<float*>(net->dY());
+        g.part_floats = (int64_t)4 * T * B;
         MTRY(launch_gemm_bf16(false, true, EPI_STORE_F32, g, s));
-        MTRY(launch_rowsum_bf16(net->dZ(cur), B, W, B, net->gr() + net->off_b[l], s));
         GemmArgs h = gargs();
         h.A = net->wb() + net->off_w[l];
         h.lda = W;
@@ -173,8 +180,8 @@ mrstat_status forward_backward(mrstat_mlp net, const float* theta, int64_t ldth,
         MTRY(launch_gemm_bf16(true, false, EPI_GELU_BWD, h, s));
         cur ^= 1;
     }
-    MTRY(launch_layer1_wgrad(net->dZ(cur), net->xs(), B, W, B, net->gr() + net->off_w[0], s));
-    MTRY(launch_rowsum_bf16(net->dZ(cur), B, W, B, net->gr() + net->off_b[0], s));
+    MTRY(launch_layer1_wgrad(net->dZ(cur), net->xs(), B, W, B, net->gr() + net->off_w[0],
+                             net->gr() + net->off_b[0], s));
     return MRSTAT_OK;
 }
 
@@ -297,8 +304,8 @@ mrstat_status mrstat_mlp_create(int32_t n_tr, int32_t width, int32_t depth, int3
     net->off_bo = o; o += (size_t)8 * n_tr;
     net->P = o;
     const size_t P = net->P, WB = (size_t)width * batch;
-    net->n_tiles = gemm_tiles(8 * n_tr, batch);
-    net->n_loss = std::max(net->n_tiles, RED_BLOCKS + 8);
+    net->n_tiles = loss_tiles(8 * n_tr, batch);
+    net->n_loss = std::max(gemm_tiles(8 * n_tr, batch), RED_BLOCKS + 8);
     size_t w = 0;
     auto take = [&](size_t b) { size_t at = w; w = a256(w + b); return at; };
     net->o_w32 = take(P * 4);

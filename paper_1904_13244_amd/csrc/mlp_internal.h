@@ -33,8 +33,12 @@ struct GemmArgs {
     int T;
     const float* head_scale; // [4]
     float grad_scale;        // dY = grad_scale (y - t)
-    double* loss_part;       // one double per tile (OUT_LOSS)
+    double* loss_part;       // loss_tiles doubles (OUT_LOSS)
     int64_t plane;           // INFER: floats between trains
+    bool vec;                // OUT_LOSS: target rows are 16-byte aligned
+    bool rowsum;             // STORE: row sums of A at Cf + M N (ldo = N)
+    float* part;             // STORE, GELU_BWD (ldo = N): scratch for splits over K, or null
+    int64_t part_floats;
 };
 
 // Fused inference (one workgroup per 32 or 64 voxels) for widths 64, 128, 256.
@@ -72,14 +76,13 @@ hipError_t launch_mlp_out(const InferArgs& a, const uint16_t* H, hipStream_t s);
 hipError_t launch_mlp_hidden(const InferArgs& a, hipStream_t s);
 
 hipError_t launch_gemm_bf16(bool ta, bool tb, int epi, const GemmArgs& g, hipStream_t s);
-int gemm_tiles(int M, int N);
+int gemm_tiles(int M, int N);    // tiles of 64 x 64
+int loss_tiles(int M, int N);    // loss partials that OUT_LOSS writes (gemm_tiles at most)
 hipError_t launch_layer1_fwd(const float* x_in, int64_t ldx, int n, const float* W1,
                              const float* b1, int width, const float* lo, const float* hi,
                              float* xs, uint16_t* Zb, uint16_t* Hb, int64_t ldo, hipStream_t s);
-hipError_t launch_rowsum_bf16(const uint16_t* X, int64_t ld, int rows, int n, float* out,
-                              hipStream_t s);
 hipError_t launch_layer1_wgrad(const uint16_t* dZ, const float* xs, int64_t ld, int width, int n,
-                               float* dW1, hipStream_t s);
+                               float* dW1, float* db1, hipStream_t s);
 hipError_t launch_adam(float* w, float* m, float* v, const float* g, uint16_t* wb, size_t n,
                        float lr, int step, hipStream_t s);
 hipError_t launch_to_bf16(const float* x, uint16_t* y, size_t n, hipStream_t s);
