@@ -598,8 +598,13 @@ void mlp_infer_kernel(InferArgs a)
 // GELU(sum + bias) back over the activations (BF16, 8-byte stores of 4 units).
 // The first layer runs in FP32 from theta; the last activations go to
 // a.hout as BF16 [voxel][256]. Same roundings as the fused kernel.
+//
+// OUT: the same workgroup goes on to the output layer instead, from the
+// activations in LDS, two 16-row output tiles per wave at a time (the next
+// two tiles' weights on their way): the output weights are read once per 208
+// voxels and no activations go through memory.
 // ------------------------------------------------------------------------
-template <int NV>
+template <int NV, bool OUT>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void mlp_hidden_kernel(InferArgs a)
 {
@@ -666,6 +671,71 @@ void mlp_hidden_kernel(InferArgs a)
                 }
             }
             __syncthreads();
+        }
+        if constexpr (OUT) {
+            const int n_pairs = (a.m_out + 31) / 32;
+            const bool vec_ok = (a.ld_out % 4) == 0 && (reinterpret_cast<uintptr_t>(a.out) & 15) == 0;
+            auto load_w = [&](uint4 (&w)[2][KB], int pair) {
+#pragma unroll
+                for (int m = 0; m < 2; ++m) {
+                    const int o = min(32 * min(pair, n_pairs - 1) + 16 * m + lr, a.m_out - 1);
+#pragma unroll
+                    for (int kb = 0; kb < KB; ++kb)
+                        w[m][kb] = *reinterpret_cast<const uint4*>(a.Wout + (size_t)o * WIDTH + 32 * kb + lk);
+                }
+            };
+            auto pair_out = [&](const uint4 (&w)[2][KB], int pair) {
+                float* dst[2];
+                float bias[2], sc[2];
+                bool ok[2];
+#pragma unroll
+                for (int m = 0; m < 2; ++m) {
+                    const int o = 32 * pair + 16 * m + lr, oc = min(o, a.m_out - 1), p = oc / a.T;
+                    ok[m] = o < a.m_out;
+                    bias[m] = a.bout[oc];
+                    sc[m] = a.head_scale[p];
+                    dst[m] = static_cast<float*>(a.out) + (size_t)p * a.plane + (size_t)(oc - p * a.T) * a.ld_out;
+                }
+#pragma unroll 1
+                for (int vt = 0; vt < VT; ++vt) {
+                    f4 acc[2] = {f4{0.f, 0.f, 0.f, 0.f}, f4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+                    for (int kb = 0; kb < KB; ++kb) {
+                        const uint4 af = Hf[vt][kb][lane];
+#pragma unroll
+                        for (int m = 0; m < 2; ++m)
+                            acc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                __builtin_bit_cast(bf16x8, af), __builtin_bit_cast(bf16x8, w[m][kb]), acc[m], 0, 0, 0);
+                    }
+                    // D: lane holds voxels 4 (lane / 16) + i of the tile, output row lr.
+                    const int jv = j0 + vt * 16 + 4 * (lane >> 4);
+#pragma unroll
+                    for (int m = 0; m < 2; ++m) {
+                        if (!ok[m]) continue;
+                        float y[4];
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) y[i] = (acc[m][i] + bias[m]) * sc[m];
+                        if (vec_ok && jv + 3 < a.n) {
+                            *reinterpret_cast<f4*>(dst[m] + jv) = f4{y[0], y[1], y[2], y[3]};
+                        } else {
+#pragma unroll
+                            for (int i = 0; i < 4; ++i)
+                                if (jv + i < a.n) dst[m][jv + i] = y[i];
+                        }
+                    }
+                }
+            };
+            uint4 w0[2][KB], w1[2][KB];
+            load_w(w0, wave);
+            for (int pair = wave; pair < n_pairs; pair += 16) {
+                load_w(w1, pair + 8);
+                pair_out(w0, pair);
+                if (pair + 8 >= n_pairs) break;
+                load_w(w0, pair + 16);
+                pair_out(w1, pair + 8);
+            }
+            __syncthreads();   // the next tile overwrites Hf
+            continue;
         }
         // Last activations to a.hout, 16 bytes per thread and store.
         for (int e = tid; e < NV * (WIDTH / 8); e += 512) {
@@ -906,6 +976,20 @@ bool infer_fused_supported(int width, int depth) { return (width == 64 || width 
 
 hipError_t launch_mlp_infer(int width, int tile, const InferArgs& a, hipStream_t s)
 {
+    // Width 256, trains in FP32: beyond 64 voxels per CU the whole network per
+    // tile of 128 or 208 voxels, whichever pads the rounds of 256 tiles to
+    // fewer voxels. 1120 TRs, us with 64-voxel workgroups / tiles of 128 / 208:
+    // 16384 voxels 140 / 172 / 222, 32768 222 / 193 / 249, 50176 414 / 374 / 283,
+    // 65536 423 / 373 / 491, 102400 738 / 743 / 599; 128 TRs: 50 / 68 / 85,
+    // 75 / 66 / 88, 127 / 121 / 89, 130 / 122 / 164, 228 / 235 / 168.
+    if (tile == 0 && width == 256 && !a.f16 && a.n > 64 * 256) {
+        auto rounds = [&](int nv) { return ceil_div(ceil_div(a.n, nv), 256); };
+        if (rounds(208) * 208 <= rounds(128) * 128)
+            mlp_hidden_kernel<208, true><<<std::min(ceil_div(a.n, 208), 256), 512, 0, s>>>(a);
+        else
+            mlp_hidden_kernel<128, true><<<std::min(ceil_div(a.n, 128), 256), 512, 0, s>>>(a);
+        return hipGetLastError();
+    }
     if (tile == 0) tile = width == 256 ? -64 : 64;
     const int grid = ceil_div(a.n, tile < 0 ? -tile : tile);
 #define INFER(W_, NV_, T_, PF_)                                              \
@@ -937,7 +1021,7 @@ hipError_t launch_mlp_hidden(const InferArgs& a, hipStream_t s)
     // 88 / 76 us; the fused kernel's hidden layers on 32-voxel tiles 108 us.
     constexpr int NV = 208;
     const int tiles = ceil_div(a.n, NV);
-    mlp_hidden_kernel<NV><<<std::min(tiles, 256), 512, 0, s>>>(a);
+    mlp_hidden_kernel<NV, false><<<std::min(tiles, 256), 512, 0, s>>>(a);
     return hipGetLastError();
 }
 
