@@ -49,10 +49,9 @@ namespace mrstat {
 namespace {
 
 constexpr float kTwoPi = 6.28318530717958647692f;
-// TRs per forward block. Measured at 224 x 224, 1120 TRs, 24 terms (J v):
-// the power chain per voxel and TR 0.67 ms; powers shared by the block's TRs
-// 0.55 with 2 TRs, 0.57 with 1; the next row's inputs loaded while a row is
-// summed 0.75 (221 registers: two waves per SIMD instead of three).
+// TRs per forward lane. Measured at 224 x 224, 1120 TRs, 24 terms (J v):
+// the power chain per voxel and TR 0.67 ms; powers shared by the lane's TRs
+// 0.55 with 2 TRs, 0.57 with 1.
 constexpr int RD_NTB = 2;
 
 __device__ __forceinline__ float2 cmul(float2 a, float2 b)
@@ -83,12 +82,10 @@ struct RdVoxel {
     float r2t;
 };
 
-__device__ __forceinline__ RdVoxel rd_voxel(const float* __restrict__ theta, const float* __restrict__ db0,
-                                             float db0_unit, int nv, int j, float te, float tmax)
+__device__ __forceinline__ RdVoxel rd_voxel(float ln_t2, float f, float te, float tmax)
 {
     RdVoxel o;
-    const float r2 = expf(-theta[(size_t)nv + j]);   // theta row 1 = ln T2
-    const float f = db0 ? db0[j] * db0_unit : 0.f;
+    const float r2 = expf(-ln_t2);
     o.r2t = r2 * tmax;
     o.L = make_float2(-o.r2t, -kTwoPi * f * tmax);
     float sn, cs;
@@ -120,10 +117,16 @@ struct EconTable {
 template <int NQ>
 __device__ constexpr EconTable<NQ> kEcon{};
 
-// Forward term sums. Block = 256 lanes, one image column per lane (nx <=
-// 256), RD_NTB TRs; the lanes walk all rows, keeping the NQ complex sums of
-// each TR in registers; then the NC economised sums V_m = sum_q e_mq U_q
-// written once per (term, TR, column), no partials.
+// Forward term sums. A lane takes one image column and RD_NTB TRs (columns and
+// TR pairs numbered through, so neither ragged widths leave lanes idle nor a few
+// workgroups make a round of their own: 224 columns x 1120 TRs are 1960 waves,
+// two per SIMD) and walks all rows, the next row's inputs on their way,
+// keeping the NQ complex sums of each TR in registers; then the NC economised
+// sums V_m = sum_q e_mq U_q written once per (term, TR, column), no partials.
+// Bound by the vector units (24 terms: 302 operations per voxel and TR, a third
+// of them the voxel's powers and exponentials). With a workgroup per TR pair and
+// the rows' loads waited for, J v at 224 x 224, 1120 TRs, 24 terms took 576 us;
+// columns and pairs numbered through 527, with the next row's loads as well 472.
 // MODE as the static y-stages: 0 signal, 1 J v with four trains, 3 J v with
 // three (B1 held fixed). db0 (Hz per db0_unit) is the map or theta row 5;
 // with Delta B0 fitted (fit, J v only) the direction's row 5 adds
@@ -138,9 +141,9 @@ __global__ __launch_bounds__(256) void rd_fwd_kernel(const TT* __restrict__ trai
                                                      int nc, int nx, int ny, int nv, int T, float te, float tmax)
 {
     constexpr bool JV = MODE != 0, DB1 = MODE == 1;
-    const int ix = threadIdx.x;
-    const bool colok = ix < nx;
-    const int n0 = blockIdx.x * RD_NTB;
+    constexpr int NTR = !JV ? 1 : DB1 ? 4 : 3;
+    const int e = blockIdx.x * blockDim.x + threadIdx.x;
+    const int ix = e % nx, n0 = e / nx * RD_NTB;
     const int c = blockIdx.y;   // coil: its sums are rows c nc .. c nc + nc - 1
     const size_t plane = (size_t)T * nv;
     float2 acc[RD_NTB][NQ];
@@ -148,25 +151,58 @@ __global__ __launch_bounds__(256) void rd_fwd_kernel(const TT* __restrict__ trai
     for (int t = 0; t < RD_NTB; ++t)
 #pragma unroll
         for (int q = 0; q < NQ; ++q) acc[t][q] = make_float2(0.f, 0.f);
-    if (colok) {
+    struct Row {
+        float t2, f, rr, ri, v0, v1, v2, v3, v4, v5, m[RD_NTB][NTR];
+        float2 ey[RD_NTB], cw;
+        bool on;
+    };
+    auto load = [&](int iy) {
+        Row r;
+        const int j = iy * nx + ix;
+        r.on = mask == nullptr || mask[j] != 0;
+        r.t2 = theta[(size_t)nv + j];   // theta row 1 = ln T2
+        r.f = db0 ? db0[j] * db0_unit : 0.f;
+        r.rr = theta[3 * (size_t)nv + j];
+        r.ri = theta[4 * (size_t)nv + j];
+        r.cw = coil != nullptr ? coil[(size_t)c * nv + j] : make_float2(1.f, 0.f);
+        if constexpr (JV) {
+            r.v0 = v[j];
+            r.v1 = v[(size_t)nv + j];
+            if constexpr (DB1) r.v2 = v[2 * (size_t)nv + j];
+            r.v3 = v[3 * (size_t)nv + j];
+            r.v4 = v[4 * (size_t)nv + j];
+            r.v5 = fit ? v[5 * (size_t)nv + j] : 0.f;
+        }
+#pragma unroll
+        for (int t = 0; t < RD_NTB; ++t) {
+            const int n = min(n0 + t, T - 1);   // TRs past the end are not stored
+            const TT* b = trains + (size_t)n * nv + j;
+#pragma unroll
+            for (int p = 0; p < NTR; ++p) r.m[t][p] = (float)b[p * plane];
+            r.ey[t] = eytab[(size_t)n * ny + iy];
+        }
+        return r;
+    };
+    if (n0 < T) {
+        Row next = load(0);
         for (int iy = 0; iy < ny; ++iy) {
-            const int j = iy * nx + ix;
-            if (mask != nullptr && mask[j] == 0) continue;   // no contribution
-            RdVoxel vx = rd_voxel(theta, db0, db0_unit, nv, j, te, tmax);
-            if (coil != nullptr) vx.c = cmul(vx.c, coil[(size_t)c * nv + j]);   // the coil weight joins c
-            const float rr = theta[3 * (size_t)nv + j], ri = theta[4 * (size_t)nv + j];
+            const Row r = next;
+            next = load(min(iy + 1, ny - 1));
+            if (!r.on) continue;   // masked: no contribution
+            RdVoxel vx = rd_voxel(r.t2, r.f, te, tmax);
+            if (coil != nullptr) vx.c = cmul(vx.c, r.cw);   // the coil weight joins c
+            const float rr = r.rr, ri = r.ri;
             float nr = 0.f, ni = 0.f, w0 = 0.f, w1 = 0.f, w2 = 0.f, cte = 0.f, ctau = 0.f;
             if constexpr (JV) {
-                nr = v[3 * (size_t)nv + j];
-                ni = v[4 * (size_t)nv + j];
-                w0 = v[j];
-                w1 = v[(size_t)nv + j];
-                if constexpr (DB1) w2 = v[2 * (size_t)nv + j];
-                if (fit) {   // 2 pi db0_unit v_5 times TE, and times tau_max
-                    const float w5 = kTwoPi * db0_unit * v[5 * (size_t)nv + j];
-                    cte = w5 * te;
-                    ctau = w5 * tmax;
-                }
+                nr = r.v3;
+                ni = r.v4;
+                w0 = r.v0;
+                w1 = r.v1;
+                if constexpr (DB1) w2 = r.v2;
+                // 2 pi db0_unit v_5 times TE, and times tau_max
+                const float w5 = kTwoPi * db0_unit * r.v5;
+                cte = w5 * te;
+                ctau = w5 * tmax;
             }
             // Powers L^q of this voxel, shared by the block's TRs.
             float2 P[NQ];
@@ -175,21 +211,19 @@ __global__ __launch_bounds__(256) void rd_fwd_kernel(const TT* __restrict__ trai
             for (int q = 1; q < NQ; ++q) P[q] = cmul(P[q - 1], vx.L);
 #pragma unroll
             for (int t = 0; t < RD_NTB; ++t) {
-                const int n = min(n0 + t, T - 1);   // TRs past the end are not stored
-                const TT* b = trains + (size_t)n * nv + j;
-                const float mu = (float)b[0];
+                const float mu = r.m[t][0];
                 float2 x, y = make_float2(0.f, 0.f);   // i rho mu / i (rho a + nu mu); i rho mu r2t v_lnT2
                 if constexpr (!JV) {
                     x = make_float2(-ri * mu, rr * mu);
                 } else {
-                    const float m1 = (float)b[plane], m2 = (float)b[2 * plane];
-                    const float a = DB1 ? fmaf(w0, m1, fmaf(w1, m2, w2 * (float)b[3 * plane])) : fmaf(w0, m1, w1 * m2);
+                    const float m1 = r.m[t][JV ? 1 : 0], m2 = r.m[t][JV ? 2 : 0];
+                    const float a = DB1 ? fmaf(w0, m1, fmaf(w1, m2, w2 * r.m[t][NTR - 1])) : fmaf(w0, m1, w1 * m2);
                     // i (rho a + nu mu) + rho mu cte; i rho mu r2t w1 + rho mu ctau
                     const float e = mu * cte, et = mu * ctau, yt = mu * vx.r2t * w1;
                     x = make_float2(fmaf(rr, e, -fmaf(ri, a, ni * mu)), fmaf(ri, e, fmaf(rr, a, nr * mu)));
                     y = make_float2(fmaf(rr, et, -ri * yt), fmaf(ri, et, rr * yt));
                 }
-                const float2 ec = cmul(eytab[(size_t)n * ny + iy], vx.c);
+                const float2 ec = cmul(r.ey[t], vx.c);
                 const float2 z = cmul(ec, x);
                 acc[t][0].x += z.x;
                 acc[t][0].y += z.y;
@@ -401,7 +435,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))) voi
         iyv[r] = iy0 + r * hy;
         jv[r] = iyv[r] < ny ? iyv[r] * nx + ix : -1;
         on[r] = jv[r] >= 0 && (mask == nullptr || mask[jv[r]] != 0);
-        vx[r] = rd_voxel(theta, db0, db0_unit, nv, on[r] ? jv[r] : jp % nv, te, tmax);
+        const int jr = on[r] ? jv[r] : jp % nv;
+        vx[r] = rd_voxel(theta[(size_t)nv + jr], db0 ? db0[jr] * db0_unit : 0.f, te, tmax);   // theta row 1 = ln T2
         cheb_coeffs<NQ>(vx[r].L, Ca[r], Cb[r]);
 #pragma unroll
         for (int p = 0; p < NTR; ++p) A[r][p] = make_float2(0.f, 0.f);
@@ -505,7 +540,7 @@ hipError_t fwd_q(const Dims& d, int mode, int nc, const TT* trains, const float*
                  float2* U, float te, float tmax, hipStream_t s)
 {
     if (nc < 1 || nc > NQ) return hipErrorInvalidValue;
-    const dim3 grid(ceil_div(d.T, RD_NTB), d.C);
+    const dim3 grid(ceil_div(ceil_div(d.T, RD_NTB) * d.nx, 256), d.C);
     const int fit = d.np == 6;
 #define RD_FWD(M)                                                                                                 \
     rd_fwd_kernel<M, NQ, TT><<<grid, 256, 0, s>>>(trains, theta, v, coil, mask, db0, db0_unit, fit, eytab, U, nc, \
