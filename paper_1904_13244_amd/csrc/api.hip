@@ -409,14 +409,14 @@ mrstat_status adjoint(mrstat_ctx ctx, const float* theta, const void* w, float* 
     if (ntr < 4 && ((param_mask >> 2) & 1))
         return fail(ctx, MRSTAT_ERR_STATE, "linearisation holds no dm/dB1 train");
     if (ctx->rd_nq > 0) {
-        const int nc = ctx->rd_nc;
+        const int nc = ctx->rd_nc, chunks = rd_adj_chunks(d, nc, p.adj_chunks);
         HIP_TRY(TRACED(MRSTAT_K_VECTOR, launch_rd_expand(d, nc, ctx->rd_dwell_u, (const float2*)w, ctx->rdw(), s)));
         HIP_TRY(TRACED(MRSTAT_K_XADJ, launch_xgemm_adj(ctx->rd_dims(), ctx->L.rdp, ctx->enc, ctx->rdw(),
                                                        ctx->dextab(), ctx->bfrag(1), ctx->rdW(), s)));
-        HIP_TRY(TRACED(MRSTAT_K_YADJ, launch_rd_adj(d, nc, ntr, p.adj_chunks, ctx->trains(), ctx->f16, theta,
+        HIP_TRY(TRACED(MRSTAT_K_YADJ, launch_rd_adj(d, nc, ntr, chunks, ctx->trains(), ctx->f16, theta,
                                                     ctx->coil, ctx->mask, ctx->rd_db0, ctx->db0_unit, ctx->deytab(),
                                                     ctx->rdW(), ctx->apart(), ctx->st.te, ctx->rd_tmax, s)));
-        HIP_TRY(TRACED(MRSTAT_K_FINISH, launch_jhw_finish(d, p.adj_chunks, ctx->apart(), theta, ctx->mask, param_mask, g,
+        HIP_TRY(TRACED(MRSTAT_K_FINISH, launch_jhw_finish(d, chunks, ctx->apart(), theta, ctx->mask, param_mask, g,
                                                           dir, dir ? ctx->red() : nullptr, s, step, res)));
         return MRSTAT_OK;
     }

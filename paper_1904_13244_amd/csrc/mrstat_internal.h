@@ -73,6 +73,8 @@ hipError_t launch_rd_combine(const Dims& d, int nc, int mode, const float2* Y, f
 hipError_t launch_rd_expand(const Dims& d, int nc, float dwell_u, const float2* w, float2* wq, hipStream_t s);
 // Chunk partials in the gradient assembly's layout; with d.np == 6 (ntr 3 or
 // 4) the Delta B0 pair follows as planes 8 and 9 of each chunk.
+// TR chunks for J^H w, at most `most` (what the partials have room for).
+int rd_adj_chunks(const Dims& d, int nc, int most);
 hipError_t launch_rd_adj(const Dims& d, int nc, int ntr, int chunks, const void* trains, bool f16,
                          const float* theta, const float2* coil, const uint8_t* mask, const float* db0,
                          float db0_unit, const float2* eytab, const float2* W, float* apart, float te, float tmax,

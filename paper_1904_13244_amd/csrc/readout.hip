@@ -395,7 +395,8 @@ __device__ __forceinline__ void cheb_coeffs(float2 Lf, float2 (&ca)[NC], float2 
 // Chebyshev form, 16 terms for the same bound, 0.52 (and its adjoint x-GEMM
 // 0.084 instead of 0.122). TR chunks (HIP events, 16 terms): 9 chunks
 // 0.53-0.57, 18 0.55; 8, 16, 24 and 32 chunks with each XCD given its own
-// chunks (so its L2 holds only their term values) 0.58, 0.60, 0.58, 0.61.
+// chunks (so its L2 holds only their term values) 0.58, 0.60, 0.58, 0.61; 5,
+// which make one round of workgroups (rd_adj_chunks), 0.48-0.52.
 // V' from the a_m alone (u T_m = (T_(m-1) + T_(m+1)) / 2 moved onto the term
 // values: 201 registers instead of 233, still two waves per SIMD) 0.60.
 // Voxels per thread of the adjoint (rows iy, iy + hy, ... of one column):
@@ -590,6 +591,25 @@ hipError_t adj_q(const Dims& d, int ntr, int chunks, const TT* trains, const flo
 }
 
 }  // namespace
+
+int rd_adj_chunks(const Dims& d, int nc, int most)
+{
+    // Workgroups of one chunk by the rule of adj_q; two are resident per CU.
+    // Every chunk pays for its voxels' coefficients again (as long as 32 of its
+    // TRs), and a lone workgroup on a CU takes three quarters of a pair's time.
+    // 224 x 224, 1120 TRs, 16 terms: 9 chunks (882 workgroups) 587 us, 5 (490) 517.
+    const int R = nc <= 16 ? rd_adj_rows<16>() : rd_adj_rows<20>();
+    const int wg = ceil_div((d.ny + R - 1) / R * d.nx, 256);
+    int best = most;
+    int64_t t_best = INT64_MAX;
+    for (int c = 1; c <= most; ++c) {
+        const int per = ceil_div(d.T, c);
+        if (ceil_div(d.T, per) != c) continue;
+        const int64_t k = ceil_div(wg * c, 256), t = (4 * (k / 2) + 3 * (k % 2)) * (per + 32);
+        if (t < t_best) t_best = t, best = c;
+    }
+    return best;
+}
 
 int rd_terms(double bound)
 {
