@@ -15,17 +15,19 @@
 // ln T2 and B1 are carried in forward mode through both updates (zero at
 // the start; d a / d B1 = alpha_n scale).
 //
-// Four lanes per voxel, isochromat q on lane q % 4 (slot q / 4); per TR the
-// lanes' weighted sums meet by two shuffles and lane p stores train p.
+// L lanes per voxel (4, 8 or 16), isochromat q on lane q % L (slot q / L); per
+// TR the lanes' weighted sums meet by shuffles that leave train p on lanes
+// p mod 4 (five for 16 lanes instead of sixteen), and lane p stores train p.
+// Bound by the sines and updates of a lane's slots, one wave after another while
+// the chip is short of waves (launch_iso).
 #include "mrstat_internal.h"
+
+#include <algorithm>
 
 namespace mrstat {
 namespace {
 
-constexpr int ISO_L = 4;                          // lanes per voxel
-constexpr int ISO_SLOTS = MAX_ISOCHROMATS / ISO_L;
-
-template <int NTAN, bool LIST, typename TT>
+template <int ISO_L, int NTAN, bool LIST, typename TT>
 __global__ __launch_bounds__(256) void iso_kernel(const float* __restrict__ theta, const float2* __restrict__ seq,
                                                   TT* __restrict__ out, int nv, int T, SeqTimes st, IsoProfile prof,
                                                   const int* __restrict__ idx, const int* __restrict__ count)
@@ -45,6 +47,7 @@ __global__ __launch_bounds__(256) void iso_kernel(const float* __restrict__ thet
         j = valid ? vox : nv - 1;   // every lane stays active for the shuffles
     }
     constexpr bool TANG = NTAN > 0, TB1 = NTAN == 3;
+    constexpr int ISO_SLOTS = MAX_ISOCHROMATS / ISO_L;
 
     const float lnT1 = theta[j], lnT2 = theta[nv + j], B1 = theta[2 * nv + j];
     const float rT1 = expf(-lnT1), rT2 = expf(-lnT2);
@@ -111,40 +114,56 @@ __global__ __launch_bounds__(256) void iso_kernel(const float* __restrict__ thet
             y[k] = E2 * yr;
             z[k] = fmaf(E1, zr, R1);
         }
-        // Sum over the voxel's four lanes; lane p stores train p.
-        m0 += __shfl_xor(m0, 1, ISO_L);
-        m0 += __shfl_xor(m0, 2, ISO_L);
+        // Sum over the voxel's lanes: lane l keeps train l mod 4.
+        float m = m0;
         if constexpr (TANG) {
-            m1 += __shfl_xor(m1, 1, ISO_L);
-            m1 += __shfl_xor(m1, 2, ISO_L);
-            m2 += __shfl_xor(m2, 1, ISO_L);
-            m2 += __shfl_xor(m2, 2, ISO_L);
+            const bool b0 = l & 1, b1 = l & 2;
+            float k0 = b0 ? m1 : m0, k1 = b0 ? m3 : m2;
+            k0 += __shfl_xor(b0 ? m0 : m1, 1, ISO_L);
+            k1 += __shfl_xor(b0 ? m2 : m3, 1, ISO_L);
+            m = b1 ? k1 : k0;
+            m += __shfl_xor(b1 ? k0 : k1, 2, ISO_L);
+        } else {
+            m += __shfl_xor(m, 1, ISO_L);
+            m += __shfl_xor(m, 2, ISO_L);
         }
-        if constexpr (TB1) {
-            m3 += __shfl_xor(m3, 1, ISO_L);
-            m3 += __shfl_xor(m3, 2, ISO_L);
-        }
+#pragma unroll
+        for (int x = 4; x < ISO_L; x *= 2) m += __shfl_xor(m, x, ISO_L);
         const float ke = sg * E2e;
-        if (valid && l <= NTAN) {
-            const float vv = l == 0 ? m0 : (l == 1 ? m1 : (l == 2 ? m2 : m3));
-            out[(size_t)l * plane + (size_t)n * nv + j] = (TT)(ke * vv);
-        }
+        if (valid && l <= NTAN)
+            out[(size_t)l * plane + (size_t)n * nv + j] = (TT)(ke * m);
     }
 }
 
+template <int L, bool LIST, typename TT>
+hipError_t iso_lanes(const Dims& d, SeqTimes st, const float* theta, const float2* seq, TT* out, int ntan,
+                     const IsoProfile& prof, const int* idx, const int* count, hipStream_t s)
+{
+    const int grid = (int)(((long)d.nv * L + 255) / 256);
+    switch (ntan) {
+    case 0: iso_kernel<L, 0, LIST, TT><<<grid, 256, 0, s>>>(theta, seq, out, d.nv, d.T, st, prof, idx, count); break;
+    case 2: iso_kernel<L, 2, LIST, TT><<<grid, 256, 0, s>>>(theta, seq, out, d.nv, d.T, st, prof, idx, count); break;
+    case 3: iso_kernel<L, 3, LIST, TT><<<grid, 256, 0, s>>>(theta, seq, out, d.nv, d.T, st, prof, idx, count); break;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+// Lanes per voxel: a wave's time is that of its slots and half a slot for the
+// sums and stores, and a SIMD takes two waves in the time of one, more in
+// proportion. 67 x 53 voxels, 16 isochromats, 210 TRs: 16 lanes 91 us, 4 lanes 189 us.
 template <bool LIST, typename TT>
 hipError_t iso_typed(const Dims& d, SeqTimes st, const float* theta, const float2* seq, TT* out, int ntan,
                      const IsoProfile& prof, const int* idx, const int* count, hipStream_t s)
 {
-    const long threads = (long)d.nv * ISO_L;
-    const int grid = (int)((threads + 255) / 256);
-    switch (ntan) {
-    case 0: iso_kernel<0, LIST, TT><<<grid, 256, 0, s>>>(theta, seq, out, d.nv, d.T, st, prof, idx, count); break;
-    case 2: iso_kernel<2, LIST, TT><<<grid, 256, 0, s>>>(theta, seq, out, d.nv, d.T, st, prof, idx, count); break;
-    case 3: iso_kernel<3, LIST, TT><<<grid, 256, 0, s>>>(theta, seq, out, d.nv, d.T, st, prof, idx, count); break;
-    default: return hipErrorInvalidValue;
+    auto cost = [&](int l) { return (2L * ceil_div(prof.n, l) + 1) * std::max(131072L, (long)d.nv * l); };
+    if constexpr (!LIST) {
+        if (cost(16) < cost(4) && cost(16) <= cost(8))
+            return iso_lanes<16, LIST, TT>(d, st, theta, seq, out, ntan, prof, idx, count, s);
+        if (cost(8) < cost(4))
+            return iso_lanes<8, LIST, TT>(d, st, theta, seq, out, ntan, prof, idx, count, s);
     }
-    return hipGetLastError();
+    return iso_lanes<4, LIST, TT>(d, st, theta, seq, out, ntan, prof, idx, count, s);
 }
 
 }  // namespace
