@@ -62,8 +62,8 @@ __device__ __forceinline__ int fwd_chunk(unsigned b, unsigned nb)
 // Forward y-stage. Block = FW = 16 waves; wave w, half h covers row
 // iy = rowbase + 32 r + 2 w + h for r < R, and ix = 32 bx + lane % 32. A block
 // therefore spans 32 R rows (all rows when ny <= 32 R: U is complete and no
-// partial sums are written). Each thread keeps its R voxels' weights (and
-// coil sensitivities) in registers for its TR chunk. Per TR every lane first
+// partial sums are written). Each thread keeps its R voxels' weights in
+// registers for its TR chunk (one coil; more in ystage_fwd_coil_kernel). Per TR every lane first
 // issues all of its loads (clamped indices, no branches between them), then
 // accumulates; the two rows of a wave are folded with a lane swap and the
 // per-wave sums of the whole chunk are kept in LDS and reduced after a
@@ -79,20 +79,19 @@ constexpr int FW = 16;
 //         row groups. With 2-byte trains a row is not a whole number of
 //         lines in general (448 bytes at 224 columns); spanning all columns
 //         keeps both halves of every line inside one block.
-template <int MODE, int R, int CC, typename TT, int G>
+template <int MODE, int R, typename TT, int G>
 __global__ __launch_bounds__(1024) void ystage_fwd_kernel(
     const TT* __restrict__ trains, const float* __restrict__ theta, const float* __restrict__ v,
-    const float2* __restrict__ coil, const uint8_t* __restrict__ mask,
-    const float2* __restrict__ eytab, float2* __restrict__ U, int nx, int ny, int nv, int T, int C,
-    int n_per_chunk)
+    const uint8_t* __restrict__ mask, const float2* __restrict__ eytab, float2* __restrict__ U, int nx, int ny,
+    int nv, int T, int n_per_chunk)
 {
     constexpr int XW = G == 0 ? 32 : 64 * G;          // columns per block
     constexpr int RS = G == 0 ? 2 * FW : FW / G;      // rows per step of the block
     constexpr int NS = G == 0 ? FW : FW / G;          // partial sums per column
-    // LDS: per-wave sums [TRs per chunk][CC][NS][XW], then the block's
+    // LDS: per-wave sums [TRs per chunk][NS][XW], then the block's
     // y-phases [TRs per chunk][RS R].
     extern __shared__ float2 lds[];
-    float2* eys = lds + (size_t)n_per_chunk * CC * NS * XW;
+    float2* eys = lds + (size_t)n_per_chunk * NS * XW;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int half = G == 0 ? lane >> 5 : 0;
     const int xl = G == 0 ? lane & 31 : (wave % (G == 0 ? 1 : G)) * 64 + lane;
@@ -116,7 +115,6 @@ __global__ __launch_bounds__(1024) void ystage_fwd_kernel(
     float2 P[R], Q[R];
     float v0[R], v1[R], v2[R];
     int jr[R], iyr[R];
-    float2 cw[R][CC];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int iy = iyb + RS * r;
@@ -133,11 +131,6 @@ __global__ __launch_bounds__(1024) void ystage_fwd_kernel(
             v0[r] = on ? v[j] : 0.f;
             v1[r] = on ? v[nv + j] : 0.f;
             if constexpr (DB1) v2[r] = on ? v[2 * nv + j] : 0.f;
-        }
-        if constexpr (CC > 1) {
-#pragma unroll
-            for (int c = 0; c < CC; ++c)
-                cw[r][c] = (ok && c < C) ? coil[(size_t)c * nv + j] : make_float2(0.f, 0.f);
         }
     }
 
@@ -161,9 +154,7 @@ __global__ __launch_bounds__(1024) void ystage_fwd_kernel(
             if constexpr (DB1) m3[r] = (float)b3[jr[r]];
             ey[r] = eyrow[RS * r];
         }
-        float2 acc[CC];
-#pragma unroll
-        for (int c = 0; c < CC; ++c) acc[c] = make_float2(0.f, 0.f);
+        float2 acc = make_float2(0.f, 0.f);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             float2 x;
@@ -175,40 +166,29 @@ __global__ __launch_bounds__(1024) void ystage_fwd_kernel(
                 x = make_float2(fmaf(P[r].x, a, Q[r].x * mu[r]), fmaf(P[r].y, a, Q[r].y * mu[r]));
             }
             const float2 z = cmul(ey[r], x);
-            if constexpr (CC == 1) {
-                acc[0].x += z.x;
-                acc[0].y += z.y;
-            } else {
-#pragma unroll
-                for (int c = 0; c < CC; ++c) acc[c] = cfma(cw[r][c], z, acc[c]);
-            }
+            acc.x += z.x;
+            acc.y += z.y;
         }
-#pragma unroll
-        for (int c = 0; c < CC; ++c) {
-            if constexpr (G == 0) {
-                const float2 t = shfl_xor2(acc[c], 32);
-                if (half == 0)
-                    lds[(((n - n0) * CC + c) * NS + slot) * XW + xl] =
-                        make_float2(acc[c].x + t.x, acc[c].y + t.y);
-            } else {
-                lds[(((n - n0) * CC + c) * NS + slot) * XW + xl] = acc[c];
-            }
+        if constexpr (G == 0) {
+            const float2 t = shfl_xor2(acc, 32);
+            if (half == 0) lds[((n - n0) * NS + slot) * XW + xl] = make_float2(acc.x + t.x, acc.y + t.y);
+        } else {
+            lds[((n - n0) * NS + slot) * XW + xl] = acc;
         }
     }
     __syncthreads();
-    const int nout = (n1 - n0) * CC * XW;
+    const int nout = (n1 - n0) * XW;
     for (int o = threadIdx.x; o < nout; o += blockDim.x) {
-        const int l = o % XW, bc = o / XW;   // bc = TR-in-chunk * CC + c
-        float2 s = lds[(bc * NS) * XW + l];
+        const int l = o % XW, b = o / XW;   // b: TR in the chunk
+        float2 s = lds[(b * NS) * XW + l];
 #pragma unroll
         for (int w = 1; w < NS; ++w) {
-            const float2 t = lds[(bc * NS + w) * XW + l];
+            const float2 t = lds[(b * NS + w) * XW + l];
             s.x += t.x;
             s.y += t.y;
         }
-        const int b = bc / CC, c = bc % CC;
         const int oix = blockIdx.x * XW + l;
-        if (oix < nx && c < C) U[(((size_t)yb * C + c) * T + (n0 + b)) * nx + oix] = s;
+        if (oix < nx) U[((size_t)yb * T + (n0 + b)) * nx + oix] = s;
     }
 }
 
@@ -499,8 +479,8 @@ __global__ void usum_kernel(const float2* upart, float2* out, int nby, size_t co
 
 // ------------------------------------------------------------------------
 // Adjoint y-stage: A_p[j] = sum_n mu_p[n,j] V[n,j],
-// V[n,j] = conj(Ey[n,iy]) sum_c conj(C_c[j]) W_c[n,ix], summed over the TRs of
-// one chunk. One thread per voxel in voxel order (each wave reads 256
+// V[n,j] = conj(Ey[n,iy]) W[n,ix], summed over the TRs of one chunk (one coil;
+// more below). One thread per voxel in voxel order (each wave reads 256
 // contiguous bytes per train), blocks of 256 voxels span at most
 // 256 / nx + 2 rows, whose y-phases for the chunk are staged in LDS; W comes
 // through the vector cache (a block reuses each W row across its rows).
@@ -513,12 +493,10 @@ __global__ void usum_kernel(const float2* upart, float2* out, int nby, size_t co
 // dm/dB1 train) keeps the four-train layout with the B1 pair left unwritten.
 __host__ __device__ constexpr int apart_planes(int ntrain) { return ntrain == 1 ? 1 : 4; }
 
-template <int NTRAIN, int CC, int NBA, typename TT, int VX>
+template <int NTRAIN, int NBA, typename TT, int VX>
 __global__ __launch_bounds__(256) void ystage_adj_kernel(
-    const TT* __restrict__ trains, const float2* __restrict__ coil,
-    const uint8_t* __restrict__ mask, const float2* __restrict__ eytab,
-    const float2* __restrict__ W, float* __restrict__ apart, int nx, int ny, int nv, int T,
-    int C, int n_per_chunk)
+    const TT* __restrict__ trains, const uint8_t* __restrict__ mask, const float2* __restrict__ eytab,
+    const float2* __restrict__ W, float* __restrict__ apart, int nx, int ny, int nv, int T, int n_per_chunk)
 {
     // VX consecutive voxels per thread (VX = 2: FP16 trains read as pairs,
     // nx even, so a pair never straddles a row); a block spans 256 VX voxels.
@@ -544,14 +522,6 @@ __global__ __launch_bounds__(256) void ystage_adj_kernel(
     __syncthreads();
     const int myrow = iy - row0;
 
-    float2 cw[VX][CC];
-    if constexpr (CC > 1) {
-#pragma unroll
-        for (int u = 0; u < VX; ++u)
-#pragma unroll
-            for (int c = 0; c < CC; ++c)
-                cw[u][c] = c < C ? coil[(size_t)c * nv + j + u] : make_float2(0.f, 0.f);
-    }
     float2 acc[VX][NTRAIN];
 #pragma unroll
     for (int u = 0; u < VX; ++u)
@@ -559,25 +529,21 @@ __global__ __launch_bounds__(256) void ystage_adj_kernel(
         for (int p = 0; p < NTRAIN; ++p) acc[u][p] = make_float2(0.f, 0.f);
 
     for (int nb0 = n0; nb0 < n1; nb0 += NBA) {
-        float2 wv[NBA][VX][CC];
+        float2 wv[NBA][VX];
         float mu[NBA][VX][NTRAIN];
 #pragma unroll
         for (int b = 0; b < NBA; ++b) {
             const int n = min(nb0 + b, n1 - 1);
+            const float2* wrow = W + (size_t)n * nx + ix;
+            if constexpr (VX >= 2) {
 #pragma unroll
-            for (int c = 0; c < CC; ++c) {
-                const int cc = c < C ? c : 0;
-                const float2* wrow = W + ((size_t)cc * T + n) * nx + ix;
-                if constexpr (VX >= 2) {
-#pragma unroll
-                    for (int h = 0; h < VX / 2; ++h) {
-                        const float4 w2 = reinterpret_cast<const float4*>(wrow)[h];
-                        wv[b][2 * h][c] = make_float2(w2.x, w2.y);
-                        wv[b][2 * h + 1][c] = make_float2(w2.z, w2.w);
-                    }
-                } else {
-                    wv[b][0][c] = wrow[0];
+                for (int h = 0; h < VX / 2; ++h) {
+                    const float4 w2 = reinterpret_cast<const float4*>(wrow)[h];
+                    wv[b][2 * h] = make_float2(w2.x, w2.y);
+                    wv[b][2 * h + 1] = make_float2(w2.z, w2.w);
                 }
+            } else {
+                wv[b][0] = wrow[0];
             }
             const TT* __restrict__ t0 = trains + (size_t)n * nv;
 #pragma unroll
@@ -598,19 +564,7 @@ __global__ __launch_bounds__(256) void ystage_adj_kernel(
             const float2 eyc = eys[nl * rows + myrow];
 #pragma unroll
             for (int u = 0; u < VX; ++u) {
-                float2 wc;
-                if constexpr (CC == 1) {
-                    wc = wv[b][u][0];
-                } else {
-                    wc = make_float2(0.f, 0.f);
-#pragma unroll
-                    for (int c = 0; c < CC; ++c) {
-                        const float2 t = cmulconj(cw[u][c], wv[b][u][c]);
-                        wc.x += t.x;
-                        wc.y += t.y;
-                    }
-                }
-                float2 V = cmulconj(eyc, wc);
+                float2 V = cmulconj(eyc, wv[b][u]);
                 V.x *= keep;
                 V.y *= keep;
 #pragma unroll
@@ -1516,8 +1470,8 @@ hipError_t fwd_R(const Dims& d, const YPlan& p, const TT* trains, const float* t
             const size_t lds = (size_t)p.fwd_tr16 * (FW * 64 + (FW / p.g16) * p.r_fwd16) * sizeof(float2);
 #define FWD16_CASE(GG, RR)                                                                      \
     if (p.g16 == GG && p.r_fwd16 == RR) {                                                       \
-        ystage_fwd_kernel<MODE, RR, 1, TT, GG><<<grid, FW * 64, lds, s>>>(                      \
-            trains, theta, v, coil, mask, eytab, U, d.nx, d.ny, d.nv, d.T, d.C, p.fwd_tr16);    \
+        ystage_fwd_kernel<MODE, RR, TT, GG><<<grid, FW * 64, lds, s>>>(                         \
+            trains, theta, v, mask, eytab, U, d.nx, d.ny, d.nv, d.T, p.fwd_tr16);               \
         return hipGetLastError();                                                               \
     }
             FWD16_CASE(1, 1) FWD16_CASE(1, 2) FWD16_CASE(1, 3) FWD16_CASE(1, 4)
@@ -1547,24 +1501,21 @@ hipError_t fwd_R(const Dims& d, const YPlan& p, const TT* trains, const float* t
             ystage_fwd_coil_kernel<MODE, CC, 32, TT><<<grid, CW * 64, lds, s>>>(
                 trains, theta, v, coil, mask, eytab, U, d.nx, d.ny, d.nv, d.T, d.C, rows);
         return hipGetLastError();
-    }
-    dim3 grid(ceil_div(d.nx, 32), p.nby, ceil_div(d.T, p.fwd_tr));
-    const size_t lds = (size_t)p.fwd_tr * (CC * FW * 32 + 32 * p.r_fwd) * sizeof(float2);
+    } else {
+        dim3 grid(ceil_div(d.nx, 32), p.nby, ceil_div(d.T, p.fwd_tr));
+        const size_t lds = (size_t)p.fwd_tr * (FW * 32 + 32 * p.r_fwd) * sizeof(float2);
 #define FWD_CASE(RR)                                                                            \
     case RR:                                                                                    \
-        if constexpr (CC == 1 || RR <= 2)                                                       \
-            ystage_fwd_kernel<MODE, RR, CC, TT, 0><<<grid, FW * 64, lds, s>>>(                  \
-                trains, theta, v, coil, mask, eytab, U, d.nx, d.ny, d.nv, d.T, d.C, p.fwd_tr);  \
-        else                                                                                    \
-            return hipErrorInvalidValue;                                                        \
+        ystage_fwd_kernel<MODE, RR, TT, 0><<<grid, FW * 64, lds, s>>>(                          \
+            trains, theta, v, mask, eytab, U, d.nx, d.ny, d.nv, d.T, p.fwd_tr);                 \
         break;
-    switch (p.r_fwd) {
-        FWD_CASE(1) FWD_CASE(2) FWD_CASE(3) FWD_CASE(4) FWD_CASE(5) FWD_CASE(6) FWD_CASE(7)
-        FWD_CASE(8)
-        default: return hipErrorInvalidValue;
-    }
+        switch (p.r_fwd) {
+            FWD_CASE(1) FWD_CASE(2) FWD_CASE(3) FWD_CASE(4)
+            default: return hipErrorInvalidValue;
+        }
 #undef FWD_CASE
-    return hipGetLastError();
+        return hipGetLastError();
+    }
 }
 
 template <int NTRAIN, int CC, typename TT>
@@ -1590,8 +1541,8 @@ hipError_t adj_launch(const Dims& d, const YPlan& p, const TT* trains, const flo
             dim3 grid(ceil_div(d.nv, 512), p.adj_chunks);
             const int rows = std::min(d.ny, 512 / d.nx + 2);
             const size_t lds = (size_t)p.adj_per_chunk * rows * sizeof(float2);
-            ystage_adj_kernel<NTRAIN, CC, 8, TT, 2><<<grid, 256, lds, s>>>(
-                trains, coil, mask, eytab, W, apart, d.nx, d.ny, d.nv, d.T, d.C, p.adj_per_chunk);
+            ystage_adj_kernel<NTRAIN, 8, TT, 2><<<grid, 256, lds, s>>>(
+                trains, mask, eytab, W, apart, d.nx, d.ny, d.nv, d.T, p.adj_per_chunk);
             return hipGetLastError();
         }
     }
@@ -1613,15 +1564,14 @@ hipError_t adj_launch(const Dims& d, const YPlan& p, const TT* trains, const flo
         };
         return w64 ? go(&ystage_adj_coil_kernel<NTRAIN, CC, 64, NBA, TT>)
                    : go(&ystage_adj_coil_kernel<NTRAIN, CC, 32, NBA, TT>);
+    } else {
+        dim3 grid(ceil_div(d.nv, 256), p.adj_chunks);
+        const int rows = std::min(d.ny, 256 / d.nx + 2);
+        const size_t lds = (size_t)p.adj_per_chunk * rows * sizeof(float2);
+        ystage_adj_kernel<NTRAIN, 4, TT, 1><<<grid, 256, lds, s>>>(trains, mask, eytab, W, apart, d.nx, d.ny, d.nv,
+                                                                  d.T, p.adj_per_chunk);
+        return hipGetLastError();
     }
-    dim3 grid(ceil_div(d.nv, 256), p.adj_chunks);
-    const int rows = std::min(d.ny, 256 / d.nx + 2);
-    const size_t lds = (size_t)p.adj_per_chunk * rows * sizeof(float2);
-    constexpr int NBA = CC == 1 ? 4 : 2;
-    ystage_adj_kernel<NTRAIN, CC, NBA, TT, 1><<<grid, 256, lds, s>>>(trains, coil, mask, eytab, W, apart,
-                                                                    d.nx, d.ny, d.nv, d.T, d.C,
-                                                                    p.adj_per_chunk);
-    return hipGetLastError();
 }
 
 }  // namespace
