@@ -177,7 +177,7 @@ Layout make_layout(const Dims& d, bool nc, int rd_rows = 0)
     const size_t npmax = rd_rows > 0 ? 6 : 5, plmax = rd_rows > 0 ? 10 : 8;
     const int M = d.C * d.T;
     const int gemm_blocks = std::max(ceil_div(2 * d.nk, 64) * ceil_div(M, 64), xgemm_direct_blocks(d));
-    L.n_red = std::max({3 * RED_BLOCKS, gemm_blocks, cg_partials(d), tr_partials(d), nc ? nc_fwd_blocks(d) : 0});
+    L.n_red = std::max({3 * RED_BLOCKS, gemm_blocks, cg_partials(d), tr_partials(d), nc ? d.C * d.T * ceil_div(d.nk, 128) : 0});
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o = align256(o + bytes); return at; };
     const size_t nv = d.nv, T = d.T;
@@ -373,12 +373,15 @@ mrstat_status forward(mrstat_ctx ctx, int mode_y, int mode_x, const void* trains
     }
     if (ctx->nc) {
         int nred = 0;
+        // Partials past ctx->red()'s room are at most n_coils n_tr nx: U's, which
+        // no non-Cartesian call uses.
+        double* red = nc_fwd_blocks(d) <= ctx->L.n_red ? ctx->red() : ctx->at<double>(ctx->L.upart);
         HIP_TRY(TRACED(MRSTAT_K_NC_FWD, launch_nc_fwd(d, ctx->enc, mode_y, mode_x, trains, ctx->f16, theta, v,
                                                       ctx->coil, ctx->mask, ctx->dax(), ctx->day(), ctx->ncx(),
                                                       ctx->at<uint16_t>(ctx->L.hbuf),
-                                                      (const float2*)data, (float2*)out, ctx->red(), &nred, s)));
+                                                      (const float2*)data, (float2*)out, red, &nred, s)));
         if (mode_x == 0 && f_out)
-            HIP_TRY(TRACED(MRSTAT_K_VECTOR, launch_sum_partials(ctx->red(), nred, f_out, s)));
+            HIP_TRY(TRACED(MRSTAT_K_VECTOR, launch_sum_partials(red, nred, f_out, s)));
         return MRSTAT_OK;
     }
     int nby = 1;

@@ -30,7 +30,8 @@ struct Dims {
 int nc_adj_chunks(const Dims& d);
 int nc_fwd_blocks(const Dims& d);
 // X: workspace of T nv 8 bytes for the forward's voxel values, small: nv 512
-// bytes more of them.
+// bytes more for them or for their rows' exponents. Partials: nc_fwd_blocks, at
+// most C T ceil(nk / 128) or, if more, C T nx.
 hipError_t launch_nc_fwd(const Dims& d, int enc, int mode_y, int mode_x, const void* trains, bool f16,
                          const float* theta, const float* v, const float2* coil, const uint8_t* mask,
                          const double* ax, const double* ay, void* X, void* small, const float2* data, float2* out,

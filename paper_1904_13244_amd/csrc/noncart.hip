@@ -14,7 +14,7 @@
 // MFMA operand layouts (16x16x32): A lane l -> (row l%16, k 8(l/16)..+7), B
 // lane l -> (k 8(l/16)..+7, col l%16); D lane l -> (rows 4(l/16)+i, col l%16).
 // Measured at 224 x 224, 1120 spokes of 448 samples (FP32 MFMA 16x16x4 tiles
-// of 64 samples and 64 x 32 voxels, as before; now): voxel values 0.31 / 0.32
+// of 64 samples and 64 x 32 voxels, as before; now): voxel values 0.31 / 0.25
 // ms, forward 3.60 / 0.75, adjoint with the trains 5.2 / 1.03 + 0.29 (the
 // split-BF16 option's tiles 0.31 + 1.39 / 2.94); errors against the FP64 sums
 // at 36 x 70, 40 spokes: J v 5.6e-7 / 5.6e-7, J^H w 6.3e-7 / 6.0e-7.
@@ -59,7 +59,7 @@ typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 typedef unsigned u4 __attribute__((ext_vector_type(4)));
 
-constexpr float kPhaseScale = 256.f;
+constexpr float kPhaseScale = 16384.f;
 
 __device__ __forceinline__ void split_h(float a, float b, unsigned& hi, unsigned& lo)
 {
@@ -74,14 +74,14 @@ __device__ __forceinline__ f4 mma(u4 a, u4 b, f4 c)
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8, a), __builtin_bit_cast(h8, b), c, 0, 0, 0);
 }
 
-// 2^e that brings the float of bits m (without its sign) into [2^10, 2^11) (1
+// 2^e that brings the float of bits m (without its sign) into [2^14, 2^15) (1
 // for 0, infinities and NaN; e is bounded so that 2^-e kPhaseScale^-1 stays a
 // normal number).
 __device__ __forceinline__ float pow2_scale(unsigned m)
 {
     const int b = (int)(m >> 23);   // biased exponent
     if (m == 0u || b == 255) return 1.f;
-    const int e = min(137 - b, 118);
+    const int e = min(141 - b, 112);
     return __uint_as_float((unsigned)(e + 127) << 23);
 }
 
@@ -101,6 +101,13 @@ __device__ __forceinline__ unsigned wave_max(unsigned x)
     const auto b = __builtin_amdgcn_permlane32_swap(x, x, false, false);
     return max(b[0], b[1]);
 }
+
+template <int ROR> __device__ __forceinline__ float add_ror(float x)
+{
+    return x + __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x120 + ROR, 0xf, 0xf, false));
+}
+// Sum over the 16 lanes of a row, in every lane.
+__device__ __forceinline__ float sum_row16(float x) { return add_ror<8>(add_ror<4>(add_ror<2>(add_ror<1>(x)))); }
 
 typedef __attribute__((address_space(3))) char* lptr;
 __device__ __forceinline__ unsigned lds_addr(const void* p) { return (unsigned)(size_t)(lptr)(char*)p; }
@@ -458,6 +465,378 @@ __global__ __launch_bounds__(512) void nc_fwd_kernel(XStore X, const double* __r
 }
 
 // ------------------------------------------------------------------------
+// The forward up to 128 columns, and with coils where passes of whole records
+// would be short: the values stay FP32 (X[n][j] = i rho_j mu0 or i (rho_j
+// sum_p v_p dm_p/dtheta_p + (v3 + i v4) mu0), one record per TR however many
+// coils), and each forward block weights, scales and splits what it stages.
+// With each row and TR goes its largest value's exponent, and with each row and
+// coil that of its weights, from which the scale is made. A group of LX lanes
+// takes an image row of XT TRs, lane l columns l + LX c, so rows of any width
+// are read in whole segments and narrow ones share a wave.
+// ------------------------------------------------------------------------
+// Keys: |x| < 2^(b - 126) for the biased exponent b of a row's largest part
+// (255: infinite or NaN); b(values) + b(coil weights) bounds the parts of
+// their products by 2^(key - 251).
+constexpr int kNoWeight = 126;   // of a weight of 1 that is not multiplied
+
+// 2^e that brings values below 2^(key - 251) below 2^15 (e bounded so that
+// 2^e and 2^-e / kPhaseScale stay normal numbers).
+__device__ __forceinline__ int key_exp(int key) { return max(min(266 - key, 112), -126); }
+__device__ __forceinline__ float key_scale(int key) { return __uint_as_float((unsigned)(key_exp(key) + 127) << 23); }
+// 2^-e / kPhaseScale.
+__device__ __forceinline__ float unscale(int key) { return __uint_as_float((unsigned)(127 - 14 - key_exp(key)) << 23); }
+static_assert(kPhaseScale == 1 << 14, "unscale");
+
+template <int NTRV, int XT, typename TT>
+__global__ __launch_bounds__(256) void nc_value_kernel(const TT* __restrict__ trains, const float* __restrict__ theta,
+                                                       const float* __restrict__ v, const uint8_t* __restrict__ mask,
+                                                       const float2* __restrict__ coil, float2* __restrict__ X,
+                                                       int* __restrict__ keys, int* __restrict__ ckeys, int nx,
+                                                       int ny, int nv, int T, int C, int n_first, int n_end, int LX)
+{
+    const int xl = threadIdx.x % LX, iy = blockIdx.x * (256 / LX) + threadIdx.x / LX;
+    const size_t plane = (size_t)T * nv;
+    // Groups past the image repeat its last row, lanes past the row its last
+    // column; neither is stored.
+    const size_t jrow = (size_t)min(iy, ny - 1) * nx;
+    auto row4 = [&](const auto* p, auto (&o)[4]) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) o[c] = p[jrow + min(xl + LX * c, nx - 1)];
+    };
+    float rr[4], ri[4], w[3][4], nr[4], ni[4];
+    bool on[4];
+    row4(theta + 3 * (size_t)nv, rr);
+    row4(theta + 4 * (size_t)nv, ri);
+    if constexpr (NTRV > 1) {
+#pragma unroll
+        for (int q = 0; q < NTRV - 1; ++q) row4(v + (size_t)q * nv, w[q]);
+        row4(v + 3 * (size_t)nv, nr);
+        row4(v + 4 * (size_t)nv, ni);
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) on[c] = xl + LX * c < nx;
+    if (mask != nullptr) {
+        uint8_t mk[4];
+        row4(mask, mk);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) on[c] = on[c] && mk[c] != 0;
+    }
+    auto row_max = [&](unsigned a) {   // biased exponent of the row's largest
+        for (int o = LX / 2; o > 0; o /= 2) a = max(a, (unsigned)__shfl_xor((int)a, o));
+        return (int)(a >> 23);
+    };
+    if (coil != nullptr && blockIdx.y == 0)
+        for (int q = 0; q < C; ++q) {
+            float2 cw[4];
+            row4(coil + (size_t)q * nv, cw);
+            unsigned a = 0u;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) a = max(a, max(mag(cw[c].x), mag(cw[c].y)));
+            const int key = row_max(a);
+            if (xl == 0 && iy < ny) ckeys[(size_t)q * ny + iy] = key;
+        }
+    const int n0 = n_first + blockIdx.y * XT;
+    TT m[XT][NTRV][4];
+#pragma unroll
+    for (int k = 0; k < XT; ++k)
+#pragma unroll
+        for (int q = 0; q < NTRV; ++q) row4(trains + q * plane + (size_t)min(n0 + k, n_end - 1) * nv, m[k][q]);
+#pragma unroll
+    for (int k = 0; k < XT; ++k) {
+        float2 x[4];
+        unsigned a = 0u;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            float t = 0.f;
+            const float mu = (float)m[k][0][c];
+#pragma unroll
+            for (int q = 1; q < NTRV; ++q) t = fmaf(w[q - 1][c], (float)m[k][q][c], t);
+            if constexpr (NTRV == 1)
+                x[c] = make_float2(-ri[c] * mu, rr[c] * mu);
+            else
+                x[c] = make_float2(-(ri[c] * t + ni[c] * mu), rr[c] * t + nr[c] * mu);
+            if (!on[c]) x[c] = make_float2(0.f, 0.f);   // whatever a masked voxel's trains hold
+            a = max(a, max(mag(x[c].x), mag(x[c].y)));
+        }
+        const int n = n0 + k, key = row_max(a);
+        if (iy >= ny || n >= n_end) continue;
+        if (xl == 0) keys[(size_t)(n - n_first) * ny + iy] = key;
+        float2* dst = X + (size_t)n * nv + jrow;
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            if (xl + LX * c < nx) dst[xl + LX * c] = x[c];
+    }
+}
+
+// ------------------------------------------------------------------------
+// Forward from FP32 values: a block of 2 WS waves per (TR, coil, 32 WS
+// samples); waves, tiles and products as above. Phases and staged values of a
+// step are made by the vector units, held in registers and written to LDS in
+// fragment order once the step before has been multiplied; the row phases of
+// the sum come from a table. These blocks are short (one to four steps), so
+// each piece of code stands once in the loop: a phase is some 50 instructions,
+// and a first pass over the code costs as much as the work. (33 x 47, 4 coils,
+// 1120 TRs: with the phases inlined at every use 94 us, now 60.)
+// ------------------------------------------------------------------------
+template <int NT, int WS, bool COIL>
+__global__ __launch_bounds__(128 * WS) void nc_fwd_staged_kernel(
+    const float2* __restrict__ X, const int* __restrict__ keys, const int* __restrict__ ckeys,
+    const float2* __restrict__ coil,
+    const double* __restrict__ ax, const double* __restrict__ ay, const float2* __restrict__ data,
+    float2* __restrict__ out, double* __restrict__ red, int mode, int nx, int ny, int nv, int T, int C, int n_first,
+    int n_end, int nk, int KT)
+{
+    constexpr int MS = 32 * WS, NTH = 128 * WS;
+    constexpr int NI = (NT + WS - 1) / WS;   // pieces of 8 voxel values per thread and step
+    constexpr int KP = 20;                   // pitch of the row phases: two samples' 16 rows in different banks
+    __shared__ u4 As[4][MS / 16][64];        // after the last step: row phases [MS][KP]
+    __shared__ u4 Bs[4][2 * NT][64];
+    __shared__ float2 tab[8][MS];    // phases of 1, 2 and 4 columns, of 16, 1, 2 and 16 NT (a row wave's) rows
+    __shared__ float2 part[2][MS];   // row sums per row wave
+    __shared__ double rs[2 * WS];
+    static_assert(sizeof(As) >= KP * MS * sizeof(float2), "row phases");
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ws = wave % WS, wr = wave / WS;
+    const int slot = blockIdx.x >> 3;
+    const int kt = slot % KT, c = slot / KT % C;
+    const int n = n_first + slot / (KT * C) * 8 + (blockIdx.x & 7);
+    if (n >= n_end) return;
+    const int k0 = kt * MS;
+    const float2* Xn = X + (size_t)n * nv;
+    const float2* Cn = COIL ? coil + (size_t)c * nv : nullptr;
+    const int* kn = keys + (size_t)(n - n_first) * ny;
+    const int* kc = ckeys + (size_t)c * ny;
+    auto row_key = [&](int iy) { return kn[iy] + (coil != nullptr ? kc[iy] : kNoWeight); };
+    // Phase generation: this thread's sample and group of 8 columns (or of 4 rows).
+    const int gs = tid % MS, gg = tid / MS;
+    const bool sample = k0 + gs < nk;
+    const double ag = sample ? ax[(size_t)n * nk + k0 + gs] : 0.0, bg = sample ? ay[(size_t)n * nk + k0 + gs] : 0.0;
+    const int KS = (nx + 31) / 32, rows = 32 * NT;
+    const bool active = k0 + 32 * ws < nk;   // whole waves of samples past the end only stage
+    const unsigned abase = lds_addr(&As[0][2 * ws][lane]);
+    const unsigned bbase = lds_addr(&Bs[0][NT * wr][lane]);
+    u4* const aw = &As[0][gs >> 4][(gs & 15) + 16 * gg];
+    float2* const eyt = reinterpret_cast<float2*>(&As[0][0][0]);
+
+    for (int y0 = 0; y0 < ny; y0 += rows) {
+        // Piece i: row tile f = e / 64 of the pass, fragment lane e % 64. Rows
+        // past ny read the last one (their sums are dropped).
+        int brow[NI];
+        float bsc[NI];
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const int e = tid + NTH * i;
+            brow[i] = min(y0 + 16 * (e >> 6) + (e & 15), ny - 1);
+            bsc[i] = key_scale(row_key(brow[i]));
+        }
+        const int yl = y0 + 16 * NT * wr + (lane & 15);   // the lane's image rows in the sums: yl + 16 t
+        int rk[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) rk[t] = row_key(min(yl + 16 * t, ny - 1));
+        f4 pr[2][NT], pi[2][NT];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) pr[i][t] = pi[i][t] = f4{0.f, 0.f, 0.f, 0.f};
+        // Turn s makes step s's operands and multiplies step s - 1's.
+#pragma unroll 1
+        for (int s = 0; s <= KS; ++s) {
+            u4 an[4], bn[NI][4];
+            if (s < KS) {
+                float2 x[NI][8], cw[NI][8];
+#pragma unroll
+                    for (int i = 0; i < NI; ++i) {
+                        const int e = tid + NTH * i, c0 = 32 * s + 8 * ((e >> 4) & 3);
+                        if (NI * WS > NT && e >= 128 * NT) continue;
+                        const float2* p = Xn + (size_t)brow[i] * nx + c0;
+                        const float2* q = COIL ? Cn + (size_t)brow[i] * nx + c0 : nullptr;
+                        if (c0 + 8 <= nx) {
+                            struct __attribute__((packed, aligned(8))) V8 { float2 e[8]; };
+                            const V8 t = *reinterpret_cast<const V8*>(p);
+#pragma unroll
+                            for (int m = 0; m < 8; ++m) x[i][m] = t.e[m];
+                            if constexpr (COIL) {
+                                const V8 u = *reinterpret_cast<const V8*>(q);
+#pragma unroll
+                                for (int m = 0; m < 8; ++m) cw[i][m] = u.e[m];
+                            }
+                        } else {
+#pragma unroll
+                            for (int m = 0; m < 8; ++m) {
+                                x[i][m] = c0 + m < nx ? p[m] : make_float2(0.f, 0.f);
+                                if constexpr (COIL) cw[i][m] = c0 + m < nx ? q[m] : make_float2(0.f, 0.f);
+                            }
+                        }
+                    }
+                if (y0 == 0 && s == 0) {
+#pragma unroll 1
+                    for (int h = 0; h < 2; ++h) {
+                        const bool col = h == 0 && gg < 3;
+                        tab[4 * h + gg][gs] = phase_of(col ? ag : bg, h == 0 ? (col ? 1 << gg : 16) : (gg < 2 ? 1 + gg : 16 * NT));
+                    }
+                    asm volatile("s_waitcnt lgkmcnt(0)\n s_barrier" ::: "memory");
+                }
+                const int c0 = 32 * s + 8 * gg;
+                float2 base = phase_of(ag, c0 - nx / 2);
+                base.x *= kPhaseScale;
+                base.y *= kPhaseScale;
+                float2 off[8];
+                off[1] = tab[0][gs];
+                off[2] = tab[1][gs];
+                off[4] = tab[2][gs];
+                off[3] = cmul(off[1], off[2]);
+                off[5] = cmul(off[4], off[1]);
+                off[6] = cmul(off[4], off[2]);
+                off[7] = cmul(off[4], off[3]);
+                float2 e[8];
+#pragma unroll
+                for (int m = 0; m < 8; ++m) {
+                    e[m] = m == 0 ? base : cmul(base, off[m]);
+                    if (c0 + m >= nx) e[m] = make_float2(0.f, 0.f);
+                }
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                    unsigned h, l;
+                    split_h(e[2 * m].x, e[2 * m + 1].x, h, l);
+                    an[0][m] = h;
+                    an[1][m] = l;
+                    split_h(e[2 * m].y, e[2 * m + 1].y, h, l);
+                    an[2][m] = h;
+                    an[3][m] = l;
+                }
+#pragma unroll
+                for (int i = 0; i < NI; ++i)
+#pragma unroll
+                    for (int m = 0; m < 4; ++m) {
+                        float2 z[2];
+#pragma unroll
+                        for (int u = 0; u < 2; ++u) {
+                            z[u] = x[i][2 * m + u];
+                            if constexpr (COIL) z[u] = cmul(cw[i][2 * m + u], z[u]);
+                            z[u].x *= bsc[i];
+                            z[u].y *= bsc[i];
+                        }
+                        unsigned h, l;
+                        split_h(z[0].x, z[1].x, h, l);
+                        bn[i][0][m] = h;
+                        bn[i][1][m] = l;
+                        split_h(z[0].y, z[1].y, h, l);
+                        bn[i][2][m] = h;
+                        bn[i][3][m] = l;
+                    }
+            }
+            if (s > 0) {
+                if (active) {
+                    u4 a[2][4];
+                    read_frag4<(MS / 16) * 1024>(a[0], abase);
+                    read_frag4<(MS / 16) * 1024>(a[1], abase + 1024);
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) {
+                        u4 b[4];
+                        read_frag4<2 * NT * 1024>(b, bbase + t * 1024);
+                        const u4 nh = b[2] ^ 0x80008000u, nl = b[3] ^ 0x80008000u;   // -Xi
+#pragma unroll
+                        for (int i = 0; i < 2; ++i) {
+                            pr[i][t] = mma(a[i][0], b[0], pr[i][t]);
+                            pi[i][t] = mma(a[i][0], b[2], pi[i][t]);
+                            pr[i][t] = mma(a[i][2], nh, pr[i][t]);
+                            pi[i][t] = mma(a[i][2], b[0], pi[i][t]);
+                            pr[i][t] = mma(a[i][0], b[1], pr[i][t]);
+                            pi[i][t] = mma(a[i][0], b[3], pi[i][t]);
+                            pr[i][t] = mma(a[i][2], nl, pr[i][t]);
+                            pi[i][t] = mma(a[i][2], b[1], pi[i][t]);
+                            pr[i][t] = mma(a[i][1], b[0], pr[i][t]);
+                            pi[i][t] = mma(a[i][1], b[2], pi[i][t]);
+                            pr[i][t] = mma(a[i][3], nh, pr[i][t]);
+                            pi[i][t] = mma(a[i][3], b[0], pi[i][t]);
+                        }
+                    }
+                }
+                asm volatile("s_waitcnt lgkmcnt(0)\n s_barrier" ::: "memory");
+            }
+            if (s < KS) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) aw[q * (MS / 16) * 64] = an[q];
+#pragma unroll
+                for (int i = 0; i < NI; ++i) {
+                    const int e = tid + NTH * i;
+                    if (NI * WS > NT && e >= 128 * NT) continue;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) Bs[q][e >> 6][e & 63] = bn[i][q];
+                }
+                asm volatile("s_waitcnt lgkmcnt(0)\n s_barrier" ::: "memory");
+            }
+        }
+        // Phases of the pass's first 16 rows per sample, 4 rows per thread.
+        {
+            const float2 e = phase_of(bg, y0 + 4 * gg - ny / 2), r1 = tab[4][gs], r2 = tab[5][gs];
+            float2* t = &eyt[KP * gs + 4 * gg];
+            t[0] = e;
+            t[1] = cmul(e, r1);
+            t[2] = cmul(e, r2);
+            t[3] = cmul(e, cmul(r1, r2));
+        }
+        __syncthreads();
+        // s[k] += sum_iy Ey[k,iy] P[k,iy] over the lane's image rows.
+        if (active) {
+            float ri[NT];
+#pragma unroll
+            for (int t = 0; t < NT; ++t) ri[t] = unscale(rk[t]);
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int kl = 32 * ws + 16 * i + 4 * (lane >> 4) + r;
+                    float2 ey = eyt[KP * kl + (lane & 15)], sum = make_float2(0.f, 0.f);
+                    if (wr > 0) ey = cmul(ey, tab[6][kl]);
+                    const float2 st = tab[3][kl];
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) {
+                        if (yl + 16 * t < ny) {
+                            const float2 p = make_float2(ri[t] * pr[i][t][r], ri[t] * pi[i][t][r]);
+                            sum.x += ey.x * p.x - ey.y * p.y;
+                            sum.y += ey.x * p.y + ey.y * p.x;
+                        }
+                        if (t + 1 < NT) ey = cmul(ey, st);
+                    }
+                    sum.x = sum_row16(sum.x);
+                    sum.y = sum_row16(sum.y);
+                    if ((lane & 15) == 0) {
+                        if (y0 > 0) {
+                            sum.x += part[wr][kl].x;
+                            sum.y += part[wr][kl].y;
+                        }
+                        part[wr][kl] = sum;
+                    }
+                }
+        }
+        if (y0 + rows < ny) __syncthreads();   // the next pass writes As
+    }
+    __syncthreads();
+    double sq = 0.0;
+    if (tid < MS && sample) {
+        const size_t idx = ((size_t)c * T + n) * nk + k0 + tid;
+        float2 v = make_float2(part[0][tid].x + part[1][tid].x, part[0][tid].y + part[1][tid].y);
+        if (mode == 0) {
+            const float2 d = data[idx];
+            v = make_float2(d.x - v.x, d.y - v.y);
+            sq = (double)v.x * v.x + (double)v.y * v.y;
+        } else if (mode == 1) {
+            v = make_float2(-v.x, -v.y);
+        }
+        out[idx] = v;
+    }
+    if (mode == 0) {
+        for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o);
+        if (lane == 0) rs[wave] = sq;
+        __syncthreads();
+        // (waves from 64 samples on hold none)
+        if (tid == 0) red[((size_t)c * T + n) * KT + kt] = MS > 64 ? rs[0] + rs[1] : rs[0];
+    }
+}
+
+// ------------------------------------------------------------------------
 // Adjoint, V[n][j] = sum_c conj(C_c[j]) sum_k conj(E[n,k,j]) w_c[n,k]: a block
 // of 8 waves per (TR, 128 columns, 32 NT rows); wave (ws, wr) owns 32 columns
 // and NT 16-row tiles, K runs over the samples in steps of 32. Both operands
@@ -807,6 +1186,96 @@ Passes fwd_passes(const Dims& d, void* main_store, void* small)
 
 int fwd_grid(int nk, int recs) { return 8 * ceil_div(nk, NC_MS) * ceil_div(recs, 8); }
 
+// How the forward takes a problem: values split once (`split`) or staged from
+// FP32, sample waves per block, 16-row tiles per wave. J v in us, 4 coils, 1120
+// TRs unless said, 1 / 2 / 4 sample waves staged / split:
+//   split: its records are per TR and coil, T / n_coils TRs per launch, and its
+//     rows take a wave each, whatever their width: 24 x 24, 48 samples 62 / 71 /
+//     115 / 200; 101 x 90, 202 samples 838 / 742 / 620 / 704. From 129 columns on
+//     the splitting that every staged block repeats costs more (224 x 224, 448
+//     samples, one coil 1487 / 1155 / 1287 / 1016; 250 TRs 1505 / 1061 / 1061 /
+//     828), unless its launches leave CUs idle (160 x 160, 160 samples, 64 TRs 120
+//     / 99 / 115 / 127) or its rows fill a fraction of a block (200 x 24, 200
+//     samples, 250 TRs 120 / 153 / 155 / 194).
+//   one wave: few rows or samples (above; 24 x 200, 24 samples 157 / 187 / 304).
+//   two or four: the one that pads rows and samples to less; in between two for
+//     one coil (128 x 128, 128 samples 238 / 179 / 188), and with coils (whose
+//     blocks hold at most 32 rows per wave) four from two row passes of two on
+//     (128 x 128, 256 samples, 250 TRs 339 / 250 / 220; 64 x 64 242 / 182 / 212).
+struct FwdPlan {
+    bool split;
+    int ws, nt, kt;   // kt: sample tiles
+};
+FwdPlan fwd_plan(const Dims& d)
+{
+    auto tiles = [&](int most) { return ceil_div(d.ny, 32 * ceil_div(d.ny, most)); };
+    auto padded = [&](int ws, int most) {   // samples times rows, the last tiles' padding counted
+        return (long)ceil_div(d.nk, 32 * ws) * ws * ceil_div(d.ny, 32 * tiles(most)) * tiles(most);
+    };
+    FwdPlan p;
+    p.split = d.nx > 128 && (d.C == 1 || (d.ny > 32 && d.T * ceil_div(d.nk, NC_MS) >= 256));
+    if (p.split)
+        p.ws = 4;
+    else if (d.ny <= 32 || (d.nk <= 32 && (d.C > 1 || d.ny <= 64)))
+        p.ws = 1;
+    else if (d.C > 1)
+        p.ws = d.ny > 64 && padded(4, 128) <= padded(2, 64) ? 4 : 2;
+    else
+        p.ws = 10 * padded(4, 224) < 9 * padded(2, 128) ? 4 : 2;
+    if (ceil_div(d.nk, 32 * p.ws) > d.nx) p.ws = 4;   // the room for the partial sums of f
+    p.nt = p.split ? row_tiles(d.ny) : tiles(d.C > 1 ? 32 * p.ws : p.ws == 4 ? 224 : 64 * p.ws);
+    p.kt = ceil_div(d.nk, 32 * p.ws);
+    return p;
+}
+
+template <typename TT>
+hipError_t value_launch(const Dims& d, int mode_y, const TT* trains, const float* theta, const float* v,
+                        const uint8_t* mask, const float2* coil, float2* X, int* keys, int* ckeys, int n_first,
+                        int n_end, hipStream_t s)
+{
+    int LX = 1;
+    while (4 * LX < d.nx) LX *= 2;
+    // One TR per group while four leave CUs idle.
+    const int gx = ceil_div(d.ny, 256 / LX), nt = n_end - n_first;
+    const bool few = gx * ceil_div(nt, 4) < 1024;
+    const dim3 grid(gx, few ? nt : ceil_div(nt, 4));
+#define NC_V2(N, XT)                                                                                               \
+    nc_value_kernel<N, XT, TT><<<grid, 256, 0, s>>>(trains, theta, v, mask, coil, X, keys, ckeys, d.nx, d.ny,      \
+                                                    d.nv, d.T, d.C, n_first, n_end, LX)
+#define NC_V(N)                                                                                                    \
+    if (few) NC_V2(N, 1);                                                                                         \
+    else NC_V2(N, 4)
+    switch (mode_y) {
+    case 0: NC_V(1); break;
+    case 1: NC_V(4); break;
+    case 3: NC_V(3); break;
+    default: return hipErrorInvalidValue;
+    }
+#undef NC_V
+#undef NC_V2
+    return hipGetLastError();
+}
+
+template <int WS, bool COIL>
+hipError_t staged_launch(const Dims& d, const FwdPlan& p, const float2* X, const int* keys, const int* ckeys,
+                         const float2* coil, const double* ax, const double* ay, const float2* data, float2* out,
+                         double* red, int mode_x, int n_first, int n_end, hipStream_t s)
+{
+    constexpr int MOST = COIL ? WS : WS == 4 ? 7 : 2 * WS;   // of 16-row tiles per wave
+    const int grid = 8 * p.kt * d.C * ceil_div(n_end - n_first, 8);
+#define NC_FWD(N)                                                                                                  \
+    if constexpr (N <= MOST)                                                                                      \
+        if (p.nt == N) {                                                                                          \
+            nc_fwd_staged_kernel<N, WS, COIL><<<grid, 128 * WS, 0, s>>>(X, keys, ckeys, coil, ax, ay, data, out,   \
+                                                                        red, mode_x, d.nx, d.ny, d.nv, d.T, d.C,   \
+                                                                        n_first, n_end, d.nk, p.kt);               \
+            return hipGetLastError();                                                                             \
+        }
+    NC_FWD(1) NC_FWD(2) NC_FWD(3) NC_FWD(4) NC_FWD(5) NC_FWD(6) NC_FWD(7)
+#undef NC_FWD
+    return hipErrorInvalidValue;
+}
+
 }  // namespace
 
 int nc_adj_chunks(const Dims& d)
@@ -819,7 +1288,7 @@ int nc_adj_chunks(const Dims& d)
     return std::min({ceil_div(1024, ceil_div(d.nv, 512)), ceil_div(512, tiles), 32, d.T});
 }
 
-int nc_fwd_blocks(const Dims& d) { return d.C * d.T * ceil_div(d.nk, NC_MS); }
+int nc_fwd_blocks(const Dims& d) { return d.C * d.T * fwd_plan(d).kt; }
 
 hipError_t launch_nc_fwd(const Dims& d, int enc, int mode_y, int mode_x, const void* trains, bool f16,
                          const float* theta, const float* v, const float2* coil, const uint8_t* mask,
@@ -827,8 +1296,31 @@ hipError_t launch_nc_fwd(const Dims& d, int enc, int mode_y, int mode_x, const v
                          double* red, int* nred, hipStream_t s)
 {
     if (d.nx > 256 || (enc != 0 && enc != 1)) return hipErrorInvalidValue;
+    const FwdPlan plan = fwd_plan(d);
+    if (nred) *nred = nc_fwd_blocks(d);
+    if (!plan.split) {
+        float2* const Xv = static_cast<float2*>(X);
+        int* const keys = static_cast<int*>(small);
+        const int trs = std::min(d.T, 128 * d.nx - d.C);   // TRs whose keys fit beside the coils'
+        int* const ckeys = keys + (size_t)trs * d.ny;
+        for (int n = 0; n < d.T; n += trs) {
+            const int end = std::min(d.T, n + trs);
+            hipError_t e = f16 ? value_launch(d, mode_y, static_cast<const _Float16*>(trains), theta, v, mask, coil, Xv,
+                                              keys, ckeys, n, end, s)
+                               : value_launch(d, mode_y, static_cast<const float*>(trains), theta, v, mask, coil, Xv,
+                                              keys, ckeys, n, end, s);
+            if (e != hipSuccess) return e;
+#define NC_FWD2(W)                                                                                                 \
+    (coil != nullptr ? staged_launch<W, true>(d, plan, Xv, keys, ckeys, coil, ax, ay, data, out, red, mode_x, n, end, s) \
+                     : staged_launch<W, false>(d, plan, Xv, keys, ckeys, coil, ax, ay, data, out, red, mode_x, n, end, s))
+            e = plan.ws == 1 ? NC_FWD2(1) : plan.ws == 2 ? NC_FWD2(2) : NC_FWD2(4);
+#undef NC_FWD2
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
     const Passes p = fwd_passes(d, X, small);
-    const int KT = ceil_div(d.nk, NC_MS), nt = row_tiles(d.ny);
+    const int KT = plan.kt, nt = plan.nt;
     for (int c = 0; c < d.C; c += p.coils) {
         const int nc = std::min(p.coils, d.C - c);
         const float2* cc = coil == nullptr ? nullptr : coil + (size_t)c * d.nv;
@@ -856,7 +1348,6 @@ hipError_t launch_nc_fwd(const Dims& d, int enc, int mode_y, int mode_x, const v
             if (e != hipSuccess) return e;
         }
     }
-    if (nred) *nred = nc_fwd_blocks(d);
     return hipSuccess;
 }
 

@@ -46,7 +46,15 @@ __global__ __launch_bounds__(RB) void sum_partials_kernel(const double* __restri
 {
     __shared__ double sh[RB / 64];
     double v = 0.0;
-    for (int i = threadIdx.x; i < n; i += RB) v += p[i];
+    int i = threadIdx.x;
+    for (; i + 7 * RB < n; i += 8 * RB) {   // eight loads on their way, summed in order
+        double t[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) t[k] = p[i + k * RB];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v += t[k];
+    }
+    for (; i < n; i += RB) v += p[i];
     v = block_sum(v, sh);
     if (threadIdx.x == 0) *out = v;
 }
