@@ -1186,6 +1186,26 @@ Passes fwd_passes(const Dims& d, void* main_store, void* small)
 
 int fwd_grid(int nk, int recs) { return 8 * ceil_div(nk, NC_MS) * ceil_div(recs, 8); }
 
+// 16-row tiles per wave of the adjoint: as above while its blocks (one per TR,
+// 128 columns and 32 NT rows) fill the 256 CUs, else fewer rows per block where
+// that is faster. A block takes the time of its phases (as long as three row
+// tiles) and of its tiles; two on a CU take 1.4 times one's time, more in
+// proportion. J^H w in us, 64 TRs, the most rows / as chosen: 128 x 128, 4 coils,
+// 128 samples 162 / 93; 24 x 200, 8 coils, 48 samples 257 / 118; 224 x 224, one
+// coil, 448 samples 149 / 108; 250 TRs and more keep the most rows.
+int adj_tiles(const Dims& d)
+{
+    int best = 0;
+    long t_best = 0;
+    for (int passes = ceil_div(d.ny, 224); passes <= ceil_div(d.ny, 32); ++passes) {
+        const int nt = ceil_div(d.ny, 32 * passes);
+        const int k = ceil_div(d.T * ceil_div(d.nx, NCA_TX) * ceil_div(d.ny, 32 * nt), 256);
+        const long t = (3 + nt) * (k == 1 ? 10 : 7 * k);
+        if (best == 0 || 10 * t < 9 * t_best) t_best = t, best = nt;
+    }
+    return best;
+}
+
 // How the forward takes a problem: values split once (`split`) or staged from
 // FP32, sample waves per block, 16-row tiles per wave. J v in us, 4 coils, 1120
 // TRs unless said, 1 / 2 / 4 sample waves staged / split:
@@ -1356,7 +1376,7 @@ hipError_t launch_nc_adj(const Dims& d, int enc, int ntr, int chunks, const void
                          const float2* w, float2* V, float* apart, hipStream_t s)
 {
     if (enc != 0 && enc != 1) return hipErrorInvalidValue;
-    const int nt = row_tiles(d.ny), ntx = ceil_div(d.nx, NCA_TX);
+    const int ntx = ceil_div(d.nx, NCA_TX), nt = adj_tiles(d);
     const int tiles = ntx * ceil_div(d.ny, 32 * nt);
     const unsigned grid = 8u * tiles * ceil_div(d.T, 8);
 #define NC_ADJ(N)                                                                                                  \
