@@ -145,11 +145,15 @@ mrstat_status mrstat_create(const mrstat_problem *prob, mrstat_ctx *out);
  * read during the call only. The encoding phase is
  *     E[n,k,j] = exp(-2 pi i (kx (ix - nx/2) / nx + ky (iy - ny/2) / ny))
  * and every call of the context evaluates the voxel x sample contraction
- * directly on the matrix cores with the phases generated on the fly (FP32 and
- * split-BF16 both run as products of operands split into two FP16 parts each,
- * accurate as FP32 products; FP16 is refused); ky_line is ignored and n_read may be below
- * nx. The workspace (mrstat_workspace_bytes) then also holds the forward's
- * voxel values, complex FP32 [n_tr][nx ny]. Requirements as mrstat_create,
+ * directly on the matrix cores with the phases generated on the fly. FP32 and
+ * split-BF16 both run as products of operands split into two FP16 parts each
+ * (22 bits), whose error in norm is that of FP32 products or less; a voxel
+ * value more than 2^14 below the largest of its image row, or a sample as far
+ * below the largest of its TR and coil, keeps fewer bits (its error stays below
+ * 2^-36 of that largest). FP16 is refused; ky_line is ignored and n_read may be
+ * below nx. The workspace (mrstat_workspace_bytes) then also holds, in turn, the
+ * forward's voxel values and the adjoint's, complex FP32 [n_tr][nx ny] (wide
+ * images: the forward's as split pairs). Requirements as mrstat_create,
  * plus nx <= 256 (MRSTAT_ERR_SHAPE) and finite coordinates (MRSTAT_ERR_ARG). */
 mrstat_status mrstat_create_traj(const mrstat_problem *prob, const double *kx, const double *ky,
                                  mrstat_ctx *out);

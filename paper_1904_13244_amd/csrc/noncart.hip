@@ -17,7 +17,7 @@
 // of 64 samples and 64 x 32 voxels, as before; now): voxel values 0.31 / 0.25
 // ms, forward 3.60 / 0.75, adjoint with the trains 5.2 / 1.03 + 0.29 (the
 // split-BF16 option's tiles 0.31 + 1.39 / 2.94); errors against the FP64 sums
-// at 36 x 70, 40 spokes: J v 5.6e-7 / 5.6e-7, J^H w 6.3e-7 / 6.0e-7.
+// of the same trains: J v 3.2e-7 / 2.8e-7, J^H w 5.9e-7 / 4.1e-7.
 #include "mrstat_internal.h"
 
 #include <algorithm>
@@ -31,14 +31,19 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 
 // exp(-2 pi i a x) for an FP64 coefficient a and an integer position x: the
 // product is reduced to a fraction of a cycle in FP64, then sin and cos of pi
-// times twice that fraction in FP32.
-__device__ __forceinline__ float2 phase_of(double a, int x)
+// times twice that fraction in FP32. FINE turns the result by what the
+// fraction's rounding to FP32 left out (up to 9e-8): the phases of the forward
+// that many products share (offsets, row steps).
+template <bool FINE> __device__ __forceinline__ float2 phase_of(double a, int x)
 {
     const double t = a * (double)x;
-    const double f = t - rint(t);   // [-0.5, 0.5]
+    const double f = -2.0 * (t - rint(t));   // [-1, 1]
+    const float h = (float)f;
     float sn, cs;
-    sincospif((float)(-2.0 * f), &sn, &cs);
-    return make_float2(cs, sn);
+    sincospif(h, &sn, &cs);
+    if constexpr (!FINE) return make_float2(cs, sn);
+    const float d = 3.14159265f * (float)(f - (double)h);
+    return make_float2(fmaf(-d, sn, cs), fmaf(d, cs, sn));
 }
 
 __device__ __forceinline__ float2 cmul(float2 a, float2 b)
@@ -50,10 +55,11 @@ __device__ __forceinline__ float2 cmul(float2 a, float2 b)
 // Split operands. The products run on v_mfma_f32_16x16x32_f16: each FP32
 // operand is written as hi + lo, hi = fp16(v), lo = fp16(v - hi), and the
 // product as hi hi + hi lo + lo hi with FP32 accumulation. Operands are first
-// scaled by powers of two (phases by 2^8, voxel values so that the largest of
-// an image row lies in [2^10, 2^11)), which keeps hi and the leading bits of
-// lo away from fp16's subnormals: 22 bits per operand, a relative error of
-// about 2^-23 against 2^-24 for FP32 operands, without its K-long serial sums.
+// scaled by powers of two (phases by 2^14, voxel values so that the largest of
+// an image row, samples so that the largest of their TR and coil lies just
+// below 2^15), which keeps hi and lo away from fp16's subnormals: 22 bits for
+// everything within 2^14 of that largest, a relative error of about 2^-23
+// against 2^-24 for FP32 operands, without their K-long serial sums.
 // ------------------------------------------------------------------------
 typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
@@ -84,6 +90,14 @@ __device__ __forceinline__ float pow2_scale(unsigned m)
     const int e = min(141 - b, 112);
     return __uint_as_float((unsigned)(e + 127) << 23);
 }
+
+// The matrix unit's FP32 sums are off to one side on average, by a part of the
+// last place that adds up where sums over many rows or TRs follow. The scale
+// takes one sign or the other by row (forward) and TR (adjoint), in the
+// Thue-Morse order, which keeps step with no period of phases or pulses. 224 x 224, 1120 spokes of 448 samples: J^H w off by 7.8e-7 without,
+// 4.1e-7 with it (FP32 products 5.9e-7); J v with fine phases 3.3e-7 and 3.0e-7
+// (3.2e-7).
+__device__ __forceinline__ float unbias(float scale, int i) { return __popc(i) & 1 ? -scale : scale; }
 
 // Bits of |x|: their order is that of the magnitudes, NaN above infinity.
 __device__ __forceinline__ unsigned mag(float x) { return __float_as_uint(x) & 0x7fffffffu; }
@@ -247,7 +261,7 @@ __global__ __launch_bounds__(256) void nc_x_kernel(const TT* __restrict__ trains
                 mx = max(mx, max(mag(xr[c]), mag(xi[c])));
             }
             // A value that is not finite makes the row's (and so the TR's) sums so.
-            const float sc = pow2_scale(wave_max(mx));
+            const float sc = unbias(pow2_scale(wave_max(mx)), iy);
             if (k >= nt) continue;
             char* rec = X.at(cl * n_count + blockIdx.y * NC_XT + k);
             if (lane == 0) reinterpret_cast<float*>(rec + x_planes(ny, X.nx8))[iy] = 1.f / (sc * kPhaseScale);
@@ -308,11 +322,11 @@ __global__ __launch_bounds__(512) void nc_fwd_kernel(XStore X, const double* __r
     const double ag = k0 + gs < nk ? ax[(size_t)n * nk + k0 + gs] : 0.0;
     float2 off[8];
 #pragma unroll
-    for (int m = 1; m < 8; ++m) off[m] = phase_of(ag, m);
+    for (int m = 1; m < 8; ++m) off[m] = phase_of<true>(ag, m);
     u4 an[4];   // the next step's fragments of this thread
     auto make_a = [&](int s) {
         const int c0 = 32 * s + 8 * gg;
-        float2 base = phase_of(ag, c0 - nx / 2);
+        float2 base = phase_of<false>(ag, c0 - nx / 2);
         base.x *= kPhaseScale;
         base.y *= kPhaseScale;
         float2 e[8];
@@ -416,8 +430,8 @@ __global__ __launch_bounds__(512) void nc_fwd_kernel(XStore X, const double* __r
             for (int r = 0; r < 4; ++r) {
                 const int kl = 32 * ws + 16 * i + 4 * (lane >> 4) + r;
                 const double ayv = k0 + kl < nk ? ay[(size_t)n * nk + k0 + kl] : 0.0;
-                float2 ey = phase_of(ayv, yl - ny / 2), sum = make_float2(0.f, 0.f);
-                const float2 st = phase_of(ayv, 16);
+                float2 ey = phase_of<false>(ayv, yl - ny / 2), sum = make_float2(0.f, 0.f);
+                const float2 st = phase_of<true>(ayv, 16);
 #pragma unroll
                 for (int t = 0; t < NT; ++t) {
                     if (yl + 16 * t < ny) {
@@ -591,7 +605,7 @@ __global__ __launch_bounds__(128 * WS) void nc_fwd_staged_kernel(
     constexpr int KP = 20;                   // pitch of the row phases: two samples' 16 rows in different banks
     __shared__ u4 As[4][MS / 16][64];        // after the last step: row phases [MS][KP]
     __shared__ u4 Bs[4][2 * NT][64];
-    __shared__ float2 tab[8][MS];    // phases of 1, 2 and 4 columns, of 16, 1, 2 and 16 NT (a row wave's) rows
+    __shared__ float2 tab[8][MS];    // phases of 1, 2 and 4 columns, of 16, 1, 2, 16 NT (a row wave's) and 64 rows
     __shared__ float2 part[2][MS];   // row sums per row wave
     __shared__ double rs[2 * WS];
     static_assert(sizeof(As) >= KP * MS * sizeof(float2), "row phases");
@@ -628,7 +642,7 @@ __global__ __launch_bounds__(128 * WS) void nc_fwd_staged_kernel(
         for (int i = 0; i < NI; ++i) {
             const int e = tid + NTH * i;
             brow[i] = min(y0 + 16 * (e >> 6) + (e & 15), ny - 1);
-            bsc[i] = key_scale(row_key(brow[i]));
+            bsc[i] = unbias(key_scale(row_key(brow[i])), brow[i]);
         }
         const int yl = y0 + 16 * NT * wr + (lane & 15);   // the lane's image rows in the sums: yl + 16 t
         int rk[NT];
@@ -673,12 +687,12 @@ __global__ __launch_bounds__(128 * WS) void nc_fwd_staged_kernel(
 #pragma unroll 1
                     for (int h = 0; h < 2; ++h) {
                         const bool col = h == 0 && gg < 3;
-                        tab[4 * h + gg][gs] = phase_of(col ? ag : bg, h == 0 ? (col ? 1 << gg : 16) : (gg < 2 ? 1 + gg : 16 * NT));
+                        tab[4 * h + gg][gs] = phase_of<true>(col ? ag : bg, h == 0 ? (col ? 1 << gg : 16) : gg < 2 ? 1 + gg : gg == 2 ? 16 * NT : 64);
                     }
                     asm volatile("s_waitcnt lgkmcnt(0)\n s_barrier" ::: "memory");
                 }
                 const int c0 = 32 * s + 8 * gg;
-                float2 base = phase_of(ag, c0 - nx / 2);
+                float2 base = phase_of<false>(ag, c0 - nx / 2);
                 base.x *= kPhaseScale;
                 base.y *= kPhaseScale;
                 float2 off[8];
@@ -770,7 +784,7 @@ __global__ __launch_bounds__(128 * WS) void nc_fwd_staged_kernel(
         }
         // Phases of the pass's first 16 rows per sample, 4 rows per thread.
         {
-            const float2 e = phase_of(bg, y0 + 4 * gg - ny / 2), r1 = tab[4][gs], r2 = tab[5][gs];
+            const float2 e = phase_of<true>(bg, y0 + 4 * gg - ny / 2), r1 = tab[4][gs], r2 = tab[5][gs];
             float2* t = &eyt[KP * gs + 4 * gg];
             t[0] = e;
             t[1] = cmul(e, r1);
@@ -782,7 +796,7 @@ __global__ __launch_bounds__(128 * WS) void nc_fwd_staged_kernel(
         if (active) {
             float ri[NT];
 #pragma unroll
-            for (int t = 0; t < NT; ++t) ri[t] = unscale(rk[t]);
+            for (int t = 0; t < NT; ++t) ri[t] = unbias(unscale(rk[t]), yl + 16 * t);
 #pragma unroll
             for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -791,6 +805,8 @@ __global__ __launch_bounds__(128 * WS) void nc_fwd_staged_kernel(
                     float2 ey = eyt[KP * kl + (lane & 15)], sum = make_float2(0.f, 0.f);
                     if (wr > 0) ey = cmul(ey, tab[6][kl]);
                     const float2 st = tab[3][kl];
+                    float2 ey4 = ey;   // a step's error grows with each use: at most three
+                    if constexpr (NT > 4) ey4 = cmul(ey, tab[7][kl]);
 #pragma unroll
                     for (int t = 0; t < NT; ++t) {
                         if (yl + 16 * t < ny) {
@@ -798,7 +814,7 @@ __global__ __launch_bounds__(128 * WS) void nc_fwd_staged_kernel(
                             sum.x += ey.x * p.x - ey.y * p.y;
                             sum.y += ey.x * p.y + ey.y * p.x;
                         }
-                        if (t + 1 < NT) ey = cmul(ey, st);
+                        if (t + 1 < NT) ey = t == 3 ? ey4 : cmul(ey, st);
                     }
                     sum.x = sum_row16(sum.x);
                     sum.y = sum_row16(sum.y);
@@ -898,7 +914,7 @@ __global__ __launch_bounds__(512) void nc_adj_kernel(const float2* __restrict__ 
         if (tid < 192) {
             const int k = 32 * s + (tid & 31), q = tid >> 5;   // q: x1 x2 x4 y1 y2 y4
             const double a = k < nk ? (q < 3 ? axn[k] : ayn[k]) : 0.0;
-            tab[buf][q][tid & 31] = phase_of(-a, 1 << (q % 3));
+            tab[buf][q][tid & 31] = phase_of<false>(-a, 1 << (q % 3));
         }
     };
     for (int c = 0; c < C; ++c) {
@@ -918,7 +934,7 @@ __global__ __launch_bounds__(512) void nc_adj_kernel(const float2* __restrict__ 
         mx = wmax[0];
 #pragma unroll
         for (int i = 1; i < 8; ++i) mx = max(mx, wmax[i]);
-        const float sc = pow2_scale(mx);
+        const float sc = unbias(pow2_scale(mx), n);
 
         unsigned hv[4][4], gv[4][NT];   // split values: [plane][pair of positions]
         auto make = [&](int s) {
@@ -947,12 +963,12 @@ __global__ __launch_bounds__(512) void nc_adj_kernel(const float2* __restrict__ 
             };
             float2 t[8];
             steps(0, t);
-            float2 base = phase_of(-ak, x0 + 8 * pg - nx / 2);
+            float2 base = phase_of<false>(-ak, x0 + 8 * pg - nx / 2);
             base.x *= kPhaseScale;
             base.y *= kPhaseScale;
             line(base, t, hv, std::integral_constant<int, 8>{}, 0);
             steps(3, t);
-            base = cmul(phase_of(-bk, y0 + NR * pg - ny / 2), wv);
+            base = cmul(phase_of<false>(-bk, y0 + NR * pg - ny / 2), wv);
             if constexpr (NR <= 8) {
                 line(base, t, gv, std::integral_constant<int, NR>{}, 0);
             } else {
@@ -1216,7 +1232,8 @@ int adj_tiles(const Dims& d)
 //     samples, one coil 1487 / 1155 / 1287 / 1016; 250 TRs 1505 / 1061 / 1061 /
 //     828), unless its launches leave CUs idle (160 x 160, 160 samples, 64 TRs 120
 //     / 99 / 115 / 127) or its rows fill a fraction of a block (200 x 24, 200
-//     samples, 250 TRs 120 / 153 / 155 / 194).
+//     samples, 250 TRs 120 / 153 / 155 / 194). Just below, with coils, it needs
+//     full launches (128 x 128, 2 coils, 256 samples, 560 TRs 257 by four, 235).
 //   one wave: few rows or samples (above; 24 x 200, 24 samples 157 / 187 / 304).
 //   two or four: the one that pads rows and samples to less; in between two for
 //     one coil (128 x 128, 128 samples 238 / 179 / 188), and with coils (whose
@@ -1233,7 +1250,9 @@ FwdPlan fwd_plan(const Dims& d)
         return (long)ceil_div(d.nk, 32 * ws) * ws * ceil_div(d.ny, 32 * tiles(most)) * tiles(most);
     };
     FwdPlan p;
-    p.split = d.nx > 128 && (d.C == 1 || (d.ny > 32 && d.T * ceil_div(d.nk, NC_MS) >= 256));
+    const int kt4 = ceil_div(d.nk, NC_MS), fill = d.T * kt4;   // blocks of a launch of the split form, with coils
+    p.split = d.nx > 128 ? d.C == 1 || (d.ny > 32 && fill >= 256)
+                         : d.nx > 112 && d.ny > 112 && d.C > 1 && kt4 > 1 && fill >= 1024;
     if (p.split)
         p.ws = 4;
     else if (d.ny <= 32 || (d.nk <= 32 && (d.C > 1 || d.ny <= 64)))
