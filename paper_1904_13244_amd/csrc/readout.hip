@@ -622,6 +622,8 @@ int rd_adj_chunks(const Dims& d, int nc, int most)
     // Every chunk pays for its voxels' coefficients again (as long as 32 of its
     // TRs), and a lone workgroup on a CU takes three quarters of a pair's time.
     // 224 x 224, 1120 TRs, 16 terms: 9 chunks (882 workgroups) 587 us, 5 (490) 517.
+    // A TR counts once per coil: 160 x 160, 250 TRs, 8 coils, the whole call with
+    // 5 chunks (its one-coil best) 626 us, with 8 509.
     const int R = nc <= 16 ? rd_adj_rows<16>() : rd_adj_rows<20>();
     const int wg = ceil_div((d.ny + R - 1) / R * d.nx, 256);
     int best = most;
@@ -629,7 +631,7 @@ int rd_adj_chunks(const Dims& d, int nc, int most)
     for (int c = 1; c <= most; ++c) {
         const int per = ceil_div(d.T, c);
         if (ceil_div(d.T, per) != c) continue;
-        const int64_t k = ceil_div(wg * c, 256), t = (4 * (k / 2) + 3 * (k % 2)) * (per + 32);
+        const int64_t k = ceil_div(wg * c, 256), t = (4 * (k / 2) + 3 * (k % 2)) * ((int64_t)d.C * per + 32);
         if (t < t_best) t_best = t, best = c;
     }
     return best;
