@@ -80,22 +80,24 @@ __device__ __forceinline__ void clear_above(float (&f)[S], int base, int K)
 //
 // FP16 trains keep the row products with c^2 and s^2 (PLAIN): their values and
 // gradients carry the rounding of the trains, to which a changed FP32 recursion
-// adds its own (a gradient's norm moved by up to 2e-6); 2.40 and 0.56 ms.
-// Waves per SIMD that the states (3 S (1 + NTAN) registers) leave room for:
-constexpr int epg_waves(int s, int ntan) { return 3 * s * (1 + ntan) > 130 ? 2 : 3 * s * (1 + ntan) > 84 ? 3 : 4; }
+// adds its own (a gradient's norm moved by up to 2e-6); 2.38 ms with 3 tangents.
+// Waves per SIMD that the states (3 S (1 + NTAN) registers) leave room for; PLAIN
+// is faster without that bound (256^2, 32 orders, 256 TRs, 3 tangents 605 and 573
+// us) except where its states then spill (24 orders on 2 lanes, 842 and 575 us).
+constexpr int epg_waves(int s, int ntan, bool plain)
+{
+    if (plain) return s == 16 && ntan == 3 ? 2 : 1;
+    return 3 * s * (1 + ntan) > 130 ? 2 : 3 * s * (1 + ntan) > 84 ? 3 : 4;
+}
 
 // TRs per turn of the loop, whose shifts then need no register moves; the
 // largest states leave no room for a second copy.
 constexpr int epg_unroll(int s, int l, int ntan) { return 3 * s * (1 + ntan) > 150 ? 1 : l >= 4 && 3 * s * (1 + ntan) <= 50 ? 4 : 2; }
 
-
 template <int S, int L, int NTAN, bool MASKED, bool LIST, typename TT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(epg_waves(S, NTAN)))) void epg_kernel(const float* __restrict__ theta,
-                                                  const float2* __restrict__ seq,
-                                                  TT* __restrict__ out, int nv, int T,
-                                                  int K, SeqTimes st,
-                                                  const int* __restrict__ idx,
-                                                  const int* __restrict__ count)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(epg_waves(S, NTAN, sizeof(TT) == 2)))) void
+epg_kernel(const float* __restrict__ theta, const float2* __restrict__ seq, TT* __restrict__ out, int nv, int T, int K,
+           SeqTimes st, const int* __restrict__ idx, const int* __restrict__ count)
 {
     const int gt = blockIdx.x * blockDim.x + threadIdx.x;
     const int vox = gt / L;
@@ -344,6 +346,80 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(epg_waves(S
     }
 }
 
+// FP16 values at 16 orders per lane, the products of PLAIN in a kernel of their
+// own: 224^2 voxels, 256 TRs, 32 orders on 2 lanes 131 us (137 as a form of
+// epg_kernel), 64 orders on 4 lanes at 160^2 131 (140).
+template <int L, bool MASKED, bool LIST>
+__global__ __launch_bounds__(256) void epg_half_value_kernel(const float* __restrict__ theta,
+                                                             const float2* __restrict__ seq,
+                                                             _Float16* __restrict__ out, int nv, int T, int K,
+                                                             SeqTimes st, const int* __restrict__ idx,
+                                                             const int* __restrict__ count)
+{
+    constexpr int S = 16;
+    const int gt = blockIdx.x * blockDim.x + threadIdx.x;
+    const int vox = gt / L;
+    const int l = gt % L;
+    int j;
+    bool valid;
+    if constexpr (LIST) {
+        const int cnt = *count;
+        if ((int)(blockIdx.x * blockDim.x / L) >= cnt) return;   // uniform per block
+        valid = vox < cnt;
+        j = idx[valid ? vox : cnt - 1];
+    } else {
+        valid = vox < nv;
+        j = valid ? vox : nv - 1;   // keep every lane active for the lane moves
+    }
+    const bool lead = (l == 0), last = (l == L - 1);
+    const bool store = valid && lead;
+    const int base = l * S;
+
+    const float lnT1 = theta[j], lnT2 = theta[nv + j], B1 = theta[2 * nv + j];
+    const float rT1 = expf(-lnT1), rT2 = expf(-lnT2);   // 1/T1, 1/T2
+    const float tau1 = st.tr * rT1, tau2 = st.tr * rT2, tau2e = st.te * rT2;
+    const float E1 = expf(-tau1), E2 = expf(-tau2);
+    const float R1 = lead ? -expm1f(-tau1) : 0.f;       // regrowth of Z_0 only
+    const float E2e = expf(-tau2e);
+    const float taui = st.tinv * rT1;
+    const float E1i = expf(-taui), R1i = -expm1f(-taui);
+
+    float f[S], g[S], z[S];
+#pragma unroll
+    for (int i = 0; i < S; ++i) f[i] = g[i] = z[i] = 0.f;
+    if (lead) z[0] = R1i - E1i;   // ideal inversion, then relaxation over t_inv
+
+    _Float16* o0 = out + j;
+    for (int n = 0; n < T; ++n) {
+        const float2 sq = seq[n];
+        const float alpha = sq.x, sg = sq.y;
+        float sh, ch;
+        sincosf(0.5f * (B1 * alpha), &sh, &ch);
+        const float c2 = ch * ch, s2 = sh * sh;
+        const float sa = 2.f * sh * ch, ca = (ch - sh) * (ch + sh);
+        const float sgsa = sg * sa;
+        const float A = E2 * c2, B = E2 * s2, Cc = E2 * sgsa;
+        const float D = 0.5f * E1 * sgsa, G = E1 * ca;
+        {
+            const float rp = fmaf(c2, f[0], fmaf(s2, g[0], -sgsa * z[0]));
+            const float ke = sg * E2e;
+            if (store) o0[(size_t)n * nv] = (_Float16)(ke * rp);
+        }
+#pragma unroll
+        for (int i = 0; i < S; ++i) {
+            const float w = f[i] - g[i];
+            const float Cz = Cc * z[i];
+            const float nf = fmaf(A, f[i], fmaf(B, g[i], -Cz));
+            const float ng = fmaf(B, f[i], fmaf(A, g[i], Cz));
+            z[i] = fmaf(D, w, G * z[i]);
+            f[i] = nf; g[i] = ng;
+        }
+        z[0] += R1;
+        shift_orders<S, L>(f, g, lead, last);
+        if constexpr (MASKED) clear_above<S>(f, base, K);
+    }
+}
+
 template <int S, int L, int NTAN, bool LIST, typename TT>
 hipError_t launch_sl(const Dims& d, SeqTimes st, const float* theta, const float2* seq, TT* out,
                      const int* idx, const int* count, hipStream_t s)
@@ -351,12 +427,15 @@ hipError_t launch_sl(const Dims& d, SeqTimes st, const float* theta, const float
     const long threads = (long)d.nv * L;
     const int block = 256;
     const int grid = (int)((threads + block - 1) / block);
-    if (d.K == S * L)
-        epg_kernel<S, L, NTAN, false, LIST, TT><<<grid, block, 0, s>>>(theta, seq, out, d.nv, d.T, d.K,
-                                                                       st, idx, count);
-    else
-        epg_kernel<S, L, NTAN, true, LIST, TT><<<grid, block, 0, s>>>(theta, seq, out, d.nv, d.T, d.K,
-                                                                      st, idx, count);
+    auto run = [&](auto kernel) { kernel<<<grid, block, 0, s>>>(theta, seq, out, d.nv, d.T, d.K, st, idx, count); };
+    const bool whole = d.K == S * L;
+    if constexpr (S == 16 && NTAN == 0 && sizeof(TT) == 2) {
+        if (whole) run(&epg_half_value_kernel<L, false, LIST>);
+        else run(&epg_half_value_kernel<L, true, LIST>);
+    } else {
+        if (whole) run(&epg_kernel<S, L, NTAN, false, LIST, TT>);
+        else run(&epg_kernel<S, L, NTAN, true, LIST, TT>);
+    }
     return hipGetLastError();
 }
 
