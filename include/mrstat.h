@@ -199,9 +199,10 @@ mrstat_status mrstat_set_encoding(mrstat_ctx ctx, mrstat_enc enc);
 mrstat_status mrstat_set_train_precision(mrstat_ctx ctx, mrstat_trains prec);
 
 /* Tuning: lanes per voxel of the EPG kernel (the K states of a voxel are split
- * over a group of `lanes` lanes: 1, 2, 4 or 8; 0 = automatic choice). Results
- * do not depend on the choice beyond FP32 rounding order (they are identical
- * in practice: every order is updated by the same arithmetic). */
+ * over a group of `lanes` lanes: 1, 2, 4 or 8; 0 = automatic choice, by voxel
+ * count, K, trains and train precision). Results depend on the choice within
+ * FP32 rounding: up to 8 orders per lane relax Z by another product than 16
+ * orders per lane do (FP32 trains of both differ by 1e-6 at 128 TRs, normwise). */
 mrstat_status mrstat_set_epg_lanes(mrstat_ctx ctx, int32_t lanes);
 
 /* Readout dynamics (Discussion: the volumetric signal model follows T2 decay

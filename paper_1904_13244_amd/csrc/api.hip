@@ -321,7 +321,8 @@ mrstat_status simulate_into(mrstat_ctx ctx, const float* theta, void* out, int n
                                                        mlp_box_hi(ctx->surr), ctx->mask, ctx->fb_idx(),
                                                        ctx->fb_count(slot), s)));
     // A short list of scattered voxels is latency bound: spread each voxel's
-    // states over the most lanes unless a split was set explicitly.
+    // states to 4 orders per lane (8 lanes from 17 orders on) unless a split was
+    // set explicitly.
     if (ctx->iso.n > 0) {
         HIP_TRY(TRACED(kind, launch_iso(d, ctx->st, theta, ctx->dseq(), out, ntan, ctx->f16, ctx->iso,
                                         ctx->fb_idx(), ctx->fb_count(slot), s)));

@@ -24,6 +24,8 @@
 // order 0 times E2(TE). Recorded value: Im m = sg E2(TE) f_0.
 #include "mrstat_internal.h"
 
+#include <algorithm>
+
 namespace mrstat {
 namespace {
 
@@ -439,35 +441,46 @@ hipError_t launch_sl(const Dims& d, SeqTimes st, const float* theta, const float
     return hipGetLastError();
 }
 
-// Lanes per voxel where the caller left them open. A wave alone on its SIMD
-// issues a vector operation in 4 cycles, two together one in 2 (measured 1.67
-// and 0.87 ns per FMA), and a wave's time falls with its orders S: more lanes
-// while the chip is short of waves, fewer, with less work repeated per lane,
-// once it is full. w(l) = waves per SIMD at l lanes (256 CUs x 4). Measured in
-// us over 1120 TRs (512 for K <= 16), 3 tangents / values only:
-//   K 32: 128^2 (w(8) = 2) 2 lanes 1545 / 442, 4 lanes 888 / 273, 8 lanes 621 / 223;
-//         160^2 (3.1) 2 lanes 1557 / 443, 4 lanes 983 / 277, 8 lanes 1099 / 349;
-//         224^2 (w(2) = 1.5) 2 lanes 1776 / 453, 4 lanes 1923 / 481;
-//         320^2 (3.1) 2 lanes 3723 / 883, 4 lanes 3332 / 843.
-//   K 16: 128^2 (w(8) = 2) 4 lanes 263 / 104, 8 lanes 225 / 94;
-//         181^2 (w(4) = 2) 2 lanes 426 / 162, 4 lanes 296 / 107; 224^2 465 / 162 and 510 / 166.
-//   K 8:  181^2 (w(4) = 2) 2 lanes 293 / 134, 4 lanes 233 / 98; 224^2 314 / 134 and 365 / 139.
-//   K 64: 128^2 (w(8) = 2) 4 lanes 721 / 179, 8 lanes 476 / 134; 181^2 (w(4) = 2)
-//         819 / 183 and 880 / 227; 224^2 1585 / 344 and 1429 / 367.
-int auto_lanes(const Dims& d, int ntan)
+// Lanes per voxel where the caller left them open: those with the least orders
+// per lane S times waves per SIMD w (of 256 CUs x 4), both with what comes on
+// top. A lane's time has a part that does not shrink with its orders (the sines;
+// for values, which leave little else, more, and with FP32 trains shared by four
+// lanes or more); two waves on a SIMD take 1.4 times one's time (one alone issues
+// a vector operation in 4 cycles, two together one in 2), more in proportion; 16
+// orders leave room for fewer waves. Near ties go to fewer lanes. Measured over
+// 256 TRs, us with 1 / 2 / 4 / 8 lanes, FP32 trains with 3 tangents; values; FP16
+// trains with 3 tangents; values:
+//   K 8   96^2    179  150  107;   71  68  48;   233 181 143;   85  82  69
+//         256^2   188  178  194;   72  79  74;   237 221 260;   87  83 105
+//         320^2   220  294  305;   78 115 110;   301 362 404;   91 121 155
+//   K 16  128^2   324  219  134  123;   93  84  56  52;   388 267 188 162;  121  91  77  69
+//         200^2   329  246  217  230;   94  92  71  85;   394 342 296 309;  121  96 101 120
+//         320^2   379  454  439  537;  106 145 136 189;   513 607 585 704;  134 157 187 262
+//   K 32  144^2        365  255  216;      112  70  72;       431 342 300;      122 106 100
+//         224^2        418  458  433;      117 115 134;       559 600 579;      137 160 186
+//         320^2        806  737  777;      206 189 237;      1071 987 1032;     236 256 324
+//   K 64  200^2             716  540;           143 141;            885 721;          195 196
+//         256^2             821  838;           179 215;           1077 1107;         246 291
+int auto_lanes(const Dims& d, int ntan, bool f16)
 {
-    auto full = [&](int l, int w) { return (long)d.nv * l > 65536L * w; };   // w(l) > w
-    if (d.K <= 8) return full(4, 2) ? 2 : 4;
-    if (d.K <= 16) return !full(8, 2) ? 8 : full(4, 2) ? 2 : 4;
-    if (d.K <= 32) return !full(8, 2) ? 8 : full(2, 1) && !full(2, 2) ? 2 : 4;
-    return !full(8, 2) || (full(4, 2) && ntan == 3) ? 8 : 4;
+    const int most = d.K <= 8 ? 4 : 8, orders = d.K <= 8 ? 8 : d.K <= 16 ? 16 : d.K <= 32 ? 32 : 64;
+    int best = 0;
+    double t_best = 0.0;
+    for (int l = std::max(1, orders / 16); l <= most; l *= 2) {
+        const int s = orders / l, w = (int)(((long)d.nv * l + 65535) / 65536);
+        const double top = ntan > 0 ? 1.8 : f16 ? 5.2 : l < 4 ? 7.5 : 4.5;
+        const double full = s < 16 || ntan == 0 ? 0.0 : ntan == 3 ? 1.6 : 1.3;
+        const double t = (s + top + full) * (w > 1 ? w : ntan > 0 ? 1.45 : 1.6);
+        if (best == 0 || t < 0.98 * t_best) t_best = t, best = l;
+    }
+    return best;
 }
 
 template <int NTAN, bool LIST, typename TT>
 hipError_t launch_any(const Dims& d, SeqTimes st, const float* theta, const float2* seq,
                       TT* out, int lanes, const int* idx, const int* count, hipStream_t s)
 {
-    if (lanes == 0) lanes = auto_lanes(d, NTAN);
+    if (lanes == 0) lanes = auto_lanes(d, NTAN, sizeof(TT) == 2);
     const int K = d.K;
 #define SL(S_, L_) launch_sl<S_, L_, NTAN, LIST, TT>(d, st, theta, seq, out, idx, count, s)
     if (K <= 8) {
