@@ -977,14 +977,18 @@ bool infer_fused_supported(int width, int depth) { return (width == 64 || width 
 hipError_t launch_mlp_infer(int width, int tile, const InferArgs& a, hipStream_t s)
 {
     // Width 256, trains in FP32: beyond 64 voxels per CU the whole network per
-    // tile of 128 or 208 voxels, whichever pads the rounds of 256 tiles to
-    // fewer voxels. 1120 TRs, us with 64-voxel workgroups / tiles of 128 / 208:
-    // 16384 voxels 140 / 172 / 222, 32768 222 / 193 / 249, 50176 414 / 374 / 283,
-    // 65536 423 / 373 / 491, 102400 738 / 743 / 599; 128 TRs: 50 / 68 / 85,
-    // 75 / 66 / 88, 127 / 121 / 89, 130 / 122 / 164, 228 / 235 / 168.
+    // tile of 128 or 208 voxels, whichever takes less time over its rounds of 256
+    // tiles: a voxel takes a tenth less in tiles of 208, which share each read of
+    // the weights. 1120 TRs, us with 64-voxel workgroups / tiles of 128 / 208:
+    // 16384 voxels 140 / 172 / 222, 32768 231 / 201 / 252, 49216 402 / 375 / 285,
+    // 65536 428 / 373 / 493, 65600 507 / 524 / 510, 90112 617 / 578 / 558, 98368
+    // 717 / 720 / 571, 131072 852 / 733 / 791, 180224 1210 / 1146 / 1153, 262144
+    // 1708 / 1529 / 1372; 128 TRs: 50 / 68 / 85, 82 / 77 / 94, 134 / 128 / 95,
+    // 138 / 130 / 173, 171 / 176 / 173, 197 / 187 / 176, 233 / 236 / 180,
+    // 266 / 253 / 253, 385 / 380 / 359, 519 / 496 / 448.
     if (tile == 0 && width == 256 && !a.f16 && a.n > 64 * 256) {
         auto rounds = [&](int nv) { return ceil_div(ceil_div(a.n, nv), 256); };
-        if (rounds(208) * 208 <= rounds(128) * 128)
+        if (rounds(208) * 208 <= 1.1 * (rounds(128) * 128))
             mlp_hidden_kernel<208, true><<<std::min(ceil_div(a.n, 208), 256), 512, 0, s>>>(a);
         else
             mlp_hidden_kernel<128, true><<<std::min(ceil_div(a.n, 128), 256), 512, 0, s>>>(a);
