@@ -61,8 +61,11 @@ __device__ __forceinline__ float gelu_grad(float z)
 // layer and loss 84 us (123; it reads and writes 147 MB), its weight gradient
 // 66, its input gradient 61 (about 260), a hidden weight gradient 11 (about 60),
 // row sums 0 (50); the whole call 372 us (820).
-// Requirements (checked on the host): K, M (when TA), N (when !TB) and the
-// leading dimensions are multiples of 8; 16-byte aligned bases.
+// Requirements, checked where it is launched: 16-byte aligned operands, K, M
+// (when TA) and the operands' leading dimensions multiples of 8. N may be ragged
+// where B's rows (!TB) reach to its next multiple of 8: the columns past N are
+// read, enter no other column and are dropped; the epilogues that store four
+// values at once (weight gradients, GELU') take multiples of 4.
 // ------------------------------------------------------------------------
 constexpr int TK = 64;
 
@@ -918,6 +921,10 @@ int loss_tiles(int M, int N) { return loss_wide(M, N) ? ceil_div(N, 128) * ceil_
 
 hipError_t launch_gemm_bf16(bool ta, bool tb, int epi, const GemmArgs& g, hipStream_t s)
 {
+    const bool whole = epi == EPI_STORE_F32 || epi == EPI_GELU_BWD;
+    if (((uintptr_t)g.A | (uintptr_t)g.B) % 16 || (g.lda | g.ldb | g.K | (ta ? g.M : 0)) % 8 ||
+        (!tb && g.ldb < 8 * (int64_t)ceil_div(g.N, 8)) || (whole && (g.N | g.ldo) % 4))
+        return hipErrorInvalidValue;
     // Splits over K: two workgroups per CU, 256 of K each at least, as many as g.part holds.
     int nz = 1;
     const int64_t out = (int64_t)g.M * g.N + (g.rowsum ? g.M : 0);
