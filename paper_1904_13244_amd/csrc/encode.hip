@@ -328,7 +328,7 @@ void ystage_fwd_wide_kernel(
 }
 
 // ------------------------------------------------------------------------
-// Forward y-stage with coils (CC = 8 or 16 coil slots): a block of CW waves
+// Forward y-stage with coils (CC = 4, 8 or 16 coil slots): a block of CW waves
 // takes TB TRs, XW columns and a slab of rows; its waves walk the rows (one
 // row of 64 columns, or two of 32 per wave and step), load each voxel's
 // weights and coil sensitivities (from L2: the blocks of neighbouring TRs
@@ -708,7 +708,7 @@ __global__ __launch_bounds__(NWA * 64) void ystage_adj_wide_kernel(
 }
 
 // ------------------------------------------------------------------------
-// Adjoint y-stage with coils (CC = 8 or 16 coil slots). A block of CW waves
+// Adjoint y-stage with coils (CC = 4, 8 or 16 coil slots). A block of CW waves
 // covers XW columns and two rows (of 64 columns; two of 32 twice) per wave, so
 // each TR's W rows of all coils (CC x XW complex) are staged once in LDS and
 // used by every row of the block instead of being fetched per voxel; TR
@@ -1474,11 +1474,8 @@ hipError_t fwd_R(const Dims& d, const YPlan& p, const TT* trains, const float* t
             trains, theta, v, mask, eytab, U, d.nx, d.ny, d.nv, d.T, p.fwd_tr16);               \
         return hipGetLastError();                                                               \
     }
-            FWD16_CASE(1, 1) FWD16_CASE(1, 2) FWD16_CASE(1, 3) FWD16_CASE(1, 4)
-            FWD16_CASE(2, 1) FWD16_CASE(2, 2) FWD16_CASE(2, 3) FWD16_CASE(2, 4)
-            FWD16_CASE(4, 1) FWD16_CASE(4, 2) FWD16_CASE(4, 3) FWD16_CASE(4, 4)
-            FWD16_CASE(8, 1) FWD16_CASE(8, 2) FWD16_CASE(8, 3) FWD16_CASE(8, 4)
-            FWD16_CASE(16, 1) FWD16_CASE(16, 2) FWD16_CASE(16, 3) FWD16_CASE(16, 4)
+            FWD16_CASE(1, 1) FWD16_CASE(1, 2) FWD16_CASE(2, 1) FWD16_CASE(2, 2) FWD16_CASE(4, 1)
+            FWD16_CASE(4, 2) FWD16_CASE(8, 1) FWD16_CASE(8, 2) FWD16_CASE(16, 1) FWD16_CASE(16, 2)
 #undef FWD16_CASE
             return hipErrorInvalidValue;
         }
@@ -1553,11 +1550,6 @@ hipError_t adj_launch(const Dims& d, const YPlan& p, const TT* trains, const flo
         const dim3 grid(ceil_div(d.nx, xw), ceil_div(d.ny, br), p.adj_chunks);
         const size_t lds = (size_t)2 * NBA * (CC * xw + br) * sizeof(float2);
         auto go = [&](auto kernel) {
-            hipError_t e = hipSuccess;
-            if (lds > 65536)
-                e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            if (e != hipSuccess) return e;
             kernel<<<grid, CW * 64, lds, s>>>(trains, coil, mask, eytab, W, apart, d.nx, d.ny, d.nv, d.T, d.C,
                                               p.adj_per_chunk);
             return hipGetLastError();
@@ -1579,15 +1571,13 @@ hipError_t adj_launch(const Dims& d, const YPlan& p, const TT* trains, const flo
 YPlan make_yplan(const Dims& d)
 {
     YPlan p{};
-    // Forward: rows per block 32 R with R <= 4 (one coil; more rows per lane
-    // spill registers in the 1024-thread block) or <= 2 / 1 with coils; the
-    // rows are split into nby balanced blocks whose partial sums of U are
-    // added by a small kernel.
-    const int rmax = d.C == 1 ? 4 : (d.C <= 8 ? 2 : 1);
-    p.nby = ceil_div(d.ny, 32 * rmax);
+    // Forward, one coil: rows per block 32 R with R <= 4 (more rows per lane
+    // spill registers in the 1024-thread block); the rows are split into nby
+    // balanced blocks whose partial sums of U are added by a small kernel.
+    p.nby = ceil_div(d.ny, 128);
     p.r_fwd = ceil_div(d.ny, 32 * p.nby);
     // TRs per block: the chunk's per-wave sums live in LDS (at most 64 KB).
-    p.fwd_tr = d.C == 1 ? 16 : (d.C <= 8 ? 2 : 1);
+    p.fwd_tr = 16;
     // Coils: row slabs of the forward, of 64 rows at least (32 with 9 to 16 coils).
     p.nbyc = ceil_div(d.ny, d.C <= 8 ? 64 : 32);
     // One-row-per-wave layout (FP16 trains, one coil): g16 column groups of
@@ -1619,10 +1609,8 @@ YPlan make_yplan(const Dims& d)
     p.nbyw = std::min(d.ny, std::max(8, ceil_div(d.ny, 256)));   // <= 256 rows per slab
     p.roww = ceil_div(d.ny, p.nbyw);
     p.nbyw = ceil_div(d.ny, p.roww);
-    // Adjoint: one row per lane (8 rows per block) and 8 TR chunks: enough
-    // blocks in flight to stream the trains near the HBM limit, with partial
-    // sums of 8 chunks x 8 floats per voxel.
-    p.r_adj = 1;
+    // Adjoint: TR chunks, enough blocks in flight to stream the trains near the
+    // HBM limit, with partial sums of 8 floats per chunk and voxel.
     // One coil: 9 chunks (measured at 224 x 224, 1120 TRs, per chunk count
     // 4 / 5 / 8 / 9 / 12: FP16 wide kernel 92 / 104 / 96 / 92 / 98 us, FP32
     // 183 / 162 / 171 / 162 / 169 us; inside GN steps, four FP16 trains:

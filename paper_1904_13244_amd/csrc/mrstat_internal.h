@@ -99,10 +99,9 @@ hipError_t launch_iso(const Dims& d, SeqTimes st, const float* theta, const floa
 
 // Tiling of the encoding kernels, chosen per problem on the host.
 struct YPlan {
-    int r_fwd;        // forward y-stage: row steps per lane (32 r_fwd rows per block)
-    int nby;          // forward row blocks (partial sums of U when > 1)
+    int r_fwd;        // forward y-stage, one coil: row steps per lane (32 r_fwd rows per block)
+    int nby;          // its row blocks (partial sums of U when > 1)
     int fwd_tr;       // TRs per forward block
-    int r_adj;        // adjoint y-stage: row steps per lane (8 r_adj rows per block)
     int adj_chunks;   // TR chunks of the adjoint y-stage (partial sums per chunk)
     int adj_per_chunk;
     int ksplit_adj;   // split-K of the adjoint x-GEMM (partial W outputs)
