@@ -87,11 +87,13 @@ def measured_traffic(kind):
     """HBM bytes per launch from the committed rocprofv3 FETCH_SIZE/WRITE_SIZE
     summary, or None when the kernel source changed since it was taken."""
     import hashlib
-    src = os.path.join(ROOT, "paper_1904_13244_amd", "csrc", "encode.hip")
+    # The adjoint's kind also holds the CG product in one pass over the trains.
+    files = ["encode.hip", "normal.hip"] if kind.startswith("ystage_adj") else ["encode.hip"]
     summary = os.path.join(ROOT, "profiles", "hbm_traffic_224x224_1120tr.txt")
     if not os.path.exists(summary):
         return None
-    sha = hashlib.sha256(open(src, "rb").read()).hexdigest()[:16]
+    sha = hashlib.sha256(b"".join(open(os.path.join(ROOT, "paper_1904_13244_amd", "csrc", f), "rb").read()
+                                  for f in files)).hexdigest()[:16]
     for line in open(summary):
         f = line.split()
         if len(f) == 4 and f[0] == "TRAFFIC" and f[1] == kind and f[2] == sha:
