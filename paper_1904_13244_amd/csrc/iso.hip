@@ -152,6 +152,7 @@ hipError_t iso_lanes(const Dims& d, SeqTimes st, const float* theta, const float
 // Lanes per voxel: a wave's time is that of its slots and half a slot for the
 // sums and stores, and a SIMD takes two waves in the time of one, more in
 // proportion. 67 x 53 voxels, 16 isochromats, 210 TRs: 16 lanes 91 us, 4 lanes 189 us.
+// An index list, whose length only the device knows, takes 4 (not measured at others).
 template <bool LIST, typename TT>
 hipError_t iso_typed(const Dims& d, SeqTimes st, const float* theta, const float2* seq, TT* out, int ntan,
                      const IsoProfile& prof, const int* idx, const int* count, hipStream_t s)
