@@ -83,13 +83,14 @@ __device__ __forceinline__ void clear_above(float (&f)[S], int base, int K)
 // The lane moves stay shuffles through LDS, a unit that is idle here: as DPP
 // moves they take vector slots and waits (3 tangents 2.03 ms instead of 1.78).
 // 224^2 voxels, 32 orders, 1120 TRs, 2 lanes: 1.78 ms with 3 tangents and
-// 0.45 ms for values (coefficients c^2, s^2 and their derivatives for every
-// row, sines per lane, one TR per turn: 2.13 and 0.52); 128^2 with 2 tangents, at
-// the lanes chosen below, 0.45 and 0.22 ms (1.24 and 0.52 with 2 lanes).
+// 0.45 ms for values in launches that follow one another, 1.91 and 0.49 inside
+// GN steps (coefficients c^2, s^2 and their derivatives for every row, sines per
+// lane, one TR per turn: 1.98 to 2.13 and 0.52); 128^2 with 2 tangents, at the
+// lanes chosen below, 0.44 and 0.21 ms in GN steps (1.24 and 0.52 with 2 lanes).
 //
 // FP16 trains keep the row products with c^2 and s^2 (PLAIN): their values and
 // gradients carry the rounding of the trains, to which a changed FP32 recursion
-// adds its own (a gradient's norm moved by up to 2e-6); 2.38 ms with 3 tangents.
+// adds its own (a gradient's norm moved by up to 2e-6); 2.39 ms with 3 tangents.
 // Waves per SIMD that the states (3 S (1 + NTAN) registers) leave room for; PLAIN
 // is faster without that bound (256^2, 32 orders, 256 TRs, 3 tangents 605 and 573
 // us) except where its states then spill (24 orders on 2 lanes, 842 and 575 us).
