@@ -200,9 +200,10 @@ mrstat_status mrstat_set_train_precision(mrstat_ctx ctx, mrstat_trains prec);
 
 /* Tuning: lanes per voxel of the EPG kernel (the K states of a voxel are split
  * over a group of `lanes` lanes: 1, 2, 4 or 8; 0 = automatic choice, by voxel
- * count, K, trains and train precision). Results depend on the choice within
- * FP32 rounding: up to 8 orders per lane relax Z by another product than 16
- * orders per lane do (FP32 trains of both differ by 1e-6 at 128 TRs, normwise). */
+ * count, K, trains and train precision). Splits of up to 8 orders per lane give
+ * the same FP32 trains; 16 orders per lane relax Z by another product, and the
+ * trains of the two differ by FP32 rounding (1e-6 to 3e-6 normwise at 128 to
+ * 1120 TRs), so a voxel's trains depend that far on the image's size too. */
 mrstat_status mrstat_set_epg_lanes(mrstat_ctx ctx, int32_t lanes);
 
 /* Readout dynamics (Discussion: the volumetric signal model follows T2 decay
@@ -399,7 +400,8 @@ typedef enum {
     MRSTAT_K_YFWD_JV = 3,    /* forward y-stage of J v (four trains, or three with B1 fixed) */
     MRSTAT_K_XFWD = 4,       /* forward x-stage GEMM (+ residual epilogue) */
     MRSTAT_K_XADJ = 5,       /* adjoint x-stage GEMM */
-    MRSTAT_K_YADJ = 6,       /* adjoint y-stage (train streaming) */
+    MRSTAT_K_YADJ = 6,       /* adjoint y-stage (train streaming); one coil: also the CG product in one
+                                pass over the trains, n_cg launches beside the gradient's one */
     MRSTAT_K_FINISH = 7,     /* gradient assembly from the adjoint partials */
     MRSTAT_K_VECTOR = 8,     /* CG / line-search / CGLS vector kernels and reductions */
     MRSTAT_K_SURR = 9,       /* surrogate inference of the linearisation's trains (+ box test) */
